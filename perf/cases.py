@@ -74,7 +74,7 @@ def listed():
         # magnetisation and susceptibility of random graphs from samples of q
         _case("susceptibility", "rrg", 128, 2048, "fp32", insts=2, name="susceptibility_rrg128"),
         # the large sparse graph at a large width: messages of up to 2^18 entries
-        _case("adjoint", "rrg", 1000, 64, "fp32", w_u=18, name="adjoint_rrg1000_w18"),
+        _case("autograd", "rrg", 1000, 64, "fp32", w_u=18, name="autograd_rrg1000_w18"),
     ]
 
 
@@ -114,11 +114,11 @@ def draw(rng):
         return _case(op, model, size, _log_int(rng, 50, 8192),
                      rng.choice(["fp32", "split", "bf16", "fp64"]), insts=rng.randint(1, 3))
     if op == "adjoint":
+        return _case(op, model, size, _log_int(rng, 100, 4096), "fp64", insts=rng.randint(1, 2))
+    if op == "autograd":
         if rng.random() < 0.3:
             return _case(op, "rrg", 2 * rng.randint(300, 500), rng.randint(8, 64), "fp32",
                          w_u=rng.randint(15, 18))
-        return _case(op, model, size, _log_int(rng, 100, 4096), "fp64", insts=rng.randint(1, 2))
-    if op == "autograd":
         return _case(op, model, size, _log_int(rng, 100, 4096), rng.choice(["fp32", "split"]),
                      insts=rng.randint(1, 3))
     if model == "lattice":
