@@ -145,7 +145,19 @@ struct tnvan_net {
   std::vector<int64_t> sample_off, spin_off;
   int64_t B_total = 0, spin_total = 0;
   DBuf d_sample_off, d_B, d_spin_off, d_spin_base, d_edge_base;
-  TileCache tc_fwd, tc_bwd;
+  TileCache tc_fwd, tc_bwd, tc_mom;
+  // every instance off the chain kernels runs the level kernels (sweep.h):
+  // the schedule per mode (forward, adjoint, jets) for its tile size
+  struct SweepTab {
+    int key = -1;               // tile the schedule was asked for
+    int tile = 0;               // samples per tile
+    int waves = 0;              // waves per workgroup
+    bool glob = false;          // arena in device memory
+    size_t lds = 0;             // 0: no tile of that size fits
+    int64_t arena = 0;          // entries per sample of the largest arena
+    DBuf insts, prog, lanes, close;
+  } sw[3];
+  bool sweep = false;
   int S_fwd = 1, S_bwd = 1;
   bool glob_fwd = false, glob_bwd = false;
   size_t lds_fwd = 0, lds_bwd = 0;
@@ -544,6 +556,7 @@ tnvan_status set_batch(tnvan_net *net, const int64_t *n_samples) {
   net->nkey = key;
   net->tc_fwd.key.clear();
   net->tc_bwd.key.clear();
+  net->tc_mom.key.clear();
   net->skey.clear();
   net->ckey.clear();
   return TNVAN_OK;
@@ -703,6 +716,89 @@ tnvan_status ensure_chain_tasks(tnvan_net *net) {
   return TNVAN_OK;
 }
 
+// The schedule of the level kernels of `mode` for the current batch, with
+// req samples per tile (0: the default rule); *ok false when the net has
+// other programs or no such tile fits the LDS: the step-by-step kernel runs.
+//
+// Tiles by default: the largest that still leave 512 workgroups (two per
+// CU), or 256 for tiles of two, at most two for the adjoint, whose joint
+// weights fill the LDS, and eight else.  A larger tile issues fewer
+// instructions per sample, more workgroups hide the tree's latency: on 4096
+// samples of a 256-spin random graph the forward pass took 252 / 169 / 173 /
+// 135 us at 1 / 2 / 4 / 8 samples and the adjoint 1083 / 773 / 1159 us at
+// 1 / 2 / 4; on 512 samples 46 / 38 / 45 / 81 and 194 / 198 / 266 us.
+// The forward arena is in LDS while two workgroups per CU fit, else in
+// device memory with tiles of eight (135 against 173 us in LDS at four), or
+// with smaller tiles where the batch has no 512 tiles of eight.
+tnvan_status ensure_sweep(tnvan_net *net, int mode, int req, bool *ok) {
+  *ok = false;
+  if (!net->sweep || req > kSweepTile) return TNVAN_OK;
+  tnvan_net::SweepTab &t = net->sw[mode];
+  const int rs = net->rs();
+  auto tiles = [&](int S) {
+    int64_t n = 0;
+    for (int q = 0; q < net->n_inst; ++q)
+      if (!net->use_chain[q]) n += (net->nkey[q] + S - 1) / S;
+    return n;
+  };
+  std::vector<int32_t> run(net->n_inst);
+  for (int q = 0; q < net->n_inst; ++q) run[q] = !net->use_chain[q];
+  SweepPlan plan;
+  const int waves = kSweepWaves;
+  auto lds_of = [&](int S, bool glob) {
+    build_sweep(net->P, run, S, waves, mode == 1, sweep_walk(mode, rs), plan);
+    size_t w = 0;
+    for (int q = 0; q < net->n_inst; ++q)
+      if (run[q]) w = std::max(w, sweep_lds_bytes(net->P.insts[q], plan.insts[q], S, mode, glob, rs));
+    return w;
+  };
+  int dev = 0, maxlds = 65536;
+  (void)hipGetDevice(&dev);
+  (void)hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+  int S = req;
+  if (S == 0) {
+    S = mode == 1 ? 2 : kSweepTile;
+    while (S > 1 && tiles(S) < (S > 2 ? 512 : 256)) S >>= 1;
+  }
+  const int S0 = S, key = 2 * S + (req > 0);
+  if (t.key == key) {   // scheduled before
+    *ok = t.lds > 0;
+    return TNVAN_OK;
+  }
+  bool glob = mode == 1;
+  size_t lds = lds_of(S, glob);
+  if (req == 0) {
+    const size_t budget = std::min<size_t>((size_t)maxlds, 80 * 1024);
+    while (S > 1 && lds > budget && (glob || (S > 2 && S0 < kSweepTile))) lds = lds_of(S >>= 1, glob);
+    if (!glob && lds > budget) {
+      glob = true;
+      S = S0;
+      lds = lds_of(S, true);
+      while (S > 1 && lds > budget) lds = lds_of(S >>= 1, true);
+    }
+  } else if (!glob && lds > (size_t)maxlds) {
+    glob = true;
+    lds = lds_of(S, true);
+  }
+  if (net->capturing) return set_err(TNVAN_E_STATE, "schedule changed while recording");
+  if (tnvan_status s = quiesce(net)) return s;
+  t.key = -1;
+  t.tile = S;
+  t.waves = waves;
+  t.glob = glob;
+  t.lds = lds <= (size_t)maxlds ? lds : 0;
+  t.arena = 1;
+  for (auto &w : plan.insts) t.arena = std::max<int64_t>(t.arena, w.arena);
+  if (mode == 2) t.arena *= 3;
+  HIPCHK(upload(t.insts, plan.insts));
+  HIPCHK(upload(t.prog, plan.prog));
+  HIPCHK(upload(t.lanes, plan.lanes));
+  HIPCHK(upload(t.close, plan.close));
+  t.key = key;
+  *ok = t.lds > 0;
+  return TNVAN_OK;
+}
+
 ChainArgs chain_args(tnvan_net *net, bool bwd) {
   ChainArgs a{};
   a.inst = net->inst.as<InstDesc>();
@@ -789,16 +885,48 @@ ContractArgs<real> contract_args(tnvan_net *net, TileCache &tc, int S) {
   return a;
 }
 
+// One launch of the level kernels of `mode` over its tiles (a.c holds the
+// batch's tables and outputs); the device arenas follow the budget of
+// arena_cap.
+template <typename real>
+tnvan_status run_sweep(tnvan_net *net, int mode, TileCache &tc, SweepArgs<real> &a, hipStream_t st) {
+  tnvan_net::SweepTab &t = net->sw[mode];
+  a.insts = t.insts.as<SweepInst>();
+  a.prog = t.prog.as<int32_t>();
+  a.lanes = t.lanes.as<int32_t>();
+  a.close = t.close.as<int32_t>();
+  int grid = persistent(net) ? std::min(tc.n_tiles, 1024) : tc.n_tiles;
+  if (t.glob && tc.n_tiles > 0) {
+    const int64_t per = t.arena * t.tile;
+    const size_t need = (size_t)per * grid * sizeof(real);
+    if (need > net->garena.bytes || net->tune.arena_limit_mib > 0)
+      if (const int cap = arena_cap(net, per * (int64_t)sizeof(real), grid)) grid = cap;
+    HIPCHK(net->garena.ensure((size_t)per * grid * sizeof(real)));
+    a.c.garena = net->garena.as<real>();
+    a.c.garena_stride = per;
+  }
+  HIPCHK(launch_sweep<real>(a, tc.n_tiles, t.lds, mode, t.glob, t.waves, grid, st));
+  return TNVAN_OK;
+}
+
 template <typename real>
 tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStream_t st) {
   Phase ph0(net, "tnvan/logz");
-  tnvan_status s = ensure_tiles(net, net->tc_fwd, net->S_fwd, false);
+  bool level = false;
+  tnvan_status s = ensure_sweep(net, 0, net->tune.general_tile_fwd, &level);
+  if (s) return s;
+  if (level) net->S_fwd = net->sw[0].tile;
+  s = ensure_tiles(net, net->tc_fwd, net->S_fwd, false);
   if (s) return s;
   auto a = contract_args<real>(net, net->tc_fwd, net->S_fwd);
   a.spins = spins;
   a.logz = logz;
   int cap = 0;
-  if (net->glob_fwd) {
+  if (level) {
+    SweepArgs<real> w{};
+    w.c = a;
+    if ((s = run_sweep<real>(net, 0, net->tc_fwd, w, st))) return s;
+  } else if (net->glob_fwd) {
     int64_t per = 0;
     for (auto &D : net->P.insts) per = std::max(per, contract_garena_entries(D, net->S_fwd, false));
     cap = arena_cap(net, per * (int64_t)sizeof(real), net->tc_fwd.n_tiles);
@@ -808,8 +936,9 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
     a.arena_per_block = cap > 0;
   }
   a.pq = net->pq.as<int32_t>();
-  HIPCHK(launch_contract<real>(a, net->tc_fwd.n_tiles, net->lds_fwd, false, net->glob_fwd, st,
-                               persistent(net) || cap > 0, cap));
+  if (!level)
+    HIPCHK(launch_contract<real>(a, net->tc_fwd.n_tiles, net->lds_fwd, false, net->glob_fwd, st,
+                                 persistent(net) || cap > 0, cap));
   if (std::count(net->use_chain.begin(), net->use_chain.end(), 1)) {
     s = ensure_chain_tasks(net);
     if (s) return s;
@@ -879,7 +1008,11 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
                           double *dh, double *dJ, double *dbeta, hipStream_t st,
                           double *logz = nullptr) {
   Phase ph0(net, "tnvan/adjoint");
-  tnvan_status s = ensure_tiles(net, net->tc_bwd, net->S_bwd, true);
+  bool level = false;
+  tnvan_status s = ensure_sweep(net, 1, net->tune.general_tile_bwd, &level);
+  if (s) return s;
+  if (level) net->S_bwd = net->sw[1].tile;
+  s = ensure_tiles(net, net->tc_bwd, net->S_bwd, true);
   if (s) return s;
   TileCache &tc = net->tc_bwd;
   auto a = contract_args<real>(net, tc, net->S_bwd);
@@ -888,7 +1021,12 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
   HIPCHK(net->partial.ensure(std::max<int64_t>(1, tc.partial_total) * sizeof(real)));
   a.partial = net->partial.as<real>();
   int cap = 0;
-  if (net->glob_bwd) {
+  a.logz = logz;
+  if (level) {
+    SweepArgs<real> w{};
+    w.c = a;
+    if ((s = run_sweep<real>(net, 1, tc, w, st))) return s;
+  } else if (net->glob_bwd) {
     int64_t per = 0;
     for (auto &D : net->P.insts) per = std::max(per, contract_garena_entries(D, net->S_bwd, true));
     cap = arena_cap(net, per * (int64_t)sizeof(real), tc.n_tiles);
@@ -898,9 +1036,9 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
     a.arena_per_block = cap > 0;
   }
   a.pq = net->pq.as<int32_t>() + 2;
-  a.logz = logz;
-  HIPCHK(launch_contract<real>(a, tc.n_tiles, net->lds_bwd, true, net->glob_bwd, st,
-                               persistent(net) || cap > 0, cap));
+  if (!level)
+    HIPCHK(launch_contract<real>(a, tc.n_tiles, net->lds_bwd, true, net->glob_bwd, st,
+                                 persistent(net) || cap > 0, cap));
   if (std::count(net->use_chain.begin(), net->use_chain.end(), 1)) {
     s = ensure_chain_tasks(net);
     if (s) return s;
@@ -1531,11 +1669,15 @@ tnvan_status run_moments(tnvan_net *net, const int8_t *spins, double *logz, doub
   // (every step of such programs has its transfer table)
   for (const StepDesc &sd : net->P.steps)
     if (sd.t_off < 0) return set_err(TNVAN_E_WIDTH, "magnetisation moments need every step's table");
+  // instances off the chain kernels: the level kernels where they fit
+  bool level = false;
+  if (tnvan_status s = ensure_sweep(net, 2, 0, &level)) return s;
   if (net->mkey != net->nkey) {
     std::vector<int64_t> jo(net->n_inst), eo(net->n_inst);
     int64_t jt = 0, et = 0;
     for (int q = 0; q < net->n_inst; ++q) {
       const InstDesc &D = net->P.insts[q];
+      if (level && !net->use_chain[q]) continue;
       jo[q] = jt;
       eo[q] = et;
       jt += ((int64_t)D.arena_fwd + D.scr_fwd) * 3 * net->nkey[q];
@@ -1553,14 +1695,27 @@ tnvan_status run_moments(tnvan_net *net, const int8_t *spins, double *logz, doub
   // list), the others the general kernel
   const bool chains = sizeof(real) == 4 && net->rbwd &&
                       std::count(net->use_chain.begin(), net->use_chain.end(), 1) > 0;
-  if (chains) {
-    if (tnvan_status s = ensure_chain_tasks(net)) return s;
+  if (level) {
+    if (tnvan_status s = ensure_tiles(net, net->tc_mom, net->sw[2].tile, false)) return s;
+    SweepArgs<real> w{};
+    w.c = contract_args<real>(net, net->tc_mom, net->sw[2].tile);
+    w.c.spins = spins;
+    w.c.logz = logz;
+    w.mean = mean;
+    w.var = var;
+    if (tnvan_status s = run_sweep<real>(net, 2, net->tc_mom, w, st)) return s;
+    if (std::count(net->use_chain.begin(), net->use_chain.end(), 1) == 0) return TNVAN_OK;
+  }
+  if (level || chains)
     if (!net->mskip_set) {
-      std::vector<int32_t> fl(net->use_chain.begin(), net->use_chain.end());
+      std::vector<int32_t> fl(net->n_inst);
+      for (int q = 0; q < net->n_inst; ++q) fl[q] = net->use_chain[q] ? chains : level;
       if (tnvan_status s = quiesce(net)) return s;
       HIPCHK(upload(net->d_mskip, fl));
       net->mskip_set = true;
     }
+  if (chains) {
+    if (tnvan_status s = ensure_chain_tasks(net)) return s;
     int64_t mtot = 0;
     for (int q = 0; q < net->n_inst; ++q)
       if (net->use_chain[q]) mtot += (int64_t)net->P.cinst[q].n_chains * net->nkey[q];
@@ -1588,11 +1743,11 @@ tnvan_status run_moments(tnvan_net *net, const int8_t *spins, double *logz, doub
                                 net->n_chain_insts, net->d_B.as<int64_t>(),
                                 net->d_sample_off.as<int64_t>(), net->cpart_off.as<int64_t>(),
                                 net->w_mpart.as<double>(), mtot, mean, var, st));
-    if (std::count(net->use_chain.begin(), net->use_chain.end(), 1) == net->n_inst)
+    if (level || std::count(net->use_chain.begin(), net->use_chain.end(), 1) == net->n_inst)
       return TNVAN_OK;
   }
   MomentArgs<real> a{};
-  a.skip = chains ? net->d_mskip.as<int32_t>() : nullptr;
+  a.skip = level || chains ? net->d_mskip.as<int32_t>() : nullptr;
   a.inst = net->inst.as<InstDesc>();
   a.steps = net->steps.as<StepDesc>();
   a.inputs = net->inputs.as<InputDesc>();
@@ -1958,6 +2113,12 @@ tnvan_status tnvan_build_network(const tnvan_instance *inst, int32_t n_inst,
   }
   for (int q = 0; q < n_inst; ++q)
     if (!net->use_chain[q] && net->P.insts[q].max_w > kTabW) net->wide = true;
+  net->sweep = false;
+  for (int q = 0; q < n_inst; ++q)
+    if (!net->use_chain[q]) {
+      net->sweep = sweep_fits(P, q);
+      if (!net->sweep) break;
+    }
   choose_tiles(net, false);
   choose_tiles(net, true);
 #undef UP
@@ -2010,7 +2171,9 @@ void tnvan_free_network(tnvan_net *net) {
     net->rw_jobs[c].release();
     net->rw_lo[c].release();
   }
-  TileCache *tcs[] = {&net->tc_fwd, &net->tc_bwd};
+  for (auto &t : net->sw)
+    for (DBuf *b : {&t.insts, &t.prog, &t.lanes, &t.close}) b->release();
+  TileCache *tcs[] = {&net->tc_fwd, &net->tc_bwd, &net->tc_mom};
   for (TileCache *tc : tcs) {
     tc->tile_inst.release(); tc->tile_start.release(); tc->first_tile.release();
     tc->n_tiles_i.release(); tc->partial_off.release();

@@ -1,5 +1,7 @@
 // Batched conditional log-partition function of the remainder and its
-// adjoint (Sec. 2, Eqs. 2-4).
+// adjoint (Sec. 2, Eqs. 2-4): programs with grouped dense steps, with wide
+// steps (scopes above 14), and tiles above eight samples; other single-spin
+// programs run the level kernels (sweep.hip).
 //
 // One workgroup (256 threads) contracts a tile of S samples of one instance
 // through every elimination step of the compiled program.  Work items of a
@@ -415,15 +417,21 @@ __device__ inline void contract_tile(const ContractArgs<real> &a, const int tile
   // when it is asked for (its forward sweep is the same arithmetic)
   if (!kBwd || a.logz) {
     for (int s = tid; s < nb; s += kThreads) {
-      double acc = D.log_const;
-      for (int p = 0; p < D.nr; ++p) acc += (double)fab[p * S + s];
+      // eight chains of every eighth position, added pairwise (the level
+      // kernels' order: the same bits)
+      double fs[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+      for (int p0 = 0; p0 < D.nr; p0 += 8)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (p0 + j < D.nr) fs[j] += (double)fab[(p0 + j) * S + s];
+      double acc = D.log_const + (((fs[0] + fs[1]) + (fs[2] + fs[3])) + ((fs[4] + fs[5]) + (fs[6] + fs[7])));
       int64_t esum = 0;
       for (int t = 0; t < D.n_steps; ++t) {
         const StepDesc sd = uload(steps + t);
         if (sd.w == 0) acc += log((double)arena[(int64_t)(kBwd ? sd.off_all : sd.off_fwd) * S + s]);
         else esum += FB::expo(mx[t * S + s]);
       }
-      acc += (double)esum * 0.69314718055994530942;
+      acc = __builtin_fma((double)esum, 0.69314718055994530942, acc);
       a.logz[a.inst_sample_off[q] + b0 + s] = acc;
     }
     if (!kBwd) return;

@@ -7,6 +7,7 @@
 
 #include "../../include/tnvan.h"
 #include "program.h"
+#include "sweep.h"
 
 namespace tnvan {
 
@@ -66,6 +67,28 @@ template <typename real>
 hipError_t launch_contract(const ContractArgs<real> &a, int n_tiles, size_t lds,
                            bool bwd, bool global_arena, hipStream_t st, bool persistent = false,
                            int max_grid = 0);
+
+// Level kernels of single-spin programs (sweep.h): the program and batch
+// tables of ContractArgs (garena: one arena of garena_stride entries per
+// workgroup) and the schedule.  mode 0: ln Z_R; 1: the adjoint (partial rows
+// per tile as launch_contract's, and ln Z_R where c.logz is set); 2: the
+// jets of the magnetisation moments (mean, var, and ln Z_R where c.logz is
+// set).  waves: per workgroup, as scheduled.  max_grid > 0: at most that
+// many workgroups.
+template <typename real>
+struct SweepArgs {
+  ContractArgs<real> c;
+  const SweepInst *insts;
+  const int32_t *prog;
+  const int32_t *lanes;
+  const int32_t *close;
+  double *mean, *var;
+};
+size_t sweep_lds_bytes(const InstDesc &D, const SweepInst &W, int S, int mode, bool global_arena,
+                       int real_size);
+template <typename real>
+hipError_t launch_sweep(const SweepArgs<real> &a, int n_tiles, size_t lds, int mode,
+                        bool global_arena, int waves, int max_grid, hipStream_t st);
 
 // Sum per-tile partials and scatter dh, dJ, dbeta (FP64).
 struct VjpArgs {

@@ -16,8 +16,8 @@
 // the parts (independent given s_W).  The same per-step power-of-two
 // rescale as the forward kernels applies to all three coefficients.
 //
-// An instance runs its general step program here (dense grouped steps and
-// single-spin steps with full tables; not the wide steps), one thread per
+// Programs of grouped dense steps run here (single-spin programs take the
+// level kernels of sweep.hip instead where those fit), one thread per
 // sample, the jets in device memory as [entry][coefficient][sample] so that
 // neighbouring threads touch neighbouring words; instances whose program is
 // a set of narrow chains run the same jets on the register-resident chain
