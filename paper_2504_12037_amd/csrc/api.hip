@@ -194,6 +194,17 @@ struct tnvan_net {
   int sample_reps = 1;
   // transfer-matrix form (chain kernels, FP32 / BF16 precisions)
   std::vector<int32_t> use_chain;
+  // FP64 nets: instances on the double-precision chain kernels, with their
+  // tasks by chain width, buffers and the batch they were laid out for
+  std::vector<int32_t> use_c64;
+  struct Chains64 {
+    std::vector<int64_t> key;
+    int lo[3] = {0, 0, 0}, n[3] = {0, 0, 0};
+    int n_list = 0, max_chunks = 0, max_steps = 0, ck_tiles = 1;
+    int64_t max_B = 0;
+    DBuf steps, ti, tc, ts, list, u_off, f_off, cpart_off, U, fabp, cpart, ckpt;
+  } c64;
+  bool on_chain(int q) const { return use_chain[q] || use_c64[q]; }
   DBuf cinst, chains, csteps, Tp, Tt, Tb, fld_wr, fld_J32, hR32;
   ChainLim lim_fwd{}, lim_bwd{};
   DBuf Tl, Tbl, cedges, ckpt;
@@ -579,7 +590,7 @@ tnvan_status ensure_tiles(tnvan_net *net, TileCache &tc, int S, bool bwd) {
   for (int q : by_cost) {
     first[q] = (int32_t)ti.size();
     const int64_t B = net->nkey[q];
-    if (net->use_chain[q]) {
+    if (net->on_chain(q)) {
       cnt[q] = (int32_t)((B + 15) / 16);        // one partial row per 16 samples
     } else {
       for (int64_t b = 0; b < B; b += S) { ti.push_back(q); ts.push_back((int32_t)b); }
@@ -738,11 +749,11 @@ tnvan_status ensure_sweep(tnvan_net *net, int mode, int req, bool *ok) {
   auto tiles = [&](int S) {
     int64_t n = 0;
     for (int q = 0; q < net->n_inst; ++q)
-      if (!net->use_chain[q]) n += (net->nkey[q] + S - 1) / S;
+      if (!net->on_chain(q)) n += (net->nkey[q] + S - 1) / S;
     return n;
   };
   std::vector<int32_t> run(net->n_inst);
-  for (int q = 0; q < net->n_inst; ++q) run[q] = !net->use_chain[q];
+  for (int q = 0; q < net->n_inst; ++q) run[q] = !net->on_chain(q);
   SweepPlan plan;
   const int waves = kSweepWaves;
   auto lds_of = [&](int S, bool glob) {
@@ -909,6 +920,117 @@ tnvan_status run_sweep(tnvan_net *net, int mode, TileCache &tc, SweepArgs<real> 
   return TNVAN_OK;
 }
 
+// The chain instances of an FP64 net: tables for the batch, then the unary
+// factors and one launch per chain width.  bwd: the adjoint (partial rows
+// at partial, laid out by poff; also ln Z_R where logz is set), else ln Z_R.
+tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const double *grad,
+                         double *partial, const int64_t *poff, double *logz, hipStream_t st) {
+  auto &c = net->c64;
+  if (c.key != net->nkey) {
+    if (tnvan_status s = quiesce(net)) return s;
+    std::vector<int32_t> ti, tc, ts, list;
+    std::vector<int64_t> uo(net->n_inst, 0), fo(net->n_inst, 0), co(net->n_inst, 0);
+    int64_t ut = 0, ft = 0, ct = 0, ck = 0;
+    c.max_chunks = 0;
+    c.max_B = 0;
+    for (int q = 0; q < net->n_inst; ++q) {
+      if (!net->use_c64[q]) continue;
+      const int64_t B = net->nkey[q];
+      const int nr = net->P.insts[q].nr, nch = (nr + kUnaryChunk - 1) / kUnaryChunk;
+      list.push_back(q);
+      uo[q] = ut;
+      fo[q] = ft;
+      co[q] = ct;
+      ut += (int64_t)nr * B;
+      ft += (int64_t)nch * B;
+      ct += (int64_t)net->P.cinst[q].n_chains * B;
+      c.max_chunks = std::max(c.max_chunks, nch);
+      c.max_B = std::max(c.max_B, B);
+    }
+    for (int gi = 2; gi >= 0; --gi) {
+      c.lo[gi] = (int)ti.size();
+      for (int q : list) {
+        const ChainInst &C = net->P.cinst[q];
+        for (int64_t b = 0; b < net->nkey[q]; b += 16)
+          for (int k = 0; k < C.n_chains; ++k)
+            if (net->P.chains[C.chain_off + k].rt == 1 << gi) {
+              ti.push_back(q);
+              tc.push_back(k);
+              ts.push_back((int32_t)b);
+            }
+      }
+      c.n[gi] = (int)ti.size() - c.lo[gi];
+    }
+    // (the two launches run one after the other and share the checkpoints)
+    c.ck_tiles = c.n[1] > 0 ? 2 : 1;
+    ck = std::max((int64_t)c.n[2] * 4, (int64_t)(c.n[0] + c.n[1]) * c.ck_tiles) * c.max_steps * 256;
+    HIPCHK(upload(c.ti, ti));
+    HIPCHK(upload(c.tc, tc));
+    HIPCHK(upload(c.ts, ts));
+    HIPCHK(upload(c.list, list));
+    HIPCHK(upload(c.u_off, uo));
+    HIPCHK(upload(c.f_off, fo));
+    HIPCHK(upload(c.cpart_off, co));
+    HIPCHK(c.U.ensure(std::max<int64_t>(1, ut) * sizeof(double)));
+    HIPCHK(c.fabp.ensure(std::max<int64_t>(1, ft) * sizeof(double)));
+    HIPCHK(c.cpart.ensure(std::max<int64_t>(1, ct) * sizeof(double)));
+    HIPCHK(c.ckpt.ensure(std::max<int64_t>(1, ck) * sizeof(double)));
+    c.n_list = (int)list.size();
+    c.key = net->nkey;
+  }
+  Chain64Args a{};
+  a.inst = net->inst.as<InstDesc>();
+  a.cinst = net->cinst.as<ChainInst>();
+  a.chains = net->chains.as<ChainDesc>();
+  a.csteps = c.steps.as<Chain64Step>();
+  a.T = net->T.as<double>();
+  a.Tsx = net->Tsx.as<float>();
+  a.Tdq = net->Tdq.as<int32_t>();
+  a.fld_ptr = net->fld_ptr.as<int32_t>();
+  a.fld_w = net->fld_w.as<int32_t>();
+  a.fld_J = net->fld_J.as<double>();
+  a.hR = net->hR.as<double>();
+  a.task_inst = c.ti.as<int32_t>();
+  a.task_chain = c.tc.as<int32_t>();
+  a.task_start = c.ts.as<int32_t>();
+  a.max_steps = c.max_steps;
+  a.write_logz = logz != nullptr;
+  a.inst_B = net->d_B.as<int64_t>();
+  a.inst_sample_off = net->d_sample_off.as<int64_t>();
+  a.inst_spin_off = net->d_spin_off.as<int64_t>();
+  a.cpart_off = c.cpart_off.as<int64_t>();
+  a.spins = spins;
+  a.U = c.U.as<double>();
+  a.u_off = c.u_off.as<int64_t>();
+  a.cpart = c.cpart.as<double>();
+  a.grad = grad;
+  a.partial = partial;
+  a.inst_partial_off = poff;
+  a.ckpt = c.ckpt.as<double>();
+  {
+    Phase ph(net, "tnvan/boundary");
+    HIPCHK(launch_unary64(a, c.list.as<int32_t>(), c.n_list, c.max_chunks, c.max_B,
+                          c.f_off.as<int64_t>(), c.U.as<double>(), c.fabp.as<double>(), st));
+  }
+  a.task_base = c.lo[2];
+  a.n_tasks = c.n[2];
+  a.ck_tiles = 4;
+  HIPCHK(launch_chain64(a, true, bwd, st));
+  a.task_base = c.lo[1];
+  a.n_two = c.n[1];
+  a.n_tasks = c.n[1] + c.n[0];
+  a.ck_tiles = c.ck_tiles;
+  HIPCHK(launch_chain64(a, false, bwd, st));
+  if (logz)
+    HIPCHK(launch_chain_sum(a.inst, a.cinst, c.list.as<int32_t>(), c.n_list, a.inst_B,
+                            a.inst_sample_off, a.cpart_off, c.cpart.as<double>(),
+                            c.f_off.as<int64_t>(), c.fabp.as<double>(), logz, st));
+  return TNVAN_OK;
+}
+bool any_c64(const tnvan_net *net) {
+  return std::count(net->use_c64.begin(), net->use_c64.end(), 1) > 0;
+}
+
 template <typename real>
 tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStream_t st) {
   Phase ph0(net, "tnvan/logz");
@@ -939,6 +1061,8 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
   if (!level)
     HIPCHK(launch_contract<real>(a, net->tc_fwd.n_tiles, net->lds_fwd, false, net->glob_fwd, st,
                                  persistent(net) || cap > 0, cap));
+  if (any_c64(net))
+    if ((s = run_chain64(net, spins, false, nullptr, nullptr, nullptr, logz, st))) return s;
   if (std::count(net->use_chain.begin(), net->use_chain.end(), 1)) {
     s = ensure_chain_tasks(net);
     if (s) return s;
@@ -1039,6 +1163,10 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
   if (!level)
     HIPCHK(launch_contract<real>(a, tc.n_tiles, net->lds_bwd, true, net->glob_bwd, st,
                                  persistent(net) || cap > 0, cap));
+  if (any_c64(net))
+    if ((s = run_chain64(net, spins, true, grad, net->partial.as<double>(),
+                         tc.partial_off.as<int64_t>(), logz, st)))
+      return s;
   if (std::count(net->use_chain.begin(), net->use_chain.end(), 1)) {
     s = ensure_chain_tasks(net);
     if (s) return s;
@@ -1677,7 +1805,7 @@ tnvan_status run_moments(tnvan_net *net, const int8_t *spins, double *logz, doub
     int64_t jt = 0, et = 0;
     for (int q = 0; q < net->n_inst; ++q) {
       const InstDesc &D = net->P.insts[q];
-      if (level && !net->use_chain[q]) continue;
+      if (level && !net->on_chain(q)) continue;
       jo[q] = jt;
       eo[q] = et;
       jt += ((int64_t)D.arena_fwd + D.scr_fwd) * 3 * net->nkey[q];
@@ -1704,12 +1832,14 @@ tnvan_status run_moments(tnvan_net *net, const int8_t *spins, double *logz, doub
     w.mean = mean;
     w.var = var;
     if (tnvan_status s = run_sweep<real>(net, 2, net->tc_mom, w, st)) return s;
-    if (std::count(net->use_chain.begin(), net->use_chain.end(), 1) == 0) return TNVAN_OK;
+    bool rest = false;
+    for (int q = 0; q < net->n_inst; ++q) rest = rest || net->on_chain(q);
+    if (!rest) return TNVAN_OK;
   }
   if (level || chains)
     if (!net->mskip_set) {
       std::vector<int32_t> fl(net->n_inst);
-      for (int q = 0; q < net->n_inst; ++q) fl[q] = net->use_chain[q] ? chains : level;
+      for (int q = 0; q < net->n_inst; ++q) fl[q] = net->use_chain[q] ? chains : net->use_c64[q] ? 0 : level;
       if (tnvan_status s = quiesce(net)) return s;
       HIPCHK(upload(net->d_mskip, fl));
       net->mskip_set = true;
@@ -2111,11 +2241,49 @@ tnvan_status tnvan_build_network(const tnvan_instance *inst, int32_t n_inst,
       net->rfwd = net->rbwd = false;
     }
   }
+  // FP64: chains of 1, 2 or 4 tiles whose adjoint fits the 16-column sums
+  net->use_c64.assign(n_inst, 0);
+  if (net->precision == TNVAN_FP64) {
+    int dev = 0, maxlds = 65536;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    for (int q = 0; q < n_inst; ++q) {
+      const ChainInst &C = P.cinst[q];
+      if (!C.ok || !C.rq_ok || C.rtiles > kChain64Tiles || P.insts[q].nr < kChain64MinR ||
+          chain64_lds(true, C.max_steps) > (size_t)maxlds)
+        continue;
+      net->use_c64[q] = 1;
+      net->c64.max_steps = std::max(net->c64.max_steps, (int)C.max_steps);
+    }
+    std::vector<Chain64Step> cs;
+    for (int q = 0; q < n_inst; ++q)
+      for (int k = 0; k < P.cinst[q].n_chains && P.cinst[q].ok; ++k) {
+        const ChainDesc &cd = P.chains[P.cinst[q].chain_off + k];
+        if ((int)cs.size() < cd.cs_off + cd.n_steps) cs.resize(cd.cs_off + cd.n_steps);
+        for (int t = 0; t < cd.n_steps; ++t) {
+          const ChainStep &c = P.csteps[cd.cs_off + t];
+          Chain64Step &o = cs[cd.cs_off + t];
+          o = Chain64Step{};
+          o.t_off = P.steps[P.insts[q].step_off + c.step].t_off;
+          o.sx_off = c.sx_off;
+          o.g = c.g;
+          o.w = c.w;
+          o.gpos = c.gpos;
+          o.dq_off = c.dq_off;
+          o.n_wri = c.n_wri;
+          for (int i = 0; i < 4; ++i) {
+            o.wri[i] = c.wri[i];
+            o.wre[i] = c.wre[i];
+          }
+        }
+      }
+    if ((e = upload(net->c64.steps, cs)) != hipSuccess) return fail(e, "chain steps");
+  }
   for (int q = 0; q < n_inst; ++q)
     if (!net->use_chain[q] && net->P.insts[q].max_w > kTabW) net->wide = true;
   net->sweep = false;
   for (int q = 0; q < n_inst; ++q)
-    if (!net->use_chain[q]) {
+    if (!net->on_chain(q)) {
       net->sweep = sweep_fits(P, q);
       if (!net->sweep) break;
     }
@@ -2171,6 +2339,10 @@ void tnvan_free_network(tnvan_net *net) {
     net->rw_jobs[c].release();
     net->rw_lo[c].release();
   }
+  for (DBuf *b : {&net->c64.steps, &net->c64.ti, &net->c64.tc, &net->c64.ts, &net->c64.list, &net->c64.u_off,
+                  &net->c64.f_off, &net->c64.cpart_off, &net->c64.U, &net->c64.fabp,
+                  &net->c64.cpart, &net->c64.ckpt})
+    b->release();
   for (auto &t : net->sw)
     for (DBuf *b : {&t.insts, &t.prog, &t.lanes, &t.close}) b->release();
   TileCache *tcs[] = {&net->tc_fwd, &net->tc_bwd, &net->tc_mom};

@@ -532,6 +532,54 @@ constexpr int kUnaryChunk = 16;
 hipError_t launch_unary(const ChainArgs &a, const int32_t *cis, int n_cis, int max_chunks,
                         int64_t max_B, const int64_t *f_off, float *U, double *fabp,
                         hipStream_t st);
+// Chains of FP64 nets (chain64.hip): one wave per (instance, chain, 16
+// samples), four waves per workgroup, chains of 1 and 2 tiles in one launch
+// (the two-tile tasks first), of 4 in another (wide); the unary factors and
+// sums of beta |f| as U and fabp above, in double precision.
+// bwd: the adjoint's partial rows (one per 16 samples) and, with
+// write_logz, the forward's chain partials.
+struct Chain64Step {                // what the kernels read of a chain step
+  int64_t t_off, sx_off;
+  int32_t g, w, gpos, dq_off, n_wri;
+  int32_t wri[4], wre[4];
+  int32_t pad;
+};
+struct Chain64Args {
+  const InstDesc *inst;
+  const ChainInst *cinst;
+  const ChainDesc *chains;
+  const Chain64Step *csteps;        // parallel to the chain steps
+  const double *T;
+  const float *Tsx;
+  const int32_t *Tdq;
+  const int32_t *fld_ptr, *fld_w;
+  const double *fld_J, *hR;
+  const int32_t *task_inst, *task_chain, *task_start;   // per wave
+  int32_t task_base, n_tasks, n_two;   // n_two: its first tasks, two tiles each
+  int32_t max_steps;                // of the longest chain
+  int32_t ck_tiles;                 // tiles of a checkpoint
+  int32_t write_logz;
+  const int64_t *inst_B, *inst_sample_off, *inst_spin_off, *cpart_off;
+  const int8_t *spins;
+  const double *U;
+  const int64_t *u_off;
+  double *cpart;
+  const double *grad;
+  double *partial;
+  const int64_t *inst_partial_off;
+  double *ckpt;                     // [task][step][tile][64 lanes][4]
+};
+constexpr int kChain64Tiles = 4;
+size_t chain64_lds(bool wide, int max_steps);
+hipError_t launch_unary64(const Chain64Args &a, const int32_t *list, int n_list, int max_chunks,
+                          int64_t max_B, const int64_t *f_off, double *U, double *fabp,
+                          hipStream_t st);
+hipError_t launch_chain64(const Chain64Args &a, bool wide, bool bwd, hipStream_t st);
+// instances with fewer remainder positions stay on the general kernel, one
+// launch instead of three (a 4x4 lattice, 12 positions, 1024 samples: 12
+// against 17 us for ln Z_R)
+constexpr int kChain64MinR = 32;
+
 // LDS bytes: shared part of a workgroup and per-wave part
 size_t chain_shared_lds(const ChainLim &L, bool bwd, bool bf16);
 size_t chain_wave_lds(const ChainLim &L, bool bwd);
