@@ -158,6 +158,16 @@ struct tnvan_net {
     DBuf insts, prog, lanes, close;
   } sw[3];
   bool sweep = false;
+  // every instance off the chain kernels runs in segments between launches
+  // of its wide steps, and some has wide steps
+  bool segments = false;
+  struct WideTab {
+    int state = 0;              // 0: not scheduled yet, 1: ready, -1: does not fit
+    std::vector<std::vector<WideSegment>> segs;
+    std::vector<int32_t> sum_lo, part, red;
+    size_t lds = 0;
+    DBuf steps, fins, sums, tab, insts, prog, lanes, close;
+  } wd;
   int S_fwd = 1, S_bwd = 1;
   bool glob_fwd = false, glob_bwd = false;
   size_t lds_fwd = 0, lds_bwd = 0;
@@ -810,6 +820,52 @@ tnvan_status ensure_sweep(tnvan_net *net, int mode, int req, bool *ok) {
   return TNVAN_OK;
 }
 
+// The schedule of nets with wide steps (tile requests above eight samples
+// keep the step-by-step kernel, as for the level kernels).  Every sample is
+// a tile of its own here, whatever smaller tile is asked for: the wide
+// steps' launches spread a sample over the chip.  On 64 samples of a
+// 1000-spin random 3-regular graph at width 18 ln Z_R and its adjoint
+// through autograd took 50.4 ms step by step (one workgroup a sample) and
+// 2.76 ms so.
+tnvan_status ensure_segments(tnvan_net *net, int req, bool *ok) {
+  *ok = false;
+  if (!net->segments || req > kSweepTile) return TNVAN_OK;
+  auto &t = net->wd;
+  if (t.state == 0) {
+    if (net->capturing) return set_err(TNVAN_E_STATE, "schedule changed while recording");
+    std::vector<int32_t> run(net->n_inst);
+    for (int q = 0; q < net->n_inst; ++q) run[q] = !net->on_chain(q);
+    WidePlan plan;
+    build_wide(net->P, run, plan);
+    int dev = 0, maxlds = 65536;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    t.lds = 0;
+    for (int q = 0; q < net->n_inst; ++q)
+      if (run[q])
+        t.lds = std::max(t.lds, sweep_lds_bytes(net->P.insts[q], plan.insts[q], 1, 3, true, net->rs()));
+    if (t.lds > (size_t)maxlds) {
+      t.state = -1;
+      return TNVAN_OK;
+    }
+    HIPCHK(upload(t.steps, plan.steps));
+    HIPCHK(upload(t.fins, plan.fins));
+    HIPCHK(upload(t.sums, plan.sums));
+    HIPCHK(upload(t.tab, plan.tab));
+    HIPCHK(upload(t.insts, plan.insts));
+    HIPCHK(upload(t.prog, plan.prog));
+    HIPCHK(upload(t.lanes, plan.lanes));
+    HIPCHK(upload(t.close, plan.close));
+    t.segs = std::move(plan.segs);
+    t.sum_lo = std::move(plan.sum_lo);
+    t.part = std::move(plan.part);
+    t.red = std::move(plan.red);
+    t.state = 1;
+  }
+  *ok = t.state > 0;
+  return TNVAN_OK;
+}
+
 ChainArgs chain_args(tnvan_net *net, bool bwd) {
   ChainArgs a{};
   a.inst = net->inst.as<InstDesc>();
@@ -917,6 +973,86 @@ tnvan_status run_sweep(tnvan_net *net, int mode, TileCache &tc, SweepArgs<real> 
     a.c.garena_stride = per;
   }
   HIPCHK(launch_sweep<real>(a, tc.n_tiles, t.lds, mode, t.glob, t.waves, grid, st));
+  return TNVAN_OK;
+}
+
+// The general instances of a net with wide steps: for each, chunks of the
+// samples whose memory fits the budget of arena_cap, each forward through
+// the segments and (bwd) back.  c: the batch's tables and outputs, one
+// sample per tile.
+template <typename real>
+tnvan_status run_segments(tnvan_net *net, const ContractArgs<real> &c, bool bwd, hipStream_t st) {
+  auto &t = net->wd;
+  auto up = [](int64_t n) { return (n + 63) / 64 * 64; };
+  int64_t words = 0;   // largest need of an instance
+  struct Lay { int64_t part, red, state, stride; int chunk; };
+  std::vector<Lay> lay(net->n_inst);
+  for (int q = 0; q < net->n_inst; ++q) {
+    if (t.segs[q].empty() || net->nkey[q] <= 0) continue;
+    const InstDesc &D = net->P.insts[q];
+    Lay &l = lay[q];
+    l.part = up(D.arena_all);
+    l.red = l.part + (bwd ? up(t.part[q]) : 0);
+    l.state = l.red + (bwd ? up(t.red[q]) : 0);
+    l.stride = l.state + up((int64_t)D.n_steps + 4 * D.nr + D.n_rr);
+    const int B = (int)net->nkey[q];
+    l.chunk = B;
+    const size_t need = (size_t)l.stride * B * sizeof(real);
+    if (need > net->garena.bytes || net->tune.arena_limit_mib > 0)
+      if (const int cap = arena_cap(net, l.stride * (int64_t)sizeof(real), B)) l.chunk = cap;
+    words = std::max(words, l.stride * l.chunk);
+  }
+  if (words == 0) return TNVAN_OK;
+  HIPCHK(net->garena.ensure((size_t)words * sizeof(real)));
+  SweepArgs<real> w{};
+  w.c = c;
+  w.c.garena = net->garena.as<real>();
+  w.insts = t.insts.as<SweepInst>();
+  w.prog = t.prog.as<int32_t>();
+  w.lanes = t.lanes.as<int32_t>();
+  w.close = t.close.as<int32_t>();
+  WideArgs<real> a{};
+  a.mem = net->garena.as<real>();
+  a.steps = t.steps.as<WideStep>();
+  a.fins = t.fins.as<WideFin>();
+  a.tab = t.tab.as<int32_t>();
+  a.edges = c.edges;
+  a.esmall = c.esmall;
+  a.T = c.T;
+  for (int q = 0; q < net->n_inst; ++q) {
+    const Lay &l = lay[q];
+    const auto &segs = t.segs[q];
+    if (l.chunk <= 0) continue;
+    w.c.garena_stride = a.stride = l.stride;
+    a.part = l.part;
+    a.red = w.seg.red = l.red;
+    a.state = w.seg.state = l.state;
+    a.n_steps = net->P.insts[q].n_steps;
+    w.seg.q = q;
+    w.seg.sums = t.sums.as<WideSum>() + t.sum_lo[q];
+    w.seg.n_sums = t.sum_lo[q + 1] - t.sum_lo[q];
+    for (int64_t b = 0; b < net->nkey[q]; b += l.chunk) {
+      const int n = (int)std::min<int64_t>(l.chunk, net->nkey[q] - b);
+      w.seg.b0 = b;
+      for (size_t i = 0; i < segs.size(); ++i) {
+        w.seg.first = i == 0;
+        w.seg.rev = w.seg.last = 0;
+        std::copy(segs[i].fwd, segs[i].fwd + kSweepWaves, w.seg.prog);
+        HIPCHK(launch_sweep_segment<real>(w, n, t.lds, st));
+        for (auto &g : segs[i].groups) HIPCHK(launch_wide<real>(a, g, n, false, st));
+      }
+      if (!bwd) continue;
+      w.seg.first = 0;
+      w.seg.rev = 1;
+      for (size_t i = segs.size(); i-- > 0;) {
+        for (size_t g = segs[i].groups.size(); g-- > 0;)
+          HIPCHK(launch_wide<real>(a, segs[i].groups[g], n, true, st));
+        w.seg.last = i == 0;
+        std::copy(segs[i].bwd, segs[i].bwd + kSweepWaves, w.seg.prog);
+        HIPCHK(launch_sweep_segment<real>(w, n, t.lds, st));
+      }
+    }
+  }
   return TNVAN_OK;
 }
 
@@ -1038,6 +1174,9 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
   tnvan_status s = ensure_sweep(net, 0, net->tune.general_tile_fwd, &level);
   if (s) return s;
   if (level) net->S_fwd = net->sw[0].tile;
+  bool segs = false;
+  if ((s = ensure_segments(net, net->tune.general_tile_fwd, &segs))) return s;
+  if (segs) net->S_fwd = 1;
   s = ensure_tiles(net, net->tc_fwd, net->S_fwd, false);
   if (s) return s;
   auto a = contract_args<real>(net, net->tc_fwd, net->S_fwd);
@@ -1048,6 +1187,8 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
     SweepArgs<real> w{};
     w.c = a;
     if ((s = run_sweep<real>(net, 0, net->tc_fwd, w, st))) return s;
+  } else if (segs) {
+    if ((s = run_segments<real>(net, a, false, st))) return s;
   } else if (net->glob_fwd) {
     int64_t per = 0;
     for (auto &D : net->P.insts) per = std::max(per, contract_garena_entries(D, net->S_fwd, false));
@@ -1058,7 +1199,7 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
     a.arena_per_block = cap > 0;
   }
   a.pq = net->pq.as<int32_t>();
-  if (!level)
+  if (!level && !segs)
     HIPCHK(launch_contract<real>(a, net->tc_fwd.n_tiles, net->lds_fwd, false, net->glob_fwd, st,
                                  persistent(net) || cap > 0, cap));
   if (any_c64(net))
@@ -1136,6 +1277,9 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
   tnvan_status s = ensure_sweep(net, 1, net->tune.general_tile_bwd, &level);
   if (s) return s;
   if (level) net->S_bwd = net->sw[1].tile;
+  bool segs = false;
+  if ((s = ensure_segments(net, net->tune.general_tile_bwd, &segs))) return s;
+  if (segs) net->S_bwd = 1;
   s = ensure_tiles(net, net->tc_bwd, net->S_bwd, true);
   if (s) return s;
   TileCache &tc = net->tc_bwd;
@@ -1150,6 +1294,8 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
     SweepArgs<real> w{};
     w.c = a;
     if ((s = run_sweep<real>(net, 1, tc, w, st))) return s;
+  } else if (segs) {
+    if ((s = run_segments<real>(net, a, true, st))) return s;
   } else if (net->glob_bwd) {
     int64_t per = 0;
     for (auto &D : net->P.insts) per = std::max(per, contract_garena_entries(D, net->S_bwd, true));
@@ -1160,7 +1306,7 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
     a.arena_per_block = cap > 0;
   }
   a.pq = net->pq.as<int32_t>() + 2;
-  if (!level)
+  if (!level && !segs)
     HIPCHK(launch_contract<real>(a, tc.n_tiles, net->lds_bwd, true, net->glob_bwd, st,
                                  persistent(net) || cap > 0, cap));
   if (any_c64(net))
@@ -2287,6 +2433,9 @@ tnvan_status tnvan_build_network(const tnvan_instance *inst, int32_t n_inst,
       net->sweep = sweep_fits(P, q);
       if (!net->sweep) break;
     }
+  net->segments = net->wide;
+  for (int q = 0; q < n_inst && net->segments; ++q)
+    if (!net->on_chain(q)) net->segments = wide_fits(P, q);
   choose_tiles(net, false);
   choose_tiles(net, true);
 #undef UP
@@ -2339,6 +2488,9 @@ void tnvan_free_network(tnvan_net *net) {
     net->rw_jobs[c].release();
     net->rw_lo[c].release();
   }
+  for (DBuf *b : {&net->wd.steps, &net->wd.fins, &net->wd.sums, &net->wd.tab, &net->wd.insts,
+                  &net->wd.prog, &net->wd.lanes, &net->wd.close})
+    b->release();
   for (DBuf *b : {&net->c64.steps, &net->c64.ti, &net->c64.tc, &net->c64.ts, &net->c64.list, &net->c64.u_off,
                   &net->c64.f_off, &net->c64.cpart_off, &net->c64.U, &net->c64.fabp,
                   &net->c64.cpart, &net->c64.ckpt})

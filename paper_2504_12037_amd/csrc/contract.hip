@@ -1,7 +1,7 @@
 // Batched conditional log-partition function of the remainder and its
-// adjoint (Sec. 2, Eqs. 2-4): programs with grouped dense steps, with wide
-// steps (scopes above 14), and tiles above eight samples; other single-spin
-// programs run the level kernels (sweep.hip).
+// adjoint (Sec. 2, Eqs. 2-4): programs with grouped dense steps, and tiles
+// above eight samples; other single-spin programs run the level kernels
+// (sweep.hip), those with scopes above 14 in segments (wide.hip).
 //
 // One workgroup (256 threads) contracts a tile of S samples of one instance
 // through every elimination step of the compiled program.  Work items of a

@@ -83,7 +83,40 @@ struct SweepArgs {
   const int32_t *lanes;
   const int32_t *close;
   double *mean, *var;
+  // a segment between wide steps: tile = sample of the chunk
+  struct Segment {
+    int32_t q;                  // instance
+    int32_t first, rev, last;   // forward from the start; reverse; reverse to the end
+    int64_t b0;                 // first sample of the chunk
+    int32_t prog[8];            // first record of each wave's program
+    int64_t state, red;         // offsets in the sample's memory
+    const WideSum *sums;        // wide steps' sums
+    int32_t n_sums;
+  } seg;
 };
+// One launch of a segment's light steps, n_samples workgroups.
+template <typename real>
+hipError_t launch_sweep_segment(const SweepArgs<real> &a, int n_samples, size_t lds, hipStream_t st);
+
+// Wide steps.  A sample's memory: arena, partial sums, sums over the steps'
+// workgroups, and the state kept between launches: largest entry of each
+// step, unary factors [2 nr], beta |f| [nr], magnetisations [nr], correlations.
+template <typename real>
+struct WideArgs {
+  real *mem;
+  int64_t stride, part, red, state;
+  int32_t n_steps;
+  int32_t w0, f0, f1;
+  const WideStep *steps;
+  const WideFin *fins;
+  const int32_t *tab;
+  const EdgeDesc *edges;
+  const real *esmall;
+  const real *T;
+};
+template <typename real>
+hipError_t launch_wide(const WideArgs<real> &a, const WideGroup &g, int n_samples, bool bwd,
+                       hipStream_t st);
 size_t sweep_lds_bytes(const InstDesc &D, const SweepInst &W, int S, int mode, bool global_arena,
                        int real_size);
 template <typename real>

@@ -93,7 +93,68 @@ struct SweepPlan {
   std::vector<int32_t> close;
 };
 
+// Programs with wide steps run in segments: the steps of kWideStep bits or
+// more spread over the chip, one launch per group of independent ones
+// (wide.hip), and between them the light steps in level programs, one
+// workgroup per sample.  A segment's light steps need only wide steps of the
+// segments before; its wide steps follow in groups by their inputs.
+//
+// A workgroup of a wide step takes 2^kWideChunk output entries o: the chunk
+// position i = thread + kWideThreads * r, whose bits stand on the output bits
+// the schedule picks (the five lowest, for runs of 32 entries, then those
+// that the inputs don't have, the largest input first, so that the sums over
+// them stay in the workgroup).  What depends on o bit by bit (o itself, the
+// index into each input) is a table of the thread's, of the r's and of the
+// workgroup's part.
+constexpr int kWideStep = 12;
+constexpr int kWideChunk = 11;
+constexpr int kWideThreads = 256;
+constexpr int kWideRegs = (1 << kWideChunk) / kWideThreads;
+struct WideInput {
+  int32_t off, step, xbit, bits;
+  int32_t idx;      // table of its index: [kWideThreads][kWideRegs][workgroups]
+  int32_t free;     // chunk positions' bits not in its scope
+  int32_t dep;      // table, per entry of the chunk in its scope: position | index << kWideChunk
+  int32_t row;      // table [workgroups]: which partial sum it holds
+  int32_t part;     // partial sums [row][entry], or -1: the workgroup has the whole sums
+};
+struct WideStep {
+  int32_t step, gpos, w, n_in, n_edge, off;
+  int32_t edge_off;
+  int32_t out;      // table of o, as WideInput::idx
+  int64_t t_off;    // transfer table, or -1: formed from the edges
+  int32_t red;      // sums [workgroup][1 + edges] (spin, edge correlations)
+  int32_t pad;
+  WideInput in[kWideIn];
+};
+// an input's rho from its partial sums; a wide step's sums over its workgroups
+struct WideFin { int32_t part, off, step, nbits, rows, first; };   // first: workgroup of the launch
+struct WideSum { int32_t first, stride, n, edge; };   // edge: R-R edge, or -1 - position
+struct WideGroup {
+  int32_t w0, w1, blocks;      // steps and their workgroups
+  int32_t f0, f1, fblocks;     // WideFin and their workgroups
+};
+struct WideSegment {
+  int32_t fwd[kSweepWaves], bwd[kSweepWaves];   // first records of the light programs
+  std::vector<WideGroup> groups;                // after the light steps
+};
+struct WidePlan {
+  std::vector<std::vector<WideSegment>> segs;   // per instance
+  std::vector<WideStep> steps;
+  std::vector<WideFin> fins;
+  std::vector<WideSum> sums;
+  std::vector<int32_t> sum_lo;                  // per instance, and the end
+  std::vector<int32_t> tab;
+  std::vector<SweepInst> insts;                 // (prog unused)
+  std::vector<int32_t> part, red;               // scratch words per sample
+  std::vector<int32_t> prog, lanes, close;
+};
+
 struct HostProgram;
+// Whether instance q can run in segments (single-spin steps within the
+// limits above and those of the wide steps); and their schedule.
+bool wide_fits(const HostProgram &P, int q);
+void build_wide(const HostProgram &P, const std::vector<int32_t> &run, WidePlan &out);
 
 // Whether instance q is a single-spin program with full tables within the
 // limits above.

@@ -69,7 +69,8 @@ struct SLay {
 };
 __host__ __device__ inline size_t up8(size_t x) { return (x + 7) & ~(size_t)7; }
 
-// mode: 0 forward, 1 adjoint, 2 jets
+// mode: 0 forward, 1 adjoint, 2 jets, 3 a segment between wide steps (its
+// forward or its reverse part)
 __host__ __device__ inline SLay sweep_layout(const InstDesc &D, const SweepInst &W, int S, int mode,
                                              bool global_arena, int rs) {
   SLay L{};
@@ -77,7 +78,7 @@ __host__ __device__ inline SLay sweep_layout(const InstDesc &D, const SweepInst 
   L.mx = o;  o = up8(o + (size_t)D.n_steps * S * rs);
   L.phi = o; o = up8(o + (size_t)D.nr * 2 * S * rs);
   L.fab = o; o = up8(o + (size_t)D.nr * S * rs);
-  if (mode == 1) {
+  if (mode == 1 || mode == 3) {
     L.gs = o;  o = up8(o + (size_t)S * rs);
     L.M = o;   o = up8(o + (size_t)D.nr * S * rs);
     L.C = o;   o = up8(o + (size_t)D.n_rr * rs);
@@ -369,16 +370,16 @@ template <typename real, int kMode, bool kGlobal, int kLogS>
 __device__ inline void sweep_tile(const SweepArgs<real> &w, const int tile, char *smem) {
   using FB = SBits<real>;
   using U = typename FB::U;
-  constexpr bool kBwd = kMode == 1, kJet = kMode == 2;
+  constexpr bool kSeg = kMode == 3, kBwd = kMode == 1 || kSeg, kJet = kMode == 2;
   constexpr int kNC = 1 << sweep_walk(kMode, (int)sizeof(real));
   const ContractArgs<real> &a = w.c;
   const int tid = threadIdx.x, lane = tid & 63;
   const int nthr = blockDim.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int q = uload(a.tile_inst + tile);
+  const int q = kSeg ? w.seg.q : uload(a.tile_inst + tile);
   const InstDesc D = uload(a.inst + q);
   constexpr int logS = kLogS, S = 1 << logS, logE = 6 - logS, E = 1 << logE;
-  const int64_t b0 = uload(a.tile_start + tile);
+  const int64_t b0 = kSeg ? w.seg.b0 + tile : uload(a.tile_start + tile);
   const int64_t Bq = uload(a.inst_B + q);
   const int nb = (int)((Bq - b0) < S ? (Bq - b0) : S);
   const int s = lane & (S - 1), lo_ = lane >> logS;
@@ -397,12 +398,25 @@ __device__ inline void sweep_tile(const SweepArgs<real> &w, const int tile, char
   const real beta = (real)D.beta;
 
   // the wave's program, one record loaded ahead
-  const int32_t *pr = w.prog + (int64_t)uload(w.insts[q].prog + wave) * kSweepRec +
+  const int32_t *pr = w.prog + (int64_t)(kSeg ? w.seg.prog[wave] : uload(w.insts[q].prog + wave)) * kSweepRec +
                       (lane < kSweepRec ? lane : kSweepRec - 1);
   int ahead = *pr;
   const int32_t *w_lanes = w.lanes + lo_;
+  real *state = arena + (kSeg ? w.seg.state : 0);
+  if (kSeg && !w.seg.first) {
+    // mx, phi, fab as the launch before left them; M and C too
+    for (int i = tid; i < D.n_steps; i += nthr) mx[i] = reinterpret_cast<const U *>(state)[i];
+    for (int i = tid; i < 2 * D.nr; i += nthr) phi[i] = state[D.n_steps + i];
+    for (int i = tid; i < D.nr; i += nthr) fab[i] = state[D.n_steps + 2 * D.nr + i];
+    if (w.seg.rev) {
+      for (int i = tid; i < D.nr; i += nthr) Mg[i] = state[D.n_steps + 3 * D.nr + i];
+      for (int i = tid; i < D.n_rr; i += nthr) Cw[i] = state[D.n_steps + 4 * D.nr + i];
+    }
+  }
+  if (!kSeg || w.seg.first)
   for (int i = tid; i < D.n_steps * S; i += nthr) mx[i] = 0;
   // unary factors of R, normalised so that the larger of the two is one
+  if (!kSeg || w.seg.first)
   for (int i = tid; i < D.nr * S; i += nthr) {
     const int p = i >> logS, ss = i & (S - 1);
     real f = a.hR[D.hr_off + p];
@@ -420,8 +434,11 @@ __device__ inline void sweep_tile(const SweepArgs<real> &w, const int tile, char
   }
   if constexpr (kBwd) {
     for (int i = tid; i < S; i += nthr)
-      gs[i] = i < nb ? (real)a.grad[a.inst_sample_off[q] + b0 + i] : (real)0;
-    for (int k = tid; k < D.n_rr; k += nthr) Cw[k] = 0;
+      gs[i] = i < nb && (!kSeg || w.seg.rev) ? (real)a.grad[a.inst_sample_off[q] + b0 + i] : (real)0;
+    if (!kSeg || w.seg.first)
+      for (int k = tid; k < D.n_rr; k += nthr) Cw[k] = 0;
+    if (kSeg && w.seg.first)
+      for (int k = tid; k < D.nr; k += nthr) Mg[k] = 0;
   }
   __syncthreads();
 
@@ -594,13 +611,43 @@ __device__ inline void sweep_tile(const SweepArgs<real> &w, const int tile, char
     }
   }
   if constexpr (!kBwd) return;
+  if constexpr (kSeg) {
+    __syncthreads();
+    if (!w.seg.rev) {
+      for (int i = tid; i < D.n_steps; i += nthr) reinterpret_cast<U *>(state)[i] = mx[i];
+      if (w.seg.first) {
+        for (int i = tid; i < 2 * D.nr; i += nthr) state[D.n_steps + i] = phi[i];
+        for (int i = tid; i < D.nr; i += nthr) state[D.n_steps + 2 * D.nr + i] = fab[i];
+      }
+    }
+    if (!w.seg.last) {
+      if (w.seg.first || w.seg.rev) {
+        for (int i = tid; i < D.nr; i += nthr) state[D.n_steps + 3 * D.nr + i] = Mg[i];
+        for (int i = tid; i < D.n_rr; i += nthr) state[D.n_steps + 4 * D.nr + i] = Cw[i];
+      }
+      return;
+    }
+    // the wide steps' sums over their workgroups, one sum per wave at a time
+    for (int i = wave; i < w.seg.n_sums; i += nthr / 64) {
+      const WideSum ws = uload(w.seg.sums + i);
+      const real *p = arena + w.seg.red + ws.first;
+      real v = 0;
+      for (int k = lane; k < ws.n; k += 64) v += p[k * ws.stride];
+      v = lanes_sum<1, 64>(v);
+      if (lane == 0) {
+        if (ws.edge < 0) Mg[-1 - ws.edge] = v;
+        else Cw[ws.edge] = gs[0] * v;
+      }
+    }
+    __syncthreads();
+  }
 
   // ------------------------------------------------- per-tile partial row
   int q2 = q;
   asm volatile("" : "+s"(q2));
   const InstDesc D2 = uload(a.inst + q2);
   const int64_t prow = uload(a.inst_partial_off + q2) +
-                       (int64_t)(tile - uload(a.inst_first_tile + q2)) * D2.n_partial;
+                       (kSeg ? b0 : (int64_t)(tile - uload(a.inst_first_tile + q2))) * D2.n_partial;
   for (int p = tid; p < D2.nr; p += nthr) {
     real acc = 0;
     for (int k = 0; k < S; ++k) acc += gs[k] * Mg[p * S + k];
@@ -662,6 +709,19 @@ hipError_t launch_sweep(const SweepArgs<real> &a, int n_tiles, size_t lds, int m
   return hipGetLastError();
 }
 
+template <typename real>
+hipError_t launch_sweep_segment(const SweepArgs<real> &a, int n_samples, size_t lds, hipStream_t st) {
+  if (n_samples <= 0) return hipSuccess;
+  void (*k)(SweepArgs<real>, int) = sweep_kernel<real, 3, true, 0>;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k, dim3(n_samples), dim3(64 * kSweepWaves), lds, st, a, n_samples);
+  return hipGetLastError();
+}
+
+template hipError_t launch_sweep_segment<float>(const SweepArgs<float> &, int, size_t, hipStream_t);
+template hipError_t launch_sweep_segment<double>(const SweepArgs<double> &, int, size_t, hipStream_t);
 template hipError_t launch_sweep<float>(const SweepArgs<float> &, int, size_t, int, bool, int, int, hipStream_t);
 template hipError_t launch_sweep<double>(const SweepArgs<double> &, int, size_t, int, bool, int, int, hipStream_t);
 

@@ -230,11 +230,137 @@ static void check(const HostProgram &P, int S, int waves, int walk) {
   }
 }
 
+// The segments of a program with wide steps: every step once, after its
+// inputs; the wide steps' tables cover every entry and index every input as
+// the program does; every sum over an input's missing bits is whole.
+static void check_wide(const HostProgram &P) {
+  const InstDesc &D = P.insts[0];
+  const StepDesc *st = P.steps.data() + D.step_off;
+  WidePlan pl;
+  build_wide(P, {1}, pl);
+  std::vector<int> made(D.n_steps, 0), back(D.n_steps, 0);
+  int closed = 0;
+  size_t n_sums = 0;
+  auto whole = [&](int t) {
+    for (int k = 0; k < st[t].n_in; ++k) CHECK(made[P.inputs[st[t].in_off + k].step] == 1 << st[P.inputs[st[t].in_off + k].step].w);
+  };
+  for (auto &sg : pl.segs.at(0)) {
+    for (int rev = 0; rev < 2; ++rev) {
+      // records by the barriers before them
+      std::vector<std::vector<const int32_t *>> phases;
+      size_t total = 0;
+      for (int k = 0; k < kSweepWaves; ++k) {
+        size_t ph = 0;
+        for (int64_t i = rev ? sg.bwd[k] : sg.fwd[k];; ++i) {
+          CHECK((i + 2) * kSweepRec <= (int64_t)pl.prog.size());
+          const int32_t *r = &pl.prog.at(i * kSweepRec);
+          ph += (r[0] >> 4) & 0xff;
+          if (phases.size() <= ph) phases.resize(ph + 1);
+          if ((r[0] & 15) == SWEEP_END) break;
+          phases[ph].push_back(r);
+        }
+        if (k == 0) total = ph;
+        CHECK(ph == total);
+      }
+      for (auto &ph : phases) {
+        std::vector<std::pair<int, int>> add;
+        for (const int32_t *r : ph) {
+          const int op = r[0] & 15, t = r[4] & 0xffff;
+          if (op == SWEEP_LOGZ) ++closed;
+          if (op != SWEEP_FWD && op != SWEEP_JOINT) continue;
+          CHECK(st[t].w < kWideStep && (op == SWEEP_JOINT) == (rev == 1));
+          if (!rev) whole(t);
+          add.push_back({t, 1 << ((r[0] >> 24) & 15)});
+        }
+        for (auto &a : add) (rev ? back : made)[a.first] += a.second;
+      }
+    }
+    for (auto &g : sg.groups) {
+      int blocks = 0, fblocks = 0;
+      std::vector<int> part_use(pl.part.at(0), 0);
+      for (int i = g.w0; i < g.w1; ++i) whole(pl.steps.at(i).step);
+      for (int i = g.w0; i < g.w1; ++i) {
+        const WideStep &w = pl.steps.at(i);
+        const StepDesc &sd = st[w.step];
+        const int nb = 1 << (w.w - kWideChunk), high = kWideThreads + kWideRegs;
+        blocks += nb;
+        CHECK(w.w == sd.w && w.w >= kWideStep && w.gpos == sd.gpos && w.off == sd.off_all &&
+              w.n_in == sd.n_in && w.n_edge == sd.n_edge && w.t_off == sd.t_off);
+        CHECK(w.red + nb * (1 + w.n_edge) <= pl.red.at(0));
+        n_sums += 1 + w.n_edge;
+        std::vector<int> seen(1 << w.w, 0);
+        auto at = [&](int tab, int c, int b) {
+          return pl.tab.at(tab + c % kWideThreads) | pl.tab.at(tab + kWideThreads + c / kWideThreads) |
+                 pl.tab.at(tab + high + b);
+        };
+        for (int b = 0; b < nb; ++b)
+          for (int c = 0; c < 1 << kWideChunk; ++c) {
+            const int o = at(w.out, c, b);
+            CHECK((o & 31) == (c & 31));
+            ++seen.at(o);
+          }
+        for (int n : seen) CHECK(n == 1);
+        for (int k = 0; k < w.n_in; ++k) {
+          const InputDesc &id = P.inputs[sd.in_off + k];
+          const WideInput &in = w.in[k];
+          CHECK(in.off == st[id.step].off_all && in.step == id.step && in.bits == id.nbits &&
+                in.xbit == id.xbit && id.nbits == st[id.step].w);
+          const int ns = kWideChunk - __builtin_popcount((unsigned)in.free);
+          // terms each entry's sums take (spin +1), by row
+          const WideFin *fin = nullptr;
+          for (int f = g.f0; f < g.f1; ++f)
+            if (in.part >= 0 && pl.fins.at(f).part == in.part) fin = &pl.fins.at(f);
+          CHECK((in.part >= 0) == (fin != nullptr));
+          if (fin) {
+            CHECK(fin->off == in.off && fin->step == in.step && fin->nbits == in.bits);
+            CHECK(fin->first == fblocks);
+            fblocks += std::max(1, (1 << fin->nbits) / kWideThreads);
+          }
+          const int rows = fin ? fin->rows : 1;
+          std::vector<int> terms((size_t)rows << id.nbits, 0);
+          for (int b = 0; b < nb; ++b) {
+            const int row = fin ? pl.tab.at(in.row + b) : 0;
+            CHECK(row < rows);
+            for (int e = 0; e < 1 << ns; ++e) {
+              const uint32_t d = (uint32_t)pl.tab.at(in.dep + e);
+              const int c0 = (int)(d & ((1u << kWideChunk) - 1));
+              const int j = pl.tab.at(in.idx + high + b) | (int)(d >> kWideChunk);
+              CHECK(!(c0 & in.free));
+              for (int z = 0, m = 0; m < 1 << (kWideChunk - ns); ++m, z = (z - in.free) & in.free) {
+                const int o = at(w.out, c0 | z, b);
+                int want = 0;
+                for (int x = 0; x < id.nbits; ++x)
+                  if (id.src[x] >= 0) want |= ((o >> id.src[x]) & 1) << x;
+                CHECK(want == j && want == at(in.idx, c0 | z, b));
+              }
+              ++terms.at(((size_t)row << id.nbits) + j);
+            }
+          }
+          for (int r = 0; r < rows; ++r)
+            for (int j = 0; j < 1 << id.nbits; ++j) {
+              CHECK(terms[((size_t)r << id.nbits) + j] == !((j >> id.xbit) & 1));
+              if (fin) ++part_use.at(fin->part + (r << id.nbits) + j);
+            }
+          const int nf = w.w - (id.nbits - 1);
+          CHECK(((kWideChunk - ns) == nf) == (rows == 1) && rows == 1 << (nf - (kWideChunk - ns)));
+        }
+      }
+      for (int n : part_use) CHECK(n <= 1);
+      for (int i = g.w0; i < g.w1; ++i) made[pl.steps[i].step] = back[pl.steps[i].step] = 1 << pl.steps[i].w;
+      CHECK(blocks == g.blocks && fblocks == g.fblocks);
+    }
+  }
+  for (int t = 0; t < D.n_steps; ++t) CHECK(made[t] == 1 << st[t].w && back[t] == 1 << st[t].w);
+  CHECK(closed == 1 && n_sums == pl.sums.size() && pl.sum_lo.at(1) == (int)pl.sums.size());
+}
+
 int main() {
   std::mt19937_64 rng(5);
   int done = 0;
-  for (int trial = 0; trial < 60; ++trial) {
-    const int n = 6 + (int)(rng() % 60), d = 1 + (int)(rng() % 3);
+  int wide = 0;
+  for (int trial = 0; trial < 90; ++trial) {
+    // (the last thirty: wide programs)
+    const int n = trial < 60 ? 6 + (int)(rng() % 60) : 45 + (int)(rng() % 20), d = trial < 60 ? 1 + (int)(rng() % 3) : 3;
     std::vector<std::vector<char>> adj(n, std::vector<char>(n, 0));
     std::vector<int32_t> ei, ej, W, order;
     std::vector<double> J;
@@ -250,7 +376,7 @@ int main() {
     std::vector<int> perm(n);
     for (int i = 0; i < n; ++i) perm[i] = i;
     std::shuffle(perm.begin(), perm.end(), rng);
-    const int m = (int)(rng() % (n / 2));
+    const int m = trial < 60 ? (int)(rng() % (n / 2)) : (int)(rng() % 6);
     for (int i = 0; i < n; ++i) (i < m ? W : order).push_back(perm[i]);
     std::vector<double> h(n, 0.1);
     tnvan_instance in{};
@@ -267,12 +393,18 @@ int main() {
     in.order = order.data();
     HostProgram P;
     std::string msg;
+    if (trial >= 60) {
+      if (compile_instance(in, 17, P, msg) != TNVAN_OK || P.insts[0].max_w < kWideStep || !wide_fits(P, 0)) continue;
+      ++wide;
+      check_wide(P);
+      continue;
+    }
     if (compile_instance(in, 12, P, msg) != TNVAN_OK || !sweep_fits(P, 0)) continue;
     ++done;
     for (int S : {1, 2, 4, 16, 64})
       for (int walk = 0; walk <= kSweepWalk; ++walk) check(P, S, 1 << (int)(rng() % 4), walk);
   }
-  if (g_fail || done < 20) return std::fprintf(stderr, "%d failed, %d programs\n", g_fail, done), 1;
-  std::printf("sweep schedule ok (%d programs)\n", done);
+  if (g_fail || done < 20 || wide < 5) return std::fprintf(stderr, "%d failed, %d and %d programs\n", g_fail, done, wide), 1;
+  std::printf("sweep schedule ok (%d programs, %d with wide steps)\n", done, wide);
   return 0;
 }
