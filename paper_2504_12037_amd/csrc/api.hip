@@ -2367,12 +2367,24 @@ tnvan_status tnvan_build_network(const tnvan_instance *inst, int32_t n_inst,
     for (int pass = 0; pass < 2 && any; ++pass) {
       const bool bwd = pass == 1;
       ChainLim L = lim;
-      L.wpb = 1;
+      L.wpb = L.spw = 1;
       if (bwd ? net->rbwd : net->rfwd) {
         (bwd ? net->lim_bwd : net->lim_fwd) = L;
         continue;
       }
       L.tlds = 1;
+      // more than 64 states: eight waves per 16 samples where their sums fit
+      // (a 64-spin SK model's 6144 samples: forward 75 us on one wave and 30
+      // on eight, adjoint 945 and 139)
+      if (lim.kbuf > 64) {
+        L.spw = kChainSplit;
+        if (chain_shared_lds(L, bwd, bf && !bwd) + chain_wave_lds(L, bwd) > (size_t)maxlds) L.tlds = 0;
+        if (chain_shared_lds(L, bwd, bf && !bwd) + chain_wave_lds(L, bwd) <= (size_t)maxlds) {
+          (bwd ? net->lim_bwd : net->lim_fwd) = L;
+          continue;
+        }
+        L.spw = L.tlds = 1;
+      }
       size_t sh = chain_shared_lds(L, bwd, bf && !bwd), per = chain_wave_lds(L, bwd);
       if (sh + per > (size_t)maxlds) {   // tables too large: read them from HBM
         L.tlds = 0;

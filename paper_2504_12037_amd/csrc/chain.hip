@@ -7,7 +7,8 @@
 //   A_0 = d_0,  out_t = A_t . T_t,  A_{t+1} = d_{t+1} * (out_t / 2^e_t)
 //
 // where A_t is [16 samples x K] and T_t is [K x N].  A workgroup takes one
-// chain and 16 samples per wave.  It first copies the chain's transfer
+// chain and 16 samples per wave, or, for chains of more than 64 states, 16
+// samples on eight waves (below).  It first copies the chain's transfer
 // tables, edge list and W-neighbour lists into LDS with coalesced loads (a
 // chain walks its tables in order, so reading them step by step from HBM
 // would expose one memory latency per step).  Each wave then runs its
@@ -29,6 +30,17 @@
 // and writes the gradient-weighted sums of one 16-sample group into one
 // partial row (every entry of the row is owned by exactly one chain).  The
 // adjoint uses FP32 products in both the FP32 and the BF16 precisions.
+//
+// Steps of more than 64 states: a wave that takes its 16 samples alone holds
+// 16 output tiles, one wave per SIMD at most and a third of a batch of 6144
+// samples' SIMDs idle, and walks 256 states serially in the adjoint's sums.
+// There eight waves share a group (kW): each has the output tiles, the
+// states of Lambda and the rows of H of its own, a step's row maxima and
+// magnetisations meet in LDS, and barriers take the place of the wave's own
+// order.  The products of a tile run over k in the same order, so ln Z_R has
+// the same bits.  Measured on a 64-spin SK model (16 remainder spins, 256 x
+// 256 tables), 6144 samples: forward 75 -> 30 us, adjoint 945 -> 139 us (171
+// with one workgroup per CU).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -59,10 +71,13 @@ __host__ __device__ inline SL shared_layout(const ChainLim &L, bool bwd, bool bf
   size_t o = 0;
   s.tl = o;
   if (L.tlds) o = al16(o + ((bf16 && !bwd) ? (size_t)L.tbl_max * 2 : (size_t)L.tl_max * 4));
-  s.ce = o;  o = al16(o + (size_t)L.ne_max * sizeof(EdgeDesc));
+  // (several waves per group: edges and W-R edge numbers stay in device
+  // memory, so that two workgroups fit a CU)
+  const bool wide = L.spw > 1;
+  s.ce = o;  if (!wide) o = al16(o + (size_t)L.ne_max * sizeof(EdgeDesc));
   s.fp = o;  o = al16(o + (size_t)(L.npos_max + 1) * 4);
   s.fw = o;  o = al16(o + (size_t)L.nf_max * 4);
-  s.fwr = o; o = al16(o + (size_t)L.nf_max * 4);
+  s.fwr = o; if (!wide) o = al16(o + (size_t)L.nf_max * 4);
   s.fj = o;  o = al16(o + (size_t)L.nf_max * 4);
   s.end = o;
   return s;
@@ -71,7 +86,7 @@ __host__ __device__ inline SL shared_layout(const ChainLim &L, bool bwd, bool bf
 // Per-wave LDS layout.
 struct WL {
   int lda;
-  size_t sp, phi, dt, lz, es, A0, gs, raw, ex, M, pb, R0, R1, seg, buf, end;
+  size_t sp, phi, dt, lz, es, A0, gs, raw, ex, M, pb, R0, R1, seg, mx, ms, af, buf, end;
 };
 __host__ __device__ inline WL wave_layout(const ChainLim &C, bool bwd) {
   WL L{};
@@ -89,10 +104,17 @@ __host__ __device__ inline WL wave_layout(const ChainLim &C, bool bwd) {
     L.raw = o; o = al16(o + CW * 4);
     L.ex = o;  o = al16(o + (size_t)C.max_steps * CW * 4);
     L.M = o;   o = al16(o + (size_t)kGM * CW * 4);
-    L.pb = o;  o = al16(o + (size_t)C.pmax * 4);
+    // (at most kbuf (w + 1) entries: they fit the diagonal's place)
+    if (C.spw > 1) L.pb = L.dt;
+    else { L.pb = o;  o = al16(o + (size_t)C.pmax * 4); }
     L.R0 = o;  o += L.buf;
     L.R1 = o;  o += L.buf;
     L.seg = o; o += (size_t)(C.kseg > 1 ? C.kseg - 1 : 0) * L.buf;
+  }
+  if (C.spw > 1) {
+    L.mx = o; o = al16(o + (size_t)C.spw * CW * 4);
+    if (bwd) { L.ms = o; o = al16(o + (size_t)C.spw * kGM * CW * 4); }
+    else { L.af = o; o = al16(o + (size_t)C.npos_max * CW * 4); }
   }
   L.end = al16(o);
   return L;
@@ -105,12 +127,24 @@ __device__ inline float tval(const ChainArgs &a, const float *tl, const ChainSte
   return kTL ? tl[cs.tl_off + x * (cs.np + 1) + o] : a.Tp[cs.tp_off + x * cs.np + o];
 }
 
+// The waves of a group: wave `sub` of kW, `tid` of its threads.
+template <int kW>
+struct Team {
+  int sub, tid;
+  static constexpr int n = 64 * kW;
+  __device__ void sync() const {
+    if constexpr (kW > 1) __syncthreads();
+    else wsync();
+  }
+};
+
 // d[s][x] = prod_j phi_j(s, x_j) of a group of g spins starting at chain
 // position po, into dst (row stride ld); entries x in [2^g, zero_to) are set
 // to zero.  Lane (s = lane & 15) produces x = (lane >> 4) + 4m: the two low
 // bits are fixed per lane, so each entry costs g - 2 multiplications.
-__device__ inline void build_diag(int g, int po, const float *phi, float *dst, int ld,
-                                  int zero_to, int lane) {
+template <int kW>
+__device__ inline void build_diag(const Team<kW> &tm, int g, int po, const float *phi, float *dst,
+                                  int ld, int zero_to, int lane) {
   const int s = lane & 15, lg = lane >> 4, K = 1 << g;
   float p0[kGM], p1[kGM];
 #pragma unroll
@@ -123,7 +157,7 @@ __device__ inline void build_diag(int g, int po, const float *phi, float *dst, i
   for (int j = 0; j < 2; ++j)
     if (j < g) lo *= ((lg >> j) & 1) ? p1[j] : p0[j];
   const int top = K > zero_to ? K : zero_to;
-  for (int m = 0; 4 * m + lg < top; ++m) {
+  for (int m = tm.sub; 4 * m + lg < top; m += kW) {
     const int x = 4 * m + lg;
     float v = 0.f;
     if (x < K) {
@@ -139,34 +173,36 @@ __device__ inline void build_diag(int g, int po, const float *phi, float *dst, i
 // One forward step of a chain for the wave's 16 samples: Aout <- scaled
 // product times the next step's diagonal (dtab, built here).  Returns the
 // per-row exponents.
-template <bool kBF, bool kTL, int NTM>
-__device__ inline void chain_step(const ChainArgs &a, const void *tsh, const ChainStep &cs,
+template <bool kBF, bool kTL, int NTM, int kW>
+__device__ inline void chain_step(const Team<kW> &tm, float *mx, const ChainArgs &a, const void *tsh, const ChainStep &cs,
                                   const ChainStep &nx, const float *Ain, float *Aout, float *dtab,
                                   int lda, int kbuf, const float *phi, int pos_lo, int lane,
                                   int e[4]) {
   const int ls = lane & 15, lg = lane >> 4;
-  const int NT = cs.np >> 4;
-  build_diag(nx.g, nx.gpos - pos_lo, phi, dtab, lda, 0, lane);
-  f4 acc[NTM];
+  // the wave's tiles nt0 + nt
+  constexpr int TP = NTM / kW;
+  const int nt0 = tm.sub * TP, NT = (cs.np >> 4) - nt0;
+  build_diag(tm, nx.g, nx.gpos - pos_lo, phi, dtab, lda, 0, lane);
+  f4 acc[TP];
 #pragma unroll
-  for (int nt = 0; nt < NTM; ++nt) acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
+  for (int nt = 0; nt < TP; ++nt) acc[nt] = f4{0.f, 0.f, 0.f, 0.f};
   if (!kBF) {
     const float *tl = static_cast<const float *>(tsh);
     const float *ap = Ain + ls * lda + lg;
     const int KC = cs.kp >> 2;        // a multiple of 4
     for (int k0 = 0; k0 < KC; k0 += 4) {
-      float av[4], bv[4][NTM];
+      float av[4], bv[4][TP];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         av[u] = ap[4 * (k0 + u)];
 #pragma unroll
-        for (int nt = 0; nt < NTM; ++nt)
-          if (nt < NT) bv[u][nt] = tval<kTL>(a, tl, cs, 4 * (k0 + u) + lg, 16 * nt + ls);
+        for (int nt = 0; nt < TP; ++nt)
+          if (nt < NT) bv[u][nt] = tval<kTL>(a, tl, cs, 4 * (k0 + u) + lg, 16 * (nt0 + nt) + ls);
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int nt = 0; nt < NTM; ++nt)
+        for (int nt = 0; nt < TP; ++nt)
           if (nt < NT) acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[u][nt], acc[nt], 0, 0, 0);
     }
   } else {
@@ -180,9 +216,9 @@ __device__ inline void chain_step(const ChainArgs &a, const void *tsh, const Cha
 #pragma unroll
       for (int i = 0; i < 8; ++i) av[i] = (__bf16)ap[i];
 #pragma unroll
-      for (int nt = 0; nt < NTM; ++nt)
+      for (int nt = 0; nt < TP; ++nt)
         if (nt < NT) {
-          const u4v raw = tb[(nt * KC + kc) * 64];
+          const u4v raw = tb[((nt0 + nt) * KC + kc) * 64];
           const bf8 bv = __builtin_bit_cast(bf8, raw);
           acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[nt], 0, 0, 0);
         }
@@ -190,28 +226,41 @@ __device__ inline void chain_step(const ChainArgs &a, const void *tsh, const Cha
   }
   float m[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int nt = 0; nt < NTM; ++nt)
+  for (int nt = 0; nt < TP; ++nt)
     if (nt < NT)
 #pragma unroll
       for (int r = 0; r < 4; ++r) m[r] = fmaxf(m[r], acc[nt][r]);
   float sc[4];
 #pragma unroll
+  for (int r = 0; r < 4; ++r) m[r] = row16_max(m[r]);
+  if constexpr (kW > 1) {
+    if (ls == 0)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mx[tm.sub * CW + 4 * lg + r] = m[r];
+  }
+  tm.sync();   // every read of Ain precedes the writes (Aout may alias Ain)
+  if constexpr (kW > 1) {
+#pragma unroll
+    for (int k = 0; k < kW; ++k)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) m[r] = fmaxf(m[r], mx[k * CW + 4 * lg + r]);
+  }
+#pragma unroll
   for (int r = 0; r < 4; ++r) {
-    e[r] = expo32(row16_max(m[r]));
+    e[r] = expo32(m[r]);
     sc[r] = pow2neg(e[r]);
   }
-  wsync();   // every read of Ain precedes the writes (Aout may alias Ain)
   const int N = 1 << cs.w;
 #pragma unroll
-  for (int nt = 0; nt < NTM; ++nt)
+  for (int nt = 0; nt < TP; ++nt)
     if (nt < NT)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int o = 16 * nt + ls, s = 4 * lg + r;
+        const int o = 16 * (nt0 + nt) + ls, s = 4 * lg + r;
         Aout[s * lda + o] = o < N ? acc[nt][r] * sc[r] * dtab[s * lda + o] : 0.f;
       }
-  for (int i = lane; i < CW * (kbuf - cs.np); i += 64) Aout[(i & 15) * lda + cs.np + (i >> 4)] = 0.f;
-  wsync();
+  for (int i = tm.tid; i < CW * (kbuf - cs.np); i += tm.n) Aout[(i & 15) * lda + cs.np + (i >> 4)] = 0.f;
+  tm.sync();
 }
 
 // raw root value sum_x A[s][x] T[x] of sample (lane & 15), on every lane
@@ -221,6 +270,7 @@ __device__ inline float chain_root(const ChainArgs &a, const float *tl, const Ch
   const int ls = lane & 15, lg = lane >> 4;
   const int K = 1 << cs.g;
   float part = 0.f;
+#pragma unroll 8
   for (int x = lg; x < K; x += 4) part += A[ls * lda + x] * tval<kTL>(a, tl, cs, x, 0);
   part += __shfl_xor(part, 16, 64);
   part += __shfl_xor(part, 32, 64);
@@ -228,9 +278,10 @@ __device__ inline float chain_root(const ChainArgs &a, const float *tl, const Ch
 }
 
 // the wave's 16 samples' width-set spins into LDS (zero for padding rows)
-__device__ inline void stage_spins(const int8_t *src, int8_t *dst, int nw, int nb, int lane) {
-  for (int i = lane; i < CW * nw; i += 64) dst[i] = i < nb * nw ? src[i] : (int8_t)0;
-  wsync();
+template <int kW>
+__device__ inline void stage_spins(const Team<kW> &tm, const int8_t *src, int8_t *dst, int nw, int nb) {
+  for (int i = tm.tid; i < CW * nw; i += tm.n) dst[i] = i < nb * nw ? src[i] : (int8_t)0;
+  tm.sync();
 }
 
 // Copy the chain's tables, edges and W-neighbour lists into the workgroup's
@@ -250,6 +301,7 @@ __device__ inline void stage_chain(const ChainArgs &a, const InstDesc &D, const 
     }
   }
   EdgeDesc *ce = reinterpret_cast<EdgeDesc *>(sh + S.ce);
+  if (a.lim.spw == 1)
   for (int i = threadIdx.x; i < cd.n_e; i += blockDim.x) ce[i] = a.cedges[cd.e_src + i];
   int32_t *fp = reinterpret_cast<int32_t *>(sh + S.fp);
   const int npos = cd.pos_hi - cd.pos_lo;
@@ -260,15 +312,17 @@ __device__ inline void stage_chain(const ChainArgs &a, const InstDesc &D, const 
   float *fj = reinterpret_cast<float *>(sh + S.fj);
   for (int i = threadIdx.x; i < cd.f_hi - cd.f_lo; i += blockDim.x) {
     fw[i] = a.fld_w[D.fld_nnz_off + cd.f_lo + i];
-    fwr[i] = a.fld_wr[D.fld_nnz_off + cd.f_lo + i];
+    if (a.lim.spw == 1) fwr[i] = a.fld_wr[D.fld_nnz_off + cd.f_lo + i];
     fj[i] = a.fld_J[D.fld_nnz_off + cd.f_lo + i];
   }
   __syncthreads();
 }
 
 // unary factors of the chain's positions, normalised to max 1; returns the
-// sum of beta |f| of sample (lane & 15)
-__device__ inline double chain_phi(const ChainArgs &a, const InstDesc &D, const ChainDesc &cd,
+// sum of beta |f| of sample (lane & 15), each lane over every fourth
+// position (af: the terms where several waves share them, or null for no sum)
+template <int kW>
+__device__ inline double chain_phi(const Team<kW> &tm, float *afs, const ChainArgs &a, const InstDesc &D, const ChainDesc &cd,
                                    const char *sh, const SL &S, const int8_t *spl, float *phi,
                                    int nb, int lane) {
   const int32_t *fp = reinterpret_cast<const int32_t *>(sh + S.fp);
@@ -277,32 +331,40 @@ __device__ inline double chain_phi(const ChainArgs &a, const InstDesc &D, const 
   double fab = 0.0;
   const int npos = cd.pos_hi - cd.pos_lo;
   const float beta = (float)D.beta;
-  for (int i = lane; i < npos * CW; i += 64) {
+  for (int i = tm.tid; i < npos * CW; i += tm.n) {
     const int pl = i >> 4, s = i & 15;
     float f = a.hR[D.hr_off + cd.pos_lo + pl];
     if (s < nb) {
       const int8_t *sp = spl + s * D.nw;
+#pragma unroll 8
       for (int k = fp[pl]; k < fp[pl + 1]; ++k) f += fj[k] * (float)sp[fw[k]];
     }
     const float af = beta * fabsf(f);
     const float sm = expf(-2.f * af);
     phi[(pl * 2) * CW + s] = f >= 0.f ? 1.f : sm;
     phi[(pl * 2 + 1) * CW + s] = f >= 0.f ? sm : 1.f;
-    fab += (double)af;
+    if constexpr (kW == 1) fab += (double)af;
+    else if (afs) afs[i] = af;
+  }
+  tm.sync();
+  if constexpr (kW > 1) {
+    if (afs)
+      for (int i = lane; i < npos * CW; i += 64) fab += (double)afs[i];
   }
   fab += __shfl_xor(fab, 16, 64);
   fab += __shfl_xor(fab, 32, 64);
-  wsync();
   return fab;
 }
 
-template <bool kBF, bool kTL, int NTM>
-__global__ __launch_bounds__(256) void chain_fwd_kernel(ChainArgs a) {
+template <bool kBF, bool kTL, int NTM, int kW>
+__global__ __launch_bounds__(kW > 1 ? 64 * kW : 256) void chain_fwd_kernel(ChainArgs a) {
   extern __shared__ __align__(16) char smem[];
   // the wave index is uniform inside a wave; saying so keeps every task and
   // step descriptor in scalar registers and the control flow uniform
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int wave = kW > 1 ? 0 : wv;   // the group
   const int lane = threadIdx.x & 63;
+  const Team<kW> tm = kW > 1 ? Team<kW>{wv, (int)threadIdx.x} : Team<kW>{0, lane};
   const int q = a.task_inst[blockIdx.x], c = a.task_chain[blockIdx.x];
   const InstDesc D = a.inst[q];
   const ChainInst C = a.cinst[q];
@@ -322,10 +384,12 @@ __global__ __launch_bounds__(256) void chain_fwd_kernel(ChainArgs a) {
   int *es = reinterpret_cast<int *>(base + L.es);
   float *A = reinterpret_cast<float *>(base + L.A0);
   int8_t *spl = reinterpret_cast<int8_t *>(base + L.sp);
-  stage_spins(a.spins + a.inst_spin_off[q] + b0 * D.nw, spl, D.nw, nb, lane);
-  const double fab = chain_phi(a, D, cd, smem, S, spl, phi, nb, lane);
-  build_diag(cs[0].g, cs[0].gpos - cd.pos_lo, phi, A, L.lda, a.lim.kbuf, lane);
-  wsync();
+  float *mx = reinterpret_cast<float *>(base + L.mx);
+  stage_spins(tm, a.spins + a.inst_spin_off[q] + b0 * D.nw, spl, D.nw, nb);
+  const double fab = chain_phi(tm, reinterpret_cast<float *>(base + L.af), a, D, cd, smem, S, spl,
+                               phi, nb, lane);
+  build_diag(tm, cs[0].g, cs[0].gpos - cd.pos_lo, phi, A, L.lda, a.lim.kbuf, lane);
+  tm.sync();
   int esum[4] = {0, 0, 0, 0};
   float raw = 1.f;
   for (int t = 0; t < cd.n_steps; ++t) {
@@ -335,11 +399,12 @@ __global__ __launch_bounds__(256) void chain_fwd_kernel(ChainArgs a) {
       break;
     }
     int e[4];
-    chain_step<kBF, kTL, NTM>(a, tsh, st, cs[t + 1], A, A, dtab, L.lda, a.lim.kbuf, phi,
+    chain_step<kBF, kTL, NTM, kW>(tm, mx, a, tsh, st, cs[t + 1], A, A, dtab, L.lda, a.lim.kbuf, phi,
                               cd.pos_lo, lane, e);
 #pragma unroll
     for (int r = 0; r < 4; ++r) esum[r] += e[r];
   }
+  if (tm.sub != 0) return;
   if ((lane & 15) == 0) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) es[4 * (lane >> 4) + r] = esum[r];
@@ -351,11 +416,13 @@ __global__ __launch_bounds__(256) void chain_fwd_kernel(ChainArgs a) {
   }
 }
 
-template <bool kTL, int NTM>
-__global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
+template <bool kTL, int NTM, int kW>
+__global__ __launch_bounds__(kW > 1 ? 64 * kW : 256, kW > 1 ? 4 : 1) void chain_bwd_kernel(ChainArgs a) {
   extern __shared__ __align__(16) char smem[];
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int wave = kW > 1 ? 0 : wv;   // the group
   const int lane = threadIdx.x & 63;
+  const Team<kW> tm = kW > 1 ? Team<kW>{wv, (int)threadIdx.x} : Team<kW>{0, lane};
   const int ls = lane & 15, lg = lane >> 4;
   const int q = a.task_inst[blockIdx.x], c = a.task_chain[blockIdx.x];
   const InstDesc D = a.inst[q];
@@ -365,10 +432,11 @@ __global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
   const SL S = shared_layout(a.lim, true, false);
   stage_chain<false>(a, D, cd, smem, S);
   const float *tl = reinterpret_cast<const float *>(smem + S.tl);
-  const EdgeDesc *ce = reinterpret_cast<const EdgeDesc *>(smem + S.ce);
+  const EdgeDesc *ce = kW > 1 ? a.cedges + cd.e_src : reinterpret_cast<const EdgeDesc *>(smem + S.ce);
   const int32_t *fp = reinterpret_cast<const int32_t *>(smem + S.fp);
   const int32_t *fw = reinterpret_cast<const int32_t *>(smem + S.fw);
-  const int32_t *fwr = reinterpret_cast<const int32_t *>(smem + S.fwr);
+  const int32_t *fwr = kW > 1 ? a.fld_wr + D.fld_nnz_off + cd.f_lo
+                              : reinterpret_cast<const int32_t *>(smem + S.fwr);
   const int64_t Bq = a.inst_B[q];
   const int64_t b0 = a.task_start[blockIdx.x] + (int64_t)wave * CW;
   if (b0 >= Bq) return;
@@ -388,46 +456,48 @@ __global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
   float *Rc = reinterpret_cast<float *>(base + L.R0);
   float *Rn = reinterpret_cast<float *>(base + L.R1);
   int8_t *spl = reinterpret_cast<int8_t *>(base + L.sp);
+  float *mx = reinterpret_cast<float *>(base + L.mx), *mred = reinterpret_cast<float *>(base + L.ms);
+  constexpr int TP = NTM / kW;   // tiles per wave
   const int T = cd.n_steps;
   const int NC = (T + kseg - 1) / kseg;
   // checkpoints of this wave: NC buffers of [16][kbuf] in HBM
   float *ckw = a.ckpt + ((int64_t)blockIdx.x * a.lim.wpb + wave) *
                             (int64_t)((a.lim.max_steps + kseg - 1) / kseg) * CW * kbuf;
-  stage_spins(a.spins + a.inst_spin_off[q] + b0 * D.nw, spl, D.nw, nb, lane);
-  chain_phi(a, D, cd, smem, S, spl, phi, nb, lane);
-  if (lane < CW) gs[lane] = lane < nb ? (float)a.grad[a.inst_sample_off[q] + b0 + lane] : 0.f;
+  stage_spins(tm, a.spins + a.inst_spin_off[q] + b0 * D.nw, spl, D.nw, nb);
+  chain_phi(tm, nullptr, a, D, cd, smem, S, spl, phi, nb, lane);
+  if (tm.tid < CW) gs[lane] = lane < nb ? (float)a.grad[a.inst_sample_off[q] + b0 + lane] : 0.f;
   const int64_t row = a.inst_partial_off[q] + (b0 / CW) * (int64_t)D.n_partial;
   float *prow = a.partial + row;
   auto save_ck = [&](int i, const float *A) {
     float *dst = ckw + (int64_t)i * CW * kbuf;
-    for (int k = lane; k < CW * kbuf; k += 64) dst[k] = A[(k / kbuf) * lda + k % kbuf];
+    for (int k = tm.tid; k < CW * kbuf; k += tm.n) dst[k] = A[(k / kbuf) * lda + k % kbuf];
   };
   auto load_ck = [&](int i, float *A) {
     const float *src = ckw + (int64_t)i * CW * kbuf;
-    for (int k = lane; k < CW * kbuf; k += 64) A[(k / kbuf) * lda + k % kbuf] = src[k];
-    wsync();
+    for (int k = tm.tid; k < CW * kbuf; k += tm.n) A[(k / kbuf) * lda + k % kbuf] = src[k];
+    tm.sync();
   };
 
   // forward, saving A every kseg steps
-  build_diag(cs[0].g, cs[0].gpos - cd.pos_lo, phi, A0, lda, kbuf, lane);
-  wsync();
+  build_diag(tm, cs[0].g, cs[0].gpos - cd.pos_lo, phi, A0, lda, kbuf, lane);
+  tm.sync();
   for (int t = 0; t < T; ++t) {
     const ChainStep st = cs[t];
     if (t % kseg == 0) save_ck(t / kseg, A0);
     if (st.w == 0) {
       const float raw = chain_root<kTL>(a, tl, st, A0, lda, lane);
-      if (lane < CW) rawb[lane] = raw;
-      wsync();
+      if (tm.tid < CW) rawb[lane] = raw;
+      tm.sync();
       break;
     }
     int e[4];
-    chain_step<false, kTL, NTM>(a, tl, st, cs[t + 1], A0, A0, dtab, lda, kbuf, phi, cd.pos_lo,
+    chain_step<false, kTL, NTM, kW>(tm, mx, a, tl, st, cs[t + 1], A0, A0, dtab, lda, kbuf, phi, cd.pos_lo,
                                 lane, e);
-    if (ls == 0) {
+    if (ls == 0 && tm.sub == 0) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) ex[t * CW + 4 * lg + r] = e[r];
     }
-    wsync();
+    tm.sync();
   }
 
   for (int seg = NC - 1; seg >= 0; --seg) {
@@ -439,7 +509,7 @@ __global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
     load_ck(seg, A0);
     for (int t = t0; t < t1 - 1; ++t) {
       int e[4];
-      chain_step<false, kTL, NTM>(a, tl, cs[t], cs[t + 1], sbuf(t - t0), sbuf(t + 1 - t0), dtab,
+      chain_step<false, kTL, NTM, kW>(tm, mx, a, tl, cs[t], cs[t + 1], sbuf(t - t0), sbuf(t + 1 - t0), dtab,
                                   lda, kbuf, phi, cd.pos_lo, lane, e);
     }
     for (int t = t1 - 1; t >= t0; --t) {
@@ -449,8 +519,8 @@ __global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
       const int po = st.gpos - cd.pos_lo;
       const bool has_prev = t > 0;
       if (has_prev) {
-        build_diag(g, po, phi, dtab, lda, 0, lane);
-        wsync();
+        build_diag(tm, g, po, phi, dtab, lda, 0, lane);
+        tm.sync();
       }
       if (w == 0) {
         // closing step: R = 1 / raw, Lambda[s][x] = T[x] R[s]
@@ -459,7 +529,7 @@ __global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
         float mloc[kGM];
 #pragma unroll
         for (int j = 0; j < kGM; ++j) mloc[j] = 0.f;
-        for (int x = lg; x < st.kp; x += 4) {
+        for (int x = lg + 4 * tm.sub; x < st.kp; x += 4 * kW) {
           const float lam = x < K ? tval<kTL>(a, tl, st, x, 0) * rinv : 0.f;
           const float cval = A[ls * lda + x] * lam;
 #pragma unroll
@@ -473,45 +543,48 @@ __global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
           mloc[j] += __shfl_xor(mloc[j], 32, 64);
         }
         if (lg == 0) {
+          float *m = kW > 1 ? mred + tm.sub * kGM * CW : Ms;
 #pragma unroll
           for (int j = 0; j < kGM; ++j)
-            if (j < g) Ms[j * CW + ls] = mloc[j];
+            if (j < g) m[j * CW + ls] = mloc[j];
         }
         if (has_prev)
-          for (int i = lane; i < CW * (kbuf - st.kp); i += 64) Rn[(i & 15) * lda + st.kp + (i >> 4)] = 0.f;
+          for (int i = tm.tid; i < CW * (kbuf - st.kp); i += tm.n) Rn[(i & 15) * lda + st.kp + (i >> 4)] = 0.f;
+        if constexpr (kW > 1) tm.sync();   // (the sums take the diagonal's place)
         // per-state sums for the edges inside the last group
-        for (int x = lane; x < K; x += 64) {
+        for (int x = tm.tid; x < K; x += tm.n) {
           float acc = 0.f;
           for (int s = 0; s < CW; ++s)
             acc += gs[s] * A[s * lda + x] * (rawb[s] > 0.f ? 1.f / rawb[s] : 0.f);
           pb[x] = acc * tval<kTL>(a, tl, st, x, 0);
         }
-        wsync();
+        tm.sync();
       } else {
-        const int NT = st.np >> 4, KT = st.kp >> 4;
+        // the wave's tiles of states xt0 + xt
+        const int NT = st.np >> 4, KT = st.kp >> 4, xt0 = tm.sub * TP;
         // Lambda = R . T^T  (samples x K)
-        f4 lam[NTM];
+        f4 lam[TP];
 #pragma unroll
-        for (int xt = 0; xt < NTM; ++xt) lam[xt] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int xt = 0; xt < TP; ++xt) lam[xt] = f4{0.f, 0.f, 0.f, 0.f};
         const float *rp = Rc + ls * lda + lg;
         const int OC = st.np >> 2;     // a multiple of 4
         for (int k0 = 0; k0 < OC; k0 += 4) {
-          float av[4], bv[4][NTM];
+          float av[4], bv[4][TP];
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             av[u] = rp[4 * (k0 + u)];
             const int o = 4 * (k0 + u) + lg;
 #pragma unroll
-            for (int xt = 0; xt < NTM; ++xt)
-              if (xt < KT)
-                bv[u][xt] = kTL ? tl[st.tl_off + (16 * xt + ls) * (st.np + 1) + o]
-                                : a.Tt[st.tt_off + o * st.kp + 16 * xt + ls];
+            for (int xt = 0; xt < TP; ++xt)
+              if (xt0 + xt < KT)
+                bv[u][xt] = kTL ? tl[st.tl_off + (16 * (xt0 + xt) + ls) * (st.np + 1) + o]
+                                : a.Tt[st.tt_off + o * st.kp + 16 * (xt0 + xt) + ls];
           }
 #pragma unroll
           for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int xt = 0; xt < NTM; ++xt)
-              if (xt < KT) lam[xt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[u][xt], lam[xt], 0, 0, 0);
+            for (int xt = 0; xt < TP; ++xt)
+              if (xt0 + xt < KT) lam[xt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[u][xt], lam[xt], 0, 0, 0);
         }
         // magnetisations and R of the previous step
         float scp[4];
@@ -523,11 +596,11 @@ __global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
 #pragma unroll
           for (int j = 0; j < kGM; ++j) Macc[r][j] = 0.f;
 #pragma unroll
-        for (int xt = 0; xt < NTM; ++xt)
-          if (xt < KT)
+        for (int xt = 0; xt < TP; ++xt)
+          if (xt0 + xt < KT)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const int x = 16 * xt + ls, s = 4 * lg + r;
+              const int x = 16 * (xt0 + xt) + ls, s = 4 * lg + r;
               float cval = 0.f, rn = 0.f;
               if (x < K) {
                 cval = A[s * lda + x] * lam[xt][r];
@@ -544,18 +617,20 @@ __global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
           for (int j = 0; j < kGM; ++j)
             if (j < g) Macc[r][j] = row16_sum(Macc[r][j]);
         if (ls == 0) {
+          float *m = kW > 1 ? mred + tm.sub * kGM * CW : Ms;
 #pragma unroll
           for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int j = 0; j < kGM; ++j)
-              if (j < g) Ms[j * CW + 4 * lg + r] = Macc[r][j];
+              if (j < g) m[j * CW + 4 * lg + r] = Macc[r][j];
         }
         if (has_prev)
-          for (int i = lane; i < CW * (kbuf - st.kp); i += 64) Rn[(i & 15) * lda + st.kp + (i >> 4)] = 0.f;
+          for (int i = tm.tid; i < CW * (kbuf - st.kp); i += tm.n) Rn[(i & 15) * lda + st.kp + (i >> 4)] = 0.f;
         // H = (g A)^T R over the 16 samples, then per-state partial sums
         if (st.n_edge > 0) {
+          if constexpr (kW > 1) tm.sync();   // (the sums take the diagonal's place)
           const int N = 1 << w;
-          for (int mt = 0; mt < KT; ++mt) {
+          for (int mt = tm.sub; mt < KT; mt += kW) {
             float P[4][kGM + 1];
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -567,6 +642,7 @@ __global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
               const int s = 4 * kc + lg;
               ga[kc] = gs[s] * A[s * lda + 16 * mt + ls];
             }
+#pragma unroll 4
             for (int nt = 0; nt < NT; ++nt) {
               f4 h = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -604,10 +680,20 @@ __global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
             }
           }
         }
-        wsync();
+        tm.sync();
+      }
+      if constexpr (kW > 1) {
+        // the waves' parts of the magnetisations, in wave order
+        for (int i = tm.tid; i < g * CW; i += tm.n) {
+          float m = 0.f;
+#pragma unroll
+          for (int k = 0; k < kW; ++k) m += mred[k * kGM * CW + i];
+          Ms[i] = m;
+        }
+        tm.sync();
       }
       // edges folded into this step: lanes split the group states
-      for (int k = 0; k < st.n_edge; ++k) {
+      for (int k = tm.sub; k < st.n_edge; k += kW) {
         const EdgeDesc ed = ce[st.ce_off + k];
         const int ju = ed.bu - w;
         const bool vin = ed.bv >= w;
@@ -625,13 +711,13 @@ __global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
       }
       // gradient-weighted magnetisations and W-R correlations of the group:
       // lane (j, s) terms, reduced over the 16 samples of a row
-      for (int j = 0; j < g; j += 4) {
+      for (int j = 4 * tm.sub; j < g; j += 4 * kW) {
         const int jj = j + lg;
         float acc = jj < g ? gs[ls] * Ms[jj * CW + ls] : 0.f;
         acc = row16_sum(acc);
         if (ls == 0 && jj < g) prow[st.gpos + jj] = acc;
       }
-      for (int j = 0; j < g; ++j) {
+      for (int j = tm.sub; j < g; j += kW) {
         const int pl = po + j;
         const int k0 = fp[pl], k1 = fp[pl + 1];
         // four W-neighbours per pass, lane (neighbour, sample)
@@ -643,7 +729,7 @@ __global__ __launch_bounds__(256) void chain_bwd_kernel(ChainArgs a) {
           if (ls == 0 && kk < k1) prow[D.nr + fwr[kk]] = acc;
         }
       }
-      wsync();
+      tm.sync();
       float *tmp = Rc; Rc = Rn; Rn = tmp;
     }
   }
@@ -789,11 +875,11 @@ __global__ __launch_bounds__(256) void layout_kernel(LayoutArgs a) {
   }
 }
 
-template <int NTM>
+template <int NTM, int kW>
 void pick_chain_kernel(bool bwd, bool bf, bool tl, void (**k)(ChainArgs)) {
-  if (bwd) *k = tl ? chain_bwd_kernel<true, NTM> : chain_bwd_kernel<false, NTM>;
-  else if (bf) *k = tl ? chain_fwd_kernel<true, true, NTM> : chain_fwd_kernel<true, false, NTM>;
-  else *k = tl ? chain_fwd_kernel<false, true, NTM> : chain_fwd_kernel<false, false, NTM>;
+  if (bwd) *k = tl ? chain_bwd_kernel<true, NTM, kW> : chain_bwd_kernel<false, NTM, kW>;
+  else if (bf) *k = tl ? chain_fwd_kernel<true, true, NTM, kW> : chain_fwd_kernel<true, false, NTM, kW>;
+  else *k = tl ? chain_fwd_kernel<false, true, NTM, kW> : chain_fwd_kernel<false, false, NTM, kW>;
 }
 
 }  // namespace
@@ -816,14 +902,17 @@ hipError_t launch_chain(const ChainArgs &a, bool bwd, hipStream_t st) {
                      (size_t)a.lim.wpb * chain_wave_lds(a.lim, bwd);
   void (*k)(ChainArgs) = nullptr;
   const bool tl = a.lim.tlds != 0;
-  if (a.ntm <= 2) pick_chain_kernel<2>(bwd, a.bf16, tl, &k);
-  else if (a.ntm <= 4) pick_chain_kernel<4>(bwd, a.bf16, tl, &k);
-  else if (a.ntm <= 16) pick_chain_kernel<16>(bwd, a.bf16, tl, &k);
+  const int spw = a.lim.spw;
+  if (spw > 1 && (spw != kChainSplit || a.lim.wpb != 1 || a.ntm > 16)) return hipErrorInvalidValue;
+  if (spw > 1) pick_chain_kernel<16, kChainSplit>(bwd, a.bf16, tl, &k);
+  else if (a.ntm <= 2) pick_chain_kernel<2, 1>(bwd, a.bf16, tl, &k);
+  else if (a.ntm <= 4) pick_chain_kernel<4, 1>(bwd, a.bf16, tl, &k);
+  else if (a.ntm <= 16) pick_chain_kernel<16, 1>(bwd, a.bf16, tl, &k);
   else return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k, dim3(a.n_tasks), dim3(64 * a.lim.wpb), lds, st, a);
+  hipLaunchKernelGGL(k, dim3(a.n_tasks), dim3(64 * a.lim.wpb * spw), lds, st, a);
   return hipGetLastError();
 }
 

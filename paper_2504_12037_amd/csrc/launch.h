@@ -493,12 +493,14 @@ void set_last_error(const char *msg);
 namespace tnvan {
 
 // Transfer-matrix (chain) kernels: a workgroup takes one chain of one
-// instance and wpb groups of 16 samples (one per wave).
+// instance and wpb groups of 16 samples, each on spw waves.
+constexpr int kChainSplit = 8;
 struct ChainLim {             // launch-wide maxima that size the LDS layout
   int32_t kbuf, npos_max, max_steps, pmax, nw;
   int32_t tl_max, tbl_max, ne_max, nf_max;
   int32_t kseg;               // checkpoint interval of the adjoint
-  int32_t wpb;                // waves per workgroup
+  int32_t wpb;                // groups of 16 samples per workgroup
+  int32_t spw;                // waves per group (1, or kChainSplit with one group)
   int32_t tlds;               // transfer tables staged in LDS
   int32_t rk;                 // register-resident adjoint: checkpoint every rk steps (1, 2, 4, 8)
 };
