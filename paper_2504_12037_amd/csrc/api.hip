@@ -201,7 +201,7 @@ struct tnvan_net {
   DBuf garena, partial, w_logz, w_logq, w_spins, w_f, w_fpart, w_hid, w_da, w_dlogit, w_sf,
       w_part, d_hw_off, d_sum_off;
   int max_partial = 0, max_out = 1;
-  int sample_reps = 1;
+  int sample_per = 1, sample_jj = 1;   // samples per lane, most positions of a lane
   // transfer-matrix form (chain kernels, FP32 / BF16 precisions)
   std::vector<int32_t> use_chain;
   // FP64 nets: instances on the double-precision chain kernels, with their
@@ -1405,19 +1405,25 @@ tnvan_status ensure_sample_blocks(tnvan_net *net) {
   }
   net->h_blk_inst.clear();
   net->h_blk_start.clear();
+  // blocks of the general sampler, the longest chains of positions first;
+  // two samples per lane where that still leaves 16 waves per CU: the two
+  // share the staged rows (the 64 mixed instances' step 2767 -> 2700 us, of
+  // 3850 groups of 32 samples; 128 groups of |W| = 100 took 126 us at one
+  // and 184 us at two)
   const int spb = 256 / net->mi[0].L;
   int64_t groups = 0;
-  for (int q = 0; q < net->n_inst; ++q) groups += (net->nkey[q] + spb - 1) / spb;
-  // a few rounds per block so that each block stages its parameters once;
-  // parameters too large to stage are read from global memory, and then
-  // more, shorter blocks keep more waves in flight (the sampler is bound by
-  // the latency of its position-by-position chain)
-  size_t stage = 0;
-  for (auto &m : net->mi) stage = std::max(stage, made_param_bytes(m.n, m.H));
-  const int64_t target = stage <= made_stage_max() ? 512 : 8192;
-  net->sample_reps = (int)std::max<int64_t>(1, (groups + target - 1) / target);
-  const int64_t per_block = (int64_t)spb * net->sample_reps;
+  net->sample_jj = 1;
+  std::vector<int> by_n(net->n_inst);
   for (int q = 0; q < net->n_inst; ++q) {
+    by_n[q] = q;
+    groups += (net->nkey[q] + spb - 1) / spb;
+    net->sample_jj = std::max(net->sample_jj, ((int)net->mi[q].n + net->mi[q].L - 1) / net->mi[q].L);
+  }
+  std::stable_sort(by_n.begin(), by_n.end(),
+                   [&](int x, int y) { return net->mi[x].n > net->mi[y].n; });
+  net->sample_per = net->rs() == 4 && net->sample_jj <= 16 && groups >= 1024 ? 2 : 1;
+  const int64_t per_block = (int64_t)spb * net->sample_per;
+  for (int q : by_n) {
     for (int64_t b = 0; b < net->nkey[q]; b += per_block) {
       net->h_blk_inst.push_back(q);
       net->h_blk_start.push_back((int32_t)b);
@@ -1510,11 +1516,7 @@ tnvan_status run_sample(tnvan_net *net, const float *uniforms, int8_t *spins, vo
   a.logq = static_cast<real *>(logq);
   a.seed = net->seed;
   a.step_ctr = net->step_ctr.as<int32_t>();
-  a.spb = 256 / net->mi[0].L;      // every instance uses the same lane count
-  a.reps = net->sample_reps;
-  size_t stage = 0;
-  for (auto &m : net->mi) stage = std::max(stage, made_param_bytes(m.n, m.H));
-  HIPCHK(launch_sample<real>(a, net->n_sblocks, stage, st));
+  HIPCHK(launch_sample<real>(a, net->n_sblocks, net->sample_per, net->sample_jj, st));
   return TNVAN_OK;
 }
 

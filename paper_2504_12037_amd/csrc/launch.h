@@ -174,16 +174,15 @@ struct SampleArgs {
   real *logq;
   uint64_t seed;
   const int32_t *step_ctr;      // per instance (device), Philox counter word 2
-  int32_t spb;                  // samples per round of a block (256 / L)
-  int32_t reps;                 // rounds per block
   const float *w0t;             // one-layer sampler: columns of W0 (w0t_kernel)
   const int64_t *w0t_off;       // per instance, floats
   real *sig;                    // one-layer sampler: q(s_i = +1 | s_<i) in the
                                 // spins' layout, or null
 };
-// stage_bytes: LDS for the parameters (0 or too large: read them from HBM)
+// Blocks of per_lane * 256 / L samples (per_lane 2: FP32 and max_jj <= 16);
+// max_jj: most positions of a lane, ceil(|W| / L).
 template <typename real>
-hipError_t launch_sample(const SampleArgs<real> &a, int n_blocks, size_t stage_bytes,
+hipError_t launch_sample(const SampleArgs<real> &a, int n_blocks, int per_lane, int max_jj,
                          hipStream_t st);
 // One-layer nets (every instance H = 0, |W| <= kH0MaxN): one wave per
 // sample, W0's columns from w0t (written by launch_w0t from the parameters;
@@ -195,8 +194,6 @@ template <typename real>
 hipError_t launch_sample_h0(const SampleArgs<real> &a, int n_inst, int64_t max_B, int max_n,
                             hipStream_t st);
 size_t made_param_bytes(int n, int H);
-// the largest parameter set the general sampler stages in LDS
-size_t made_stage_max();
 
 // Deeper networks (some instance with D > 1 hidden layers): one wave per
 // sample for every instance, a lane owning hidden units lane + 64 kk and
