@@ -1485,11 +1485,15 @@ tnvan_status run_sample(tnvan_net *net, const float *uniforms, int8_t *spins, vo
     int64_t maxB = 0;
     for (int q = 0; q < net->n_inst; ++q) maxB = std::max(maxB, net->nkey[q]);
     ProfScope ps(net, TNVAN_KERNEL_SAMPLE, st);
-    // small networks: 16 lanes per sample
+    // small networks: four lanes per sample
     bool small = true;
-    for (auto &m : net->mi)
-      if (m.n > kDeep16MaxN || m.H > kDeep16MaxH) small = false;
-    HIPCHK(launch_sample_deep<real>(a, net->n_inst, maxB, small, st));
+    int max_n = 1, max_D = 1;
+    for (auto &m : net->mi) {
+      if (m.n > kDeep4MaxN || m.H > kDeep4MaxH) small = false;
+      max_n = std::max(max_n, (int)m.n);
+      max_D = std::max(max_D, (int)m.D);
+    }
+    HIPCHK(launch_sample_deep<real>(a, net->n_inst, maxB, small, max_n, max_D, st));
     return TNVAN_OK;
   }
   if (net->h0) {

@@ -134,6 +134,63 @@ __device__ inline MadeView made_stage(const MadeView g, int n, int H, float *s) 
   return v;
 }
 
+// Rows of a sampler's parameters in LDS, [position][lane][SL]: of lane l the
+// words of W2 and W1^T for units l + L kk and of W0 for positions l + L jj;
+// zeros for what the masks of Eq. 7 leave out of W2 and W0 (units of a higher
+// degree, later positions) and past the matrices.
+constexpr int kSampleRows = 64;   // positions staged at once, times L
+template <int kT, int NJ>
+struct SampleRows {
+  static constexpr int SL = 2 * KH + NJ + 4;   // words per lane and position
+  static_assert(SL % 8 == 4, "lanes' rows an odd number of 16 bytes apart");
+  static constexpr int kW2 = kSampleRows * KH / kT, kW0 = kSampleRows * NJ / kT;
+  const MadeView &w;
+  const int n, H, logL, tid = threadIdx.x;
+  const float inv;
+  float w2[kW2], w1[kW2], w0[kW0];
+  __device__ SampleRows(const MadeView &view, int n_, int H_, int l)
+      : w(view), n(n_), H(H_), logL(l), inv(1.f / (float)(n_ - 1)) {}
+  // degree(k, n), the quotient from a product: k + 1/2 is at least 1/2 from a
+  // multiple of n - 1, and k at most 1024
+  __device__ int deg(int k) const { return 1 + k - (int)(((float)k + 0.5f) * inv) * (n - 1); }
+  // positions i0 .. i0 + kSampleRows / L - 1: this thread's words
+  __device__ void fetch(int i0) {
+    const int C = kSampleRows >> logL;
+#pragma unroll
+    for (int m = 0; m < kW2; ++m) {
+      const int e = tid + kT * m;
+      int i = i0 + (e >> (logL + 4)), k = e & ((KH << logL) - 1);
+      w2[m] = (k < H && i < n && deg(k) <= i) ? w.W2[(int64_t)i * H + k] : 0.f;
+      i = i0 + (e & (C - 1));
+      k = e >> (6 - logL);
+      w1[m] = (k < H && i < n) ? w.W1[(int64_t)k * n + i] : 0.f;
+    }
+#pragma unroll
+    for (int m = 0; m < kW0; ++m) {
+      const int e = tid + kT * m;
+      const int i = i0 + e / (NJ << logL), j = e & ((NJ << logL) - 1);
+      w0[m] = (i < n && j < i) ? w.W0[(int64_t)i * n + j] : 0.f;
+    }
+  }
+  __device__ void put(float *dst) {
+    const int C = kSampleRows >> logL, L = 1 << logL;
+    auto at = [&](int r, int k, int c0) -> float & {
+      return dst[((r << logL) + (k & (L - 1))) * SL + c0 + (k >> logL)];
+    };
+#pragma unroll
+    for (int m = 0; m < kW2; ++m) {
+      const int e = tid + kT * m;
+      at(e >> (logL + 4), e & ((KH << logL) - 1), 0) = w2[m];
+      at(e & (C - 1), e >> (6 - logL), KH) = w1[m];
+    }
+#pragma unroll
+    for (int m = 0; m < kW0; ++m) {
+      const int e = tid + kT * m;
+      at(e / (NJ << logL), e & ((NJ << logL) - 1), 2 * KH) = w0[m];
+    }
+  }
+};
+
 // One group of L lanes per kP samples; lane l owns hidden units k = l + L*kk
 // and positions j = l + L*jj of each.  Spins are drawn one position after the
 // other; a block takes kP * 256 / L samples of one instance.
@@ -156,15 +213,12 @@ __device__ inline MadeView made_stage(const MadeView g, int n, int H, float *s) 
 // samples, FP32), against a test and a load from global memory per term:
 // 1554 -> 356 us; 4096 samples of |W| = 100, H = 128: 433 -> 126 us in FP32,
 // 511 -> 188 us in FP64.
-constexpr int kSampleRows = 64;   // positions staged at once, times L
 template <typename real, int kP, int NJ>
 __global__ __launch_bounds__(256) void sample_kernel(SampleArgs<real> a) {
   typedef float w4 __attribute__((ext_vector_type(4)));
   typedef real vk __attribute__((ext_vector_type(KH)));
   typedef float vn __attribute__((ext_vector_type(NJ)));   // spins (0 before they are drawn)
-  constexpr int SL = 2 * KH + NJ + 4;   // words per lane and position
-  static_assert(SL % 32 == 20 || SL % 32 == 4, "lanes' rows 4 banks apart");
-  constexpr int kW2 = kSampleRows * KH / 256, kW0 = kSampleRows * NJ / 256;
+  constexpr int SL = SampleRows<256, NJ>::SL;
   __shared__ __align__(16) float rows[2][kSampleRows * SL];
   const int q = uload(a.blk_inst + blockIdx.x);
   const MadeInst mi = uload(a.mi + q);
@@ -176,42 +230,7 @@ __global__ __launch_bounds__(256) void sample_kernel(SampleArgs<real> a) {
   const int C = kSampleRows >> logL, logC = 6 - logL, chunks = (n + C - 1) >> logC;
   const int nk4 = (H + 4 * L - 1) >> (logL + 2);   // groups of four units per lane
 
-  // rows i0 .. i0 + C - 1: this thread's words, and their places
-  float w2[kW2], w1[kW2], w0[kW0];
-  auto fetch = [&](int i0) {
-#pragma unroll
-    for (int m = 0; m < kW2; ++m) {
-      const int e = tid + 256 * m;
-      int i = i0 + (e >> (logL + 4)), k = e & (16 * L - 1);
-      w2[m] = (k < H && i < n && degree(k, n) <= i) ? w.W2[(int64_t)i * H + k] : 0.f;
-      i = i0 + (e & (C - 1));
-      k = e >> logC;
-      w1[m] = (k < H && i < n) ? w.W1[(int64_t)k * n + i] : 0.f;
-    }
-#pragma unroll
-    for (int m = 0; m < kW0; ++m) {
-      const int e = tid + 256 * m;
-      const int i = i0 + e / (NJ * L), j = e & (NJ * L - 1);
-      w0[m] = (i < n && j < i) ? w.W0[(int64_t)i * n + j] : 0.f;
-    }
-  };
-  auto put = [&](float *dst) {
-    auto at = [&](int r, int k, int c0) -> float & {
-      return dst[((r << logL) + (k & (L - 1))) * SL + c0 + (k >> logL)];
-    };
-#pragma unroll
-    for (int m = 0; m < kW2; ++m) {
-      const int e = tid + 256 * m;
-      at(e >> (logL + 4), e & (16 * L - 1), 0) = w2[m];
-      at(e & (C - 1), e >> logC, KH) = w1[m];
-    }
-#pragma unroll
-    for (int m = 0; m < kW0; ++m) {
-      const int e = tid + 256 * m;
-      at(e / (NJ * L), e & (NJ * L - 1), 2 * KH) = w0[m];
-    }
-  };
-
+  SampleRows<256, NJ> stage(w, n, H, logL);
   int64_t b[kP];
   bool live[kP];
   const float *u[kP];
@@ -237,12 +256,12 @@ __global__ __launch_bounds__(256) void sample_kernel(SampleArgs<real> a) {
   }
   const int lm = n >= 2 ? l % (n - 1) : l;
   if (chunks > 0) {
-    fetch(0);
-    put(rows[0]);
+    stage.fetch(0);
+    stage.put(rows[0]);
   }
   __syncthreads();
   for (int c = 0; c < chunks; ++c) {
-    if (c + 1 < chunks) fetch((c + 1) << logC);
+    if (c + 1 < chunks) stage.fetch((c + 1) << logC);
     const int i1 = min(n, (c + 1) << logC);
     for (int i = c << logC; i < i1; ++i) {
       const float *row = rows[c & 1] + (((i & (C - 1)) << logL) + l) * SL;
@@ -329,7 +348,7 @@ __global__ __launch_bounds__(256) void sample_kernel(SampleArgs<real> a) {
           while (k < (kk + 1) * L) k += n - 1;
         }
     }
-    if (c + 1 < chunks) put(rows[(c + 1) & 1]);
+    if (c + 1 < chunks) stage.put(rows[(c + 1) & 1]);
     __syncthreads();
   }
 #pragma unroll
@@ -456,107 +475,180 @@ __global__ __launch_bounds__(256) void sample_deep_kernel(SampleArgs<real> a) {
 }
 
 // The same sampler for small deeper networks (every instance |W| <= 128 and
-// H <= 64): 16 lanes per sample, four samples per wave and sixteen per
-// block, so that four times as many independent position chains are in
-// flight.  Lane c of a sample owns units c + 16 kk and positions c + 16 jj;
-// the logit is the 16-lane row sum.  Each sample's completed tanh values go
-// to its own slice of LDS, read by its own lanes after a wave barrier.
-constexpr int kD16KK = kDeep16MaxH / 16, kD16JJ = kDeep16MaxN / 16;
-template <typename real>
-__global__ __launch_bounds__(256) void sample_deep16_kernel(SampleArgs<real> a) {
-  __shared__ real hs[16][kDeepMaxD][kDeep16MaxH];
-  const int q = blockIdx.y, lane = threadIdx.x & 63, c = lane & 15;
-  const int slot = threadIdx.x >> 4;   // the block's sample 0..15
+// H <= 64): four lanes per sample.  Lane c owns units c + 4 m and positions
+// c + 4 m of every layer, all in registers; its logit terms are added in
+// four classes m mod 4 and those over the lanes and classes as a row of 16
+// lanes with units c + 16 kk would, which fixes the drawn spins.
+//
+// What bounds it is instruction issue, most of it tanh of the units that a
+// position completes (one of a run of |W| - 1 units): the units of several
+// runs sit on different lanes and share one evaluation.  The rows of W2, W1
+// and W0 are staged as in the sampler above, the deeper layers' matrices
+// whole, column by column with zeros for the units of a lower degree.
+// Measured on three instances of 8192 samples, |W| = 32, H = 64, two layers,
+// FP32, against 16 lanes per sample that read the parameters from global
+// memory: 235 -> 92 us.
+constexpr int kD4Threads = 128, kD4Samples = kD4Threads / 4;
+constexpr int kD4Col = 4 * (KH + 4);   // words of a staged column
+template <typename real, int kD, int NJ>
+__global__ __launch_bounds__(kD4Threads) void sample_deep4_kernel(SampleArgs<real> a) {
+  typedef float w4 __attribute__((ext_vector_type(4)));
+  typedef real vk __attribute__((ext_vector_type(KH)));
+  typedef float vn __attribute__((ext_vector_type(NJ)));
+  constexpr int SL = SampleRows<kD4Threads, NJ>::SL;
+  static_assert(kDeep4MaxH <= 4 * KH && kDeep4MaxN <= 4 * 32, "units and positions of a lane");
+  __shared__ __align__(16) float rows[2][kSampleRows * SL];
+  __shared__ __align__(16) float cols[kD - 1][kDeep4MaxH * kD4Col];
+  const int q = blockIdx.y, tid = threadIdx.x, c = tid & 3;
   const MadeInst mi = uload(a.mi + q);
-  if ((int64_t)blockIdx.x * 16 >= mi.B) return;   // uniform over the block
-  const int64_t b = (int64_t)blockIdx.x * 16 + slot;
+  if ((int64_t)blockIdx.x * kD4Samples >= mi.B) return;   // uniform over the block
+  const int64_t b = (int64_t)blockIdx.x * kD4Samples + (tid >> 2);
   const bool live = b < mi.B;
   const int64_t bs = live ? b : 0;
   const int n = mi.n, H = n >= 2 ? mi.H : 0, D = H > 0 ? mi.D : 1;
   const float *P = a.params + mi.param_off;
   const MadeView w = made_view(P, n, mi.H);
   const uint32_t step = a.step_ctr ? (uint32_t)a.step_ctr[q] : 0u;
-  real acc[kDeepMaxD][kD16KK], sv[kD16JJ];
-  int dg[kD16KK];
+  SampleRows<kD4Threads, NJ> stage(w, n, H, 2);
+  vk acc[kD], hv;
+  vn sv;
 #pragma unroll
-  for (int kk = 0; kk < kD16KK; ++kk) {
-    const int k = c + 16 * kk;
-    dg[kk] = k < H ? degree(k, n) : 0;
+  for (int m = 0; m < KH; ++m) {
+    const int k = c + 4 * m;
+    hv[m] = 0;
 #pragma unroll
-    for (int l = 0; l < kDeepMaxD; ++l) {
+    for (int l = 0; l < kD; ++l) {
       const float *bl = l == 0 ? w.b1 : deep_layer(P, n, mi.H, l + 1) + (int64_t)mi.H * mi.H;
-      acc[l][kk] = (k < H && l < D) ? (real)bl[k] : (real)0;
+      acc[l][m] = (k < H && l < D) ? (real)bl[k] : (real)0;
     }
   }
 #pragma unroll
-  for (int jj = 0; jj < kD16JJ; ++jj) sv[jj] = 0;
+  for (int m = 0; m < NJ; ++m) sv[m] = 0;
+  for (int l = 1; l < D; ++l) {
+    const float *Wl = deep_layer(P, n, H, l + 1);
+    for (int e = tid; e < H * 4 * KH; e += kD4Threads) {
+      const int k2 = e & (4 * KH - 1), k = e / (4 * KH);
+      cols[l - 1][k * kD4Col + (k2 & 3) * (KH + 4) + (k2 >> 2)] =
+          k2 < H && stage.deg(k2) >= stage.deg(k) ? Wl[(int64_t)k2 * H + k] : 0.f;
+    }
+  }
   const float *u = a.uniforms ? a.uniforms + mi.spin_off + bs * n : nullptr;
-  int8_t *so = a.spins + mi.spin_off + bs * n;
   uint32_t pw[4] = {0, 0, 0, 0};
-  real lq = 0;
-  for (int i = 0; i < n; ++i) {
-    // logit_i from the last layer's completed units and the earlier spins
-    real part = 0;
+  real lq = 0, mine = 0;
+  // units of one degree, n - 1 apart, on different lanes: that many at once
+  const int G = (n - 1) & 1 ? 4 : (n - 1) & 2 ? 2 : 1;
+  const int chunks = (n + 15) >> 4, hg = (H + 15) >> 4;
+  if (chunks > 0) {
+    stage.fetch(0);
+    stage.put(rows[0]);
+  }
+  __syncthreads();
+  for (int ch = 0; ch < chunks; ++ch) {
+    if (ch + 1 < chunks) stage.fetch((ch + 1) * 16);
+    const int i1 = min(n, ch * 16 + 16);
+    for (int i = ch * 16; i < i1; ++i) {
+      const float *row = rows[ch & 1] + ((i & 15) * 4 + c) * SL;
+      // logit_i from the last layer's completed units and the earlier spins
+      real part[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int kk = 0; kk < kD16KK; ++kk) {
-      const int k = c + 16 * kk;
-      if (k < H && dg[kk] <= i) part += (real)w.W2[(int64_t)i * mi.H + k] * hs[slot][D - 1][k];
-    }
+      for (int g = 0; g < KH / 4; ++g)
+        if (g < hg) {
+          const w4 x = *reinterpret_cast<const w4 *>(row + 4 * g);
 #pragma unroll
-    for (int jj = 0; jj < kD16JJ; ++jj) {
-      const int j = c + 16 * jj;
-      if (j < i) part += (real)w.W0[(int64_t)i * n + j] * sv[jj];
-    }
-    // the sample's sum over its 16 lanes
-    if constexpr (sizeof(real) == 4) {
-      part = row16_sum(part);
-    } else {
-#pragma unroll
-      for (int off = 8; off > 0; off >>= 1) part += __shfl_xor(part, off, 16);
-    }
-    const real logit = part + (real)w.b2[i];
-    float ui;
-    if (u) {
-      ui = live ? u[i] : 0.5f;
-    } else {
-      if ((i & 3) == 0) {
-        pw[0] = (uint32_t)(i >> 2); pw[1] = (uint32_t)bs; pw[2] = step; pw[3] = (uint32_t)q;
-        philox4x32_10(pw, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
-      }
-      ui = (float)(pw[i & 3] >> 8) * 5.9604644775390625e-08f;
-    }
-    const real p = sigmoid<real>(logit);
-    const real si = ((real)ui < p) ? (real)1 : (real)-1;
-    lq += log_sigmoid<real>(si * logit);
-#pragma unroll
-    for (int jj = 0; jj < kD16JJ; ++jj)
-      if (c + 16 * jj == i) sv[jj] = si;
-    if (c == 0 && live) so[i] = (int8_t)(si > 0 ? 1 : -1);
-    // layer 1: the new spin, and the units it completes
-#pragma unroll
-    for (int kk = 0; kk < kD16KK; ++kk) {
-      const int k = c + 16 * kk;
-      if (k < H && dg[kk] >= i + 1) {
-        acc[0][kk] += (real)w.W1[(int64_t)k * n + i] * si;
-        if (dg[kk] == i + 1) hs[slot][0][k] = rtanh<real>(acc[0][kk]);
-      }
-    }
-    // deeper layers: the units of degree i + 1 just completed below
-    for (int l = 1; l < D; ++l) {
-      wsync();
-      const float *Wl = deep_layer(P, n, mi.H, l + 1);
-#pragma unroll
-      for (int kk = 0; kk < kD16KK; ++kk) {
-        const int k2 = c + 16 * kk;
-        if (k2 < H && dg[kk] >= i + 1) {
-          if (i + 1 <= n - 1)
-            for (int k = i; k < H; k += n - 1)
-              acc[l][kk] += (real)Wl[(int64_t)k2 * mi.H + k] * hs[slot][l - 1][k];
-          if (dg[kk] == i + 1) hs[slot][l][k2] = rtanh<real>(acc[l][kk]);
+          for (int t = 0; t < 4; ++t) part[t] += (real)x[t] * hv[4 * g + t];
         }
+#pragma unroll
+      for (int g = 0; g < NJ / 4; ++g)
+        if (16 * g < i) {
+          const w4 x = *reinterpret_cast<const w4 *>(row + 2 * KH + 4 * g);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) part[t] += (real)x[t] * (real)sv[4 * g + t];
+        }
+      real logit;
+      if constexpr (sizeof(real) == 4) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          part[t] += lane_xor<1>(part[t]);
+          part[t] += lane_xor<2>(part[t]);
+        }
+        logit = (part[0] + part[1]) + (part[2] + part[3]);
+      } else {
+        logit = (part[0] + part[2]) + (part[1] + part[3]);
+        logit += lane_xor<2>(logit);
+        logit += lane_xor<1>(logit);
       }
+      logit += (real)w.b2[i];
+      float ui;
+      if (u) {
+        ui = live ? u[i] : 0.5f;
+      } else {
+        if ((i & 3) == 0) {
+          pw[0] = (uint32_t)(i >> 2); pw[1] = (uint32_t)bs; pw[2] = step; pw[3] = (uint32_t)q;
+          philox4x32_10(pw, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
+        }
+        const uint32_t r = (i & 2) ? ((i & 1) ? pw[3] : pw[2]) : ((i & 1) ? pw[1] : pw[0]);
+        ui = (float)(r >> 8) * 5.9604644775390625e-08f;
+      }
+      const real si = ((real)ui < sigmoid<real>(logit)) ? (real)1 : (real)-1;
+      const int il = i & 3;
+      if (c == il) {
+        mine = si * logit;
+        sv[i >> 2] = (float)si;
+      }
+      if (il == 3 || i == n - 1) {
+        // the last four positions' terms, and their spins
+        const real ls = log_sigmoid<real>(mine);
+        for (int r = 0; r <= il; ++r) lq += __shfl(ls, r, 4);
+        if (live && c <= il)
+          a.spins[mi.spin_off + b * n + (i - il + c)] = (int8_t)(sv[i >> 2] > 0 ? 1 : -1);
+      }
+      // layer 1: the new spin; then layer by layer the units of degree i + 1
+      // (k = i modulo n - 1), complete once the layer below has its own
+#pragma unroll
+      for (int g = 0; g < KH / 4; ++g)
+        if (g < hg) {
+          const w4 x = *reinterpret_cast<const w4 *>(row + KH + 4 * g);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) acc[0][4 * g + t] += (real)x[t] * si;
+        }
+      if (i >= n - 1) continue;
+#pragma unroll
+      for (int l = 0; l < kD; ++l)
+        if (l < D)
+          for (int k = i; k < H;) {
+            real x = acc[l][k >> 2];
+            int k1 = k;
+            for (int g = 1; g < G && k1 + n - 1 < H; ++g) {
+              k1 += n - 1;
+              x = c == (k1 & 3) ? acc[l][k1 >> 2] : x;
+            }
+            const real h = rtanh<real>(x);
+            for (; k <= k1; k += n - 1) {
+              const bool own = c == (k & 3);
+              if (l == D - 1) {
+                hv[k >> 2] = own ? h : hv[k >> 2];
+              } else if constexpr (kD > 1) {
+                if (l + 1 < kD) {
+                  // the unit's value on the sample's lanes, into the layer above
+                  real v = own ? h : (real)0;
+                  v += lane_xor<1>(v);
+                  v += lane_xor<2>(v);
+                  const float *col = cols[l < kD - 1 ? l : 0] + k * kD4Col + c * (KH + 4);
+#pragma unroll
+                  for (int g = 0; g < KH / 4; ++g)
+                    if (g < hg) {
+                      const w4 y = *reinterpret_cast<const w4 *>(col + 4 * g);
+#pragma unroll
+                      for (int t = 0; t < 4; ++t)
+                        acc[l + 1 < kD ? l + 1 : l][4 * g + t] += (real)y[t] * v;
+                    }
+                }
+              }
+            }
+          }
     }
-    wsync();
+    if (ch + 1 < chunks) stage.put(rows[(ch + 1) & 1]);
+    __syncthreads();
   }
   if (live && c == 0) a.logq[mi.sample_off + b] = lq;
 }
@@ -2838,13 +2930,22 @@ hipError_t launch_rows_deep(const RowArgs<real> &a, int rb, hipStream_t st) {
 
 template <typename real>
 hipError_t launch_sample_deep(const SampleArgs<real> &a, int n_inst, int64_t max_B, bool small,
-                              hipStream_t st) {
+                              int max_n, int max_D, hipStream_t st) {
   if (n_inst <= 0 || max_B <= 0) return hipSuccess;
   if (small) {
-    const int64_t bx = (max_B + 15) / 16;
+    const int64_t bx = (max_B + kD4Samples - 1) / kD4Samples;
     if (bx > 0x7fffffff || n_inst > 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(sample_deep16_kernel<real>, dim3((unsigned)bx, n_inst), dim3(256), 0, st,
-                       a);
+    void (*k)(SampleArgs<real>) = nullptr;
+    auto by_D = [&](auto nj) {
+      constexpr int NJ = decltype(nj)::value;
+      k = max_D <= 2   ? sample_deep4_kernel<real, 2, NJ>
+          : max_D <= 3 ? sample_deep4_kernel<real, 3, NJ>
+                       : sample_deep4_kernel<real, kDeepMaxD, NJ>;
+    };
+    if (max_n <= 32) by_D(std::integral_constant<int, 8>{});
+    else if (max_n <= 64) by_D(std::integral_constant<int, 16>{});
+    else by_D(std::integral_constant<int, 32>{});
+    hipLaunchKernelGGL(k, dim3((unsigned)bx, n_inst), dim3(kD4Threads), 0, st, a);
     return hipGetLastError();
   }
   const int64_t bx = (max_B + 3) / 4;
@@ -2929,10 +3030,10 @@ hipError_t launch_obs_w(const ObsArgs &a, int n_inst, hipStream_t st) {
 
 template hipError_t launch_sample<float>(const SampleArgs<float> &, int, int, int, hipStream_t);
 template hipError_t launch_sample<double>(const SampleArgs<double> &, int, int, int, hipStream_t);
-template hipError_t launch_sample_deep<float>(const SampleArgs<float> &, int, int64_t, bool,
-                                              hipStream_t);
-template hipError_t launch_sample_deep<double>(const SampleArgs<double> &, int, int64_t, bool,
-                                               hipStream_t);
+template hipError_t launch_sample_deep<float>(const SampleArgs<float> &, int, int64_t, bool, int,
+                                              int, hipStream_t);
+template hipError_t launch_sample_deep<double>(const SampleArgs<double> &, int, int64_t, bool, int,
+                                               int, hipStream_t);
 template hipError_t launch_rows_deep<float>(const RowArgs<float> &, int, hipStream_t);
 template hipError_t launch_rows_deep<double>(const RowArgs<double> &, int, hipStream_t);
 template hipError_t launch_sample_h0<float>(const SampleArgs<float> &, int, int64_t, int, hipStream_t);
