@@ -192,12 +192,11 @@ struct tnvan_net {
   DBuf bs_atb, bs_col, bs_alo, bs_aflo, bs_clo, bs_cflo;
   std::vector<int64_t> bkey;
   int32_t bs_counts[6] = {0, 0, 0, 0, 0, 0};
-  // jobs of the batched REINFORCE rows of one-layer nets, one launch per
-  // class of LDS need (ensure_batch_sums): jobs, first blocks, counts, LDS
-  // bytes
-  DBuf rw_jobs[4], rw_lo[4];
-  int32_t rw_njobs[4] = {0, 0, 0, 0}, rw_blocks[4] = {0, 0, 0, 0};
-  size_t rw_lds[4] = {0, 0, 0, 0};
+  // jobs of the batched REINFORCE rows (ensure_batch_sums): jobs, first
+  // blocks, counts, LDS bytes
+  DBuf rw_jobs, rw_lo;
+  int32_t rw_njobs = 0, rw_blocks = 0;
+  size_t rw_lds = 0;
   DBuf garena, partial, w_logz, w_logq, w_spins, w_f, w_fpart, w_hid, w_da, w_dlogit, w_sf,
       w_part, d_hw_off, d_sum_off;
   int max_partial = 0, max_out = 1;
@@ -1595,50 +1594,47 @@ tnvan_status ensure_batch_sums(tnvan_net *net, const std::vector<int64_t> &hoff,
       atb(dl, n, sf, n, m.B, n, n, ks, gW0, n, 2, n);
       col(dl, n, m.B, n, ks, gb2);
     }
-    // one-layer nets: the per-sample rows, jobs in classes of LDS need
-    // (staged parameters <= 40 KB, <= 80 KB, <= the device's block limit,
-    // parameters read from global memory), one launch per class
-    std::vector<RowJob> rj[4];
-    std::vector<int32_t> rlo[4] = {{0}, {0}, {0}, {0}};
-    size_t rlds[4] = {0, 0, 0, 0};
-    if (!net->deep && !net->h0) {
+    // the per-sample rows (one-layer nets with no hidden units have their
+    // own): 32 samples per block while that leaves two blocks per CU and
+    // fits 32 KB of LDS (five blocks per CU), else 16, or what fits; small
+    // FP64 batches 4, one of a lane's four outputs of a tile (the 4x4
+    // lattice's 1024 samples 10.5 -> 7.7 us)
+    std::vector<RowJob> rj;
+    std::vector<int32_t> rlo{0};
+    size_t rlds = 0;
+    if (!net->h0) {
       int dev = 0, maxlds = 65536;
       hipGetDevice(&dev);
       (void)hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-      const size_t lim[3] = {40 * 1024, 80 * 1024, (size_t)maxlds};
+      int64_t by32 = 0;
+      for (auto &m : net->mi) by32 += (m.B + 31) / 32;
       for (int q = 0; q < net->n_inst; ++q) {
         const MadeInst &m = net->mi[q];
         if (m.B <= 0) continue;
-        const size_t need = rows_lds_bytes(m.n, m.H, sizeof(real), true);
-        int c = 0;
-        while (c < 3 && need > lim[c]) ++c;
-        const size_t lds = rows_lds_bytes(m.n, m.H, sizeof(real), c < 3);
-        if (lds > (size_t)maxlds)
+        const int D = (net->deep && m.n >= 2 && m.H > 0) ? m.D : 1;
+        // widest one-layer network: 16 samples' spins, logits and units
+        const size_t need = sizeof(real) * 16 * (2 * ((size_t)m.n + 1) + m.H + 1);
+        if (!net->deep && need > (size_t)maxlds)
           return set_err(TNVAN_E_INVALID, "instance %d: the REINFORCE rows of |W| = %d, H = %d "
                          "need %zu bytes of LDS per block, above the device's %d", q, m.n, m.H,
-                         lds, maxlds);
-        // samples per block: one round of 16 for small parameter sets, up
-        // to four rounds per staging of the larger ones, and at most 256
-        // blocks per instance
-        const int64_t wb = (int64_t)(need - rows_lds_bytes(m.n, m.H, sizeof(real), false));
-        int64_t chunk = 16 * std::min<int64_t>(4, std::max<int64_t>(1, (wb + 32767) / 32768));
-        chunk = std::max<int64_t>(chunk, ((m.B + 255) / 256 + 15) / 16 * 16);
+                         need, maxlds);
+        int chunk = by32 >= 512 && rows_lds_bytes(m.n, m.H, D, 32, sizeof(real)) <= 32768 ? 32 : 16;
+        if (sizeof(real) == 8 && by32 < 128) chunk = 4;
+        while (chunk > 1 && rows_lds_bytes(m.n, m.H, D, chunk, sizeof(real)) > (size_t)maxlds) chunk >>= 1;
         const int64_t blocks = (m.B + chunk - 1) / chunk;
-        if (rlo[c].back() + blocks > 0x7fffffff)
+        if (rlo.back() + blocks > 0x7fffffff)
           return set_err(TNVAN_E_INVALID, "instance %d: %lld rows blocks", q, (long long)blocks);
-        rj[c].push_back(RowJob{q, (int32_t)chunk, hoff[q], doff[q]});
-        rlo[c].push_back(rlo[c].back() + (int32_t)blocks);
-        rlds[c] = std::max(rlds[c], lds);
+        rj.push_back(RowJob{q, chunk, hoff[q], doff[q]});
+        rlo.push_back(rlo.back() + (int32_t)blocks);
+        rlds = std::max(rlds, rows_lds_bytes(m.n, m.H, D, chunk, sizeof(real)));
       }
     }
     if (tnvan_status s = quiesce(net)) return s;
-    for (int c = 0; c < 4; ++c) {
-      HIPCHK(upload(net->rw_jobs[c], rj[c]));
-      HIPCHK(upload(net->rw_lo[c], rlo[c]));
-      net->rw_njobs[c] = (int32_t)rj[c].size();
-      net->rw_blocks[c] = rlo[c].back();
-      net->rw_lds[c] = rlds[c];
-    }
+    HIPCHK(upload(net->rw_jobs, rj));
+    HIPCHK(upload(net->rw_lo, rlo));
+    net->rw_njobs = (int32_t)rj.size();
+    net->rw_blocks = rlo.back();
+    net->rw_lds = rlds;
     HIPCHK(upload(net->bs_atb, aj));
     HIPCHK(upload(net->bs_col, cj));
     HIPCHK(upload(net->bs_alo, alo));
@@ -1802,10 +1798,7 @@ tnvan_status run_step(tnvan_net *net, float lr, double *stats, int8_t *spins_out
     if (tnvan_status s2 = ensure_batch_sums<real>(net, hoff, doff, &bs)) return s2;
     for (int q = 0; q < net->n_inst; ++q) {
       const MadeInst &m = net->mi[q];
-      if (m.B <= 0 || !(net->deep || net->h0)) continue;
-      const int n = m.n, H = m.H;
-      // hidden layers run (deeper networks hold every layer in a row)
-      const int D = (net->deep && n >= 2 && H > 0) ? m.D : 1;
+      if (m.B <= 0 || !net->h0) continue;
       RowArgs<real> r{};
       r.mi = m;
       r.params = net->params.as<float>();
@@ -1817,22 +1810,11 @@ tnvan_status run_step(tnvan_net *net, float lr, double *stats, int8_t *spins_out
       r.da = net->w_da.as<real>() + hoff[q];
       r.dlogit = net->w_dlogit.as<real>() + doff[q];
       r.sf = net->w_sf.as<real>() + doff[q];
-      if (net->deep) {
-        // rows of at most 4096 / H samples and about 48 KB of LDS per round
-        const size_t per = sizeof(real) * (2 * (size_t)n + (size_t)D * H + H);
-        // (8 rows per block and one round each: every sample's rows are
-        // independent, and the block count fills the CUs)
-        const int rb = (int)std::max<int64_t>(1, std::min<int64_t>({8, 4096 / std::max(1, H),
-                                                                    (int64_t)(49152 / per)}));
-        r.chunk = rb;
-        HIPCHK(launch_rows_deep<real>(r, rb, st));
-      } else if (net->h0) {
-        // the conditionals the sampler stored for these spins and parameters
-        r.sig = net->w_sig.as<real>() + m.spin_off;
-        HIPCHK(launch_rows_h0<real>(r, st));
-      }
+      // the conditionals the sampler stored for these spins and parameters
+      r.sig = net->w_sig.as<real>() + m.spin_off;
+      HIPCHK(launch_rows_h0<real>(r, st));
     }
-    if (!net->deep && !net->h0) {
+    if (!net->h0) {
       RowBatch<real> rb{};
       rb.mi = net->d_mi.as<MadeInst>();
       rb.params = net->params.as<float>();
@@ -1843,15 +1825,12 @@ tnvan_status run_step(tnvan_net *net, float lr, double *stats, int8_t *spins_out
       rb.da = net->w_da.as<real>();
       rb.dlogit = net->w_dlogit.as<real>();
       rb.sf = net->w_sf.as<real>();
-      // more waves per block where the LDS need leaves fewer blocks per CU
-      const int threads[4] = {256, 512, 1024, 1024};
-      for (int c = 0; c < 4; ++c) {
-        rb.jobs = net->rw_jobs[c].as<RowJob>();
-        rb.lo = net->rw_lo[c].as<int32_t>();
-        rb.n_jobs = net->rw_njobs[c];
-        rb.blocks = net->rw_blocks[c];
-        HIPCHK(launch_rows_batch<real>(rb, c < 3, net->rw_lds[c], threads[c], st));
-      }
+      rb.jobs = net->rw_jobs.as<RowJob>();
+      rb.lo = net->rw_lo.as<int32_t>();
+      rb.n_jobs = net->rw_njobs;
+      rb.blocks = net->rw_blocks;
+      rb.deep = net->deep;
+      HIPCHK(launch_rows<real>(rb, net->rw_lds, st));
     }
     HIPCHK(launch_batch_sums<real>(bs, st));
   }
@@ -2502,10 +2481,8 @@ void tnvan_free_network(tnvan_net *net) {
                  &net->mg_task_start, &net->mg_first, &net->mg_count,
                  &net->cpart_off, &net->chain_list, &net->cpart};
   for (DBuf *b : all) b->release();
-  for (int c = 0; c < 4; ++c) {
-    net->rw_jobs[c].release();
-    net->rw_lo[c].release();
-  }
+  net->rw_jobs.release();
+  net->rw_lo.release();
   for (DBuf *b : {&net->wd.steps, &net->wd.fins, &net->wd.sums, &net->wd.tab, &net->wd.insts,
                   &net->wd.prog, &net->wd.lanes, &net->wd.close})
     b->release();

@@ -193,7 +193,6 @@ hipError_t launch_w0t(const MadeInst *mi, int n_inst, int max_n, const float *pa
 template <typename real>
 hipError_t launch_sample_h0(const SampleArgs<real> &a, int n_inst, int64_t max_B, int max_n,
                             hipStream_t st);
-size_t made_param_bytes(int n, int H);
 
 // Deeper networks (some instance with D > 1 hidden layers): one wave per
 // sample for every instance, a lane owning hidden units lane + 64 kk and
@@ -272,8 +271,8 @@ struct RowArgs {
 };
 // The rows of every instance in one launch: job j is one instance with its
 // chunk (samples per block) and its slices of the row buffers, and owns the
-// blocks [lo[j], lo[j + 1]).  `staged`: parameters staged in LDS; `threads`
-// per block, a multiple of 64 up to 1024.
+// blocks [lo[j], lo[j + 1]).  Deeper networks' hid and da hold every layer,
+// [B, D * H] (layer-major inside a row).
 struct RowJob {
   int32_t q, chunk;
   int64_t hoff, doff;      // offsets into hid / da and into dlogit / sf
@@ -288,17 +287,13 @@ struct RowBatch {
   const RowJob *jobs;
   const int32_t *lo;       // [n_jobs + 1]
   int32_t n_jobs, blocks;
+  int32_t deep;            // some instance has hidden layers beyond the first
   real *hid, *da, *dlogit, *sf;
 };
 template <typename real>
-hipError_t launch_rows_batch(const RowBatch<real> &a, bool staged, size_t lds_bytes,
-                             int threads, hipStream_t st);
-// LDS bytes of one block of the batched rows for an (n, H) instance
-size_t rows_lds_bytes(int n, int H, size_t real_bytes, bool staged);
-// deeper networks: hid and da hold every layer, [B, D * H] (layer-major
-// inside a row); rb samples per block round
-template <typename real>
-hipError_t launch_rows_deep(const RowArgs<real> &a, int rb, hipStream_t st);
+hipError_t launch_rows(const RowBatch<real> &a, size_t lds_bytes, hipStream_t st);
+// LDS bytes of a block of `rows` samples of an (n, H, D) instance
+size_t rows_lds_bytes(int n, int H, int D, int rows, size_t real_bytes);
 // one-layer nets: the rows from the conditionals the sampler stored
 template <typename real>
 hipError_t launch_rows_h0(const RowArgs<real> &a, hipStream_t st);

@@ -85,19 +85,10 @@ constexpr int kFreeLanes = 4;      // lanes per sample in the free-energy kernel
 constexpr int KH = 16;    // hidden units per lane
 constexpr int KN = 32;    // width-set positions per lane
 
-// Parameter views with row strides.  With kLDS a block of the row kernel
-// first copies the parameters of its instance into LDS, every matrix's rows
-// padded by one word so that lanes walking down a column hit distinct banks.
+// Parameter views: W1 [H][n], W2 [n][H], W0 [n][n].
 struct MadeView {
-  const float *W1;   // [H][ld1]
-  const float *b1, *W2, *b2, *W0;
-  int ld1, ld2, ld0;
+  const float *W1, *b1, *W2, *b2, *W0;
 };
-
-// LDS bytes of the staged parameters
-__host__ __device__ inline size_t made_stage_bytes(int n, int H) {
-  return (size_t)(H * (n + 1) + n * (H + 1) + n * (n + 1) + H + n) * 4;
-}
 
 __device__ inline MadeView made_view(const float *p, int n, int H) {
   MadeView v;
@@ -106,31 +97,6 @@ __device__ inline MadeView made_view(const float *p, int n, int H) {
   v.W2 = v.b1 + H;
   v.b2 = v.W2 + (int64_t)n * H;
   v.W0 = v.b2 + n;
-  v.ld1 = n; v.ld2 = H; v.ld0 = n;
-  return v;
-}
-
-__device__ inline MadeView made_stage(const MadeView g, int n, int H, float *s) {
-  MadeView v;
-  v.ld1 = n + 1;
-  v.ld2 = H + 1;
-  v.ld0 = n + 1;
-  float *W1 = s, *W2 = W1 + (size_t)H * v.ld1, *W0 = W2 + (size_t)n * v.ld2,
-        *b1 = W0 + (size_t)n * v.ld0, *b2 = b1 + H;
-  for (int i = threadIdx.x; i < n * H; i += blockDim.x) {
-    const int k1 = i / n, j = i - k1 * n;
-    W1[(size_t)k1 * v.ld1 + j] = g.W1[i];
-    const int ii = i / H, k = i - ii * H;
-    W2[(size_t)ii * v.ld2 + k] = g.W2[i];
-  }
-  for (int i = threadIdx.x; i < n * n; i += blockDim.x) {
-    const int ii = i / n, j = i - ii * n;
-    W0[(size_t)ii * v.ld0 + j] = g.W0[i];
-  }
-  for (int i = threadIdx.x; i < H; i += blockDim.x) b1[i] = g.b1[i];
-  for (int i = threadIdx.x; i < n; i += blockDim.x) b2[i] = g.b2[i];
-  __syncthreads();
-  v.W1 = W1; v.b1 = b1; v.W2 = W2; v.b2 = b2; v.W0 = W0;
   return v;
 }
 
@@ -653,152 +619,6 @@ __global__ __launch_bounds__(kD4Threads) void sample_deep4_kernel(SampleArgs<rea
   if (live && c == 0) a.logq[mi.sample_off + b] = lq;
 }
 
-constexpr int kDeepRows = 4096;                // rb H of one block round
-constexpr int kDeepND = kDeepRows / 256;       // per-thread entries of one layer's dh
-
-// Rows of the REINFORCE backward for deeper networks: per sample every
-// layer's h^l, the logits, dlogit = w ((1+s)/2 - sigmoid), and back through
-// the layers da^l = (dh^l) (1 - (h^l)^2) with dh^D = dlogit . W2m and
-// dh^{l-1} = da^l . W^l m.  Rows of rb samples per block round, in LDS with
-// rows padded by one entry.  Items run sample-fastest, so the rb samples of
-// a round share each weight read; the masked sums walk the units of each
-// run of |W| - 1 (degree 1 + t for the t-th unit of a run) without a
-// per-unit test, in ascending order as every sum here.
-template <typename real>
-__global__ __launch_bounds__(256) void rows_deep_kernel(RowArgs<real> a, int rb) {
-  extern __shared__ __align__(16) char smem[];
-  const MadeInst mi = a.mi;
-  const int n = mi.n, Hs = mi.H, H = n >= 2 ? mi.H : 0, D = H > 0 ? mi.D : 1;
-  const int DH = D * Hs;
-  const int ln = n + 1, lh = DH + 1, ld = Hs + 1;
-  const float *P = a.params + mi.param_off;
-  const MadeView w = made_view(P, n, Hs);
-  real *ss = reinterpret_cast<real *>(smem);   // [rb][n + 1]
-  real *hh = ss + (size_t)rb * ln;              // [rb][D H + 1]
-  real *dl = hh + (size_t)rb * lh;              // [rb][n + 1]
-  real *d0 = dl + (size_t)rb * ln;              // [rb][H + 1]: dh of the current layer
-  const double Fq = a.stats[0];
-  const double invB = 1.0 / (double)mi.B;
-  const int64_t c0 = (int64_t)blockIdx.x * a.chunk;
-  const int64_t c1 = (c0 + a.chunk) < mi.B ? (c0 + a.chunk) : mi.B;
-  for (int64_t r0 = c0; r0 < c1; r0 += rb) {
-    const int nr = (int)((c1 - r0) < rb ? (c1 - r0) : rb);
-    for (int i = threadIdx.x; i < rb * n; i += blockDim.x) {
-      const int r = i / n, j = i - r * n;
-      ss[r * ln + j] = r < nr ? (real)a.spins[r0 * n + i] : (real)0;
-    }
-    __syncthreads();
-    // forward through the layers
-    for (int i = threadIdx.x; i < rb * Hs; i += blockDim.x) {
-      const int k = i / rb, r = i - k * rb;
-      real acc = 0;
-      if (k < H) {
-        acc = (real)w.b1[k];
-        const int m = degree(k, n);
-        for (int j = 0; j < m; ++j) acc += (real)w.W1[(int64_t)k * n + j] * ss[r * ln + j];
-        acc = rtanh<real>(acc);
-      }
-      hh[(size_t)r * lh + k] = acc;
-    }
-    __syncthreads();
-    for (int l = 2; l <= D; ++l) {
-      const float *Wl = deep_layer(P, n, Hs, l), *bl = Wl + (int64_t)Hs * Hs;
-      for (int i = threadIdx.x; i < rb * Hs; i += blockDim.x) {
-        const int k2 = i / rb, r = i - k2 * rb;
-        real acc = 0;
-        if (k2 < H) {
-          acc = (real)bl[k2];
-          const int m2 = degree(k2, n);
-          const real *hp = hh + (size_t)r * lh + (size_t)(l - 2) * Hs;
-          // units k with degree(k, n) <= m2
-          for (int base = 0; base < H; base += n - 1) {
-            const int e = m2 < H - base ? m2 : H - base;
-            for (int t = 0; t < e; ++t)
-              acc += (real)Wl[(int64_t)k2 * Hs + base + t] * hp[base + t];
-          }
-          acc = rtanh<real>(acc);
-        }
-        hh[(size_t)r * lh + (size_t)(l - 1) * Hs + k2] = acc;
-      }
-      __syncthreads();
-    }
-    // logits and dlogit
-    for (int i = threadIdx.x; i < rb * n; i += blockDim.x) {
-      const int ii = i / rb, r = i - ii * rb;
-      const real *hD = hh + (size_t)r * lh + (size_t)(D - 1) * Hs;
-      real z = (real)w.b2[ii];
-      // units k with degree(k, n) <= ii
-      for (int base = 0; base < H; base += n - 1) {
-        const int e = ii < H - base ? ii : H - base;
-        for (int t = 0; t < e; ++t) z += (real)w.W2[(int64_t)ii * Hs + base + t] * hD[base + t];
-      }
-      for (int j = 0; j < ii; ++j) z += (real)w.W0[(int64_t)ii * n + j] * ss[r * ln + j];
-      const real sv = ss[r * ln + ii];
-      const real wt = r < nr ? (real)((a.f[mi.sample_off + r0 + r] - Fq) * invB) : (real)0;
-      const real d = wt * (((real)1 + sv) * (real)0.5 - sigmoid<real>(z));
-      dl[r * ln + ii] = d;
-      if (r < nr) {
-        a.dlogit[(r0 + r) * n + ii] = d;
-        a.sf[(r0 + r) * n + ii] = sv;
-      }
-    }
-    __syncthreads();
-    // back through the layers: dh^D from the logits, then W^l down
-    for (int i = threadIdx.x; i < rb * Hs; i += blockDim.x) {
-      const int k = i / rb, r = i - k * rb;
-      real acc = 0;
-      if (k < H) {
-        const int m = degree(k, n);
-        for (int ii = m; ii < n; ++ii) acc += dl[r * ln + ii] * (real)w.W2[(int64_t)ii * Hs + k];
-      }
-      d0[r * ld + k] = acc;
-    }
-    __syncthreads();
-    for (int l = D; l >= 1; --l) {
-      // da^l = dh^l (1 - h^2), written out with h^l
-      for (int i = threadIdx.x; i < rb * Hs; i += blockDim.x) {
-        const int k = i / rb, r = i - k * rb;
-        const real hk = hh[(size_t)r * lh + (size_t)(l - 1) * Hs + k];
-        const real da = d0[r * ld + k] * ((real)1 - hk * hk);
-        d0[r * ld + k] = da;
-        if (r < nr) {
-          a.hid[(r0 + r) * DH + (int64_t)(l - 1) * Hs + k] = hk;
-          a.da[(r0 + r) * DH + (int64_t)(l - 1) * Hs + k] = da;
-        }
-      }
-      __syncthreads();
-      if (l == 1) break;
-      // dh^{l-1}[k] = sum over k2 with m(k2) >= m(k) of da^l[k2] W^l[k2, k],
-      // kept per thread until every thread has read d0
-      const float *Wl = deep_layer(P, n, Hs, l);
-      // (rb H <= kDeepRows: at most kDeepND entries per thread)
-      real nd[kDeepND];
-      int c = 0;
-      for (int i = threadIdx.x; i < rb * Hs && c < kDeepND; i += blockDim.x, ++c) {
-        const int k = i / rb, r = i - k * rb;
-        real acc = 0;
-        if (k < H) {
-          const int m = degree(k, n);
-          // units k2 with degree(k2, n) = 1 + t >= m: t from m - 1 in each run
-          for (int base = 0; base < H; base += n - 1) {
-            const int e = (n - 1) < H - base ? (n - 1) : H - base;
-            for (int t = m - 1; t < e; ++t)
-              acc += d0[r * ld + base + t] * (real)Wl[(int64_t)(base + t) * Hs + k];
-          }
-        }
-        nd[c] = acc;
-      }
-      __syncthreads();
-      c = 0;
-      for (int i = threadIdx.x; i < rb * Hs && c < kDeepND; i += blockDim.x, ++c) {
-        const int k = i / rb, r = i - k * rb;
-        d0[r * ld + k] = nd[c];
-      }
-      __syncthreads();
-    }
-  }
-}
-
 // Columns of W0 for the one-layer sampler: w0t[i][k] = W0[k][i] for k > i,
 // 0 on and above the diagonal (whatever the parameters hold there, as the
 // masks of Eq. 7 require).  32x32 tiles through LDS, both sides coalesced.
@@ -956,10 +776,8 @@ __global__ __launch_bounds__(256) void sample_h0_kernel(SampleArgs<real> a) {
   if (live && lane == 0) a.logq[mi.sample_off + b] = lq;
 }
 
-// Per-sample rows of the log-prob pass and the REINFORCE backward:
-// The batched form: block b belongs to the last job whose first block is
-// at most b (a search over the prefix sums); inside its job it is the block
-// of the same index in the one-job launch's grid.
+// Block b of a batched launch belongs to the last job whose first block is
+// at most b (a search over the prefix sums).
 __device__ inline int job_of(const int32_t *lo, int nj, int b) {
   int a = 0, z = nj - 1;
   while (a < z) {
@@ -970,111 +788,195 @@ __device__ inline int job_of(const int32_t *lo, int nj, int b) {
   return a;
 }
 
-// a, tanh(a), logits, dlogit = w ((1+s)/2 - sigmoid(logit)) with the weight
-// w_b = (f_b - F_q) / B, and da = (dlogit . W2m) (1 - tanh^2).  Block `blk`
-// of an instance walks its chunk of samples in rounds of RB, with the
-// parameters staged in LDS (kLDS).  Items run sample-fastest: the RB samples
-// of a round share each weight (one LDS or cache line per 16 lanes), and the
-// per-sample rows in LDS are padded by one entry against bank conflicts.
-// Every sum runs in ascending index order.
-constexpr int RB = 16;
-template <typename real, bool kLDS>
-__device__ inline void rows_block(const RowArgs<real> &a, int64_t blk, char *smem) {
-  const MadeInst mi = a.mi;
-  const int n = mi.n, H = (n >= 2) ? mi.H : 0, Hs = mi.H;
-  MadeView w = made_view(a.params + mi.param_off, n, Hs);
-  size_t woff = 0;
-  if (kLDS) {
-    w = made_stage(w, n, Hs, reinterpret_cast<float *>(smem));
-    woff = (made_stage_bytes(n, Hs) + 15) & ~(size_t)15;
-  }
-  const int ln = n + 1, lh = Hs + 1;
-  real *ss = reinterpret_cast<real *>(smem + woff);  // [RB][n + 1]
-  real *hh = ss + RB * ln;                           // [RB][H + 1]
-  real *dl = hh + RB * lh;                           // [RB][n + 1]
-  const double Fq = a.stats[0];
-  const double invB = 1.0 / (double)mi.B;
-  const int64_t c0 = blk * a.chunk;
-  const int64_t c1 = (c0 + a.chunk) < mi.B ? (c0 + a.chunk) : mi.B;
-  for (int64_t r0 = c0; r0 < c1; r0 += RB) {
-    const int nr = (int)((c1 - r0) < RB ? (c1 - r0) : RB);
-    const int8_t *sp = a.spins + r0 * n;
-    for (int i = threadIdx.x; i < RB * n; i += blockDim.x) {
-      const int r = i / n, j = i - r * n;
-      ss[r * ln + j] = r < nr ? (real)sp[i] : (real)0;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < RB * Hs; i += blockDim.x) {
-      const int k = i / RB, r = i - k * RB;
-      real acc = 0;
-      if (k < H) {
-        acc = (real)w.b1[k];
-        const int m = degree(k, n);
-        for (int j = 0; j < m; ++j) acc += (real)w.W1[(int64_t)k * w.ld1 + j] * ss[r * ln + j];
-        acc = rtanh<real>(acc);
-      }
-      hh[r * lh + k] = acc;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < RB * n; i += blockDim.x) {
-      const int ii = i / RB, r = i - ii * RB;
-      real z = (real)w.b2[ii];
-      // the units k with degree(k, n) = 1 + k mod (n - 1) <= ii: in every
-      // run of n - 1 units, the first ii
-      for (int base = 0; base < H; base += n - 1) {
-        const int e = ii < H - base ? ii : H - base;
-        for (int t = 0; t < e; ++t)
-          z += (real)w.W2[(int64_t)ii * w.ld2 + base + t] * hh[r * lh + base + t];
-      }
-      for (int j = 0; j < ii; ++j) z += (real)w.W0[(int64_t)ii * w.ld0 + j] * ss[r * ln + j];
-      const real s = ss[r * ln + ii];
-      const real wt = r < nr ? (real)((a.f[mi.sample_off + r0 + r] - Fq) * invB) : (real)0;
-      const real d = wt * (((real)1 + s) * (real)0.5 - sigmoid<real>(z));
-      dl[r * ln + ii] = d;
-      if (r < nr) {
-        a.dlogit[(r0 + r) * n + ii] = d;
-        a.sf[(r0 + r) * n + ii] = s;
-      }
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < RB * Hs; i += blockDim.x) {
-      const int k = i / RB, r = i - k * RB;
-      if (r < nr) {
-        real acc = 0;
-        const real hk = hh[r * lh + k];
-        if (k < H) {
-          const int m = degree(k, n);
-          for (int ii = m; ii < n; ++ii)
-            acc += dl[r * ln + ii] * (real)w.W2[(int64_t)ii * w.ld2 + k];
-        }
-        a.hid[(r0 + r) * Hs + k] = hk;
-        a.da[(r0 + r) * Hs + k] = acc * ((real)1 - hk * hk);
-      }
-    }
-    __syncthreads();
-  }
+// Rows of the log-prob pass and the REINFORCE backward on the matrix cores:
+// h^l = tanh(W^l m h^{l-1} + b^l) from the spins up, the logits, dlogit = w
+// ((1 + s) / 2 - sigmoid(logit)) with the weight w_b = (f_b - F_q) / B, and
+// back down da^D = (dlogit . W2m) (1 - (h^D)^2), da^{l-1} = (da^l . W^l m)
+// (1 - (h^{l-1})^2).
+//
+// A workgroup takes the samples of one chunk: the spins, every layer's rows
+// and dlogit in LDS, 16 samples x 16 outputs per wave and tile as 16x16x4
+// products over the inputs (double precision on the same shape).  A lane's
+// four inputs of a pass of 16 are consecutive, one LDS read; the weights come
+// from memory through the cache, the masks of Eq. 7 applied as zeros.  da^l
+// takes the place of h^l.  What bounds it is the latency of the weight reads;
+// the workgroups per CU hide it.
+//
+// Measured against a thread per (sample, output) with the parameters in LDS
+// or memory: 64 mixed instances (123 k samples, |W| up to 96, H = 128, FP32)
+// 504 -> 190 us in place of three launches; two-layer networks (three
+// instances of 8192 samples, |W| = 32, H = 64) 140 -> 47 us.
+constexpr int kRowThreads = 256;
+__host__ __device__ inline int row_ld(int k) { return ((k + 31) & ~31) + 4; }
+__host__ __device__ inline size_t rows_bytes(int n, int H, int D, int rows, size_t rs) {
+  return rs * (size_t)rows * (2 * row_ld(n) + (size_t)D * row_ld(H) + 1) +
+         4 * (size_t)((H + 15) & ~15);
 }
 
-// Every instance's rows in one launch: the block finds its job (a search
-// over the jobs' first blocks) and runs that instance's block of the same
-// index.
-template <typename real, bool kLDS>
-__global__ __launch_bounds__(1024) void rows_batch_kernel(RowBatch<real> b) {
+template <typename real> struct Tile16;
+template <> struct Tile16<float> {
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  __device__ static v4 mul(float a, float b, v4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  __device__ static int row(int r, int lg) { return 4 * lg + r; }
+};
+template <> struct Tile16<double> {
+  typedef double v4 __attribute__((ext_vector_type(4)));
+  __device__ static v4 mul(double a, double b, v4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+  __device__ static int row(int r, int lg) { return 4 * r + lg; }
+};
+
+template <typename real>
+__global__ __launch_bounds__(kRowThreads) void rows_kernel(RowBatch<real> b) {
+  using TL = Tile16<real>;
+  using v4 = typename TL::v4;
   extern __shared__ __align__(16) char smem[];
-  const int j = job_of(b.lo, b.n_jobs, blockIdx.x);
-  const RowJob J = uload(b.jobs + j);
-  RowArgs<real> a{};
-  a.mi = uload(b.mi + J.q);
-  a.params = b.params;
-  a.spins = b.spins + a.mi.spin_off;
-  a.f = b.f;
-  a.stats = b.stats + 4 * (int64_t)J.q;
-  a.chunk = J.chunk;
-  a.hid = b.hid + J.hoff;
-  a.da = b.da + J.hoff;
-  a.dlogit = b.dlogit + J.doff;
-  a.sf = b.sf + J.doff;
-  rows_block<real, kLDS>(a, (int64_t)blockIdx.x - uload(b.lo + j), smem);
+  const int job = job_of(b.lo, b.n_jobs, blockIdx.x);
+  const RowJob J = uload(b.jobs + job);
+  const MadeInst mi = uload(b.mi + J.q);
+  const int n = mi.n, Hs = mi.H, H = (n >= 2) ? mi.H : 0;
+  const int D = b.deep && H > 0 ? mi.D : 1, DH = D * Hs;
+  const float *P = b.params + mi.param_off;
+  const MadeView w = made_view(P, n, Hs);
+  const int rows = J.chunk, NG = (rows + 15) >> 4;
+  const int64_t r0 = ((int64_t)blockIdx.x - uload(b.lo + job)) * rows;
+  const int nr = (int)(mi.B - r0 < rows ? mi.B - r0 : rows);
+  const int ln = row_ld(n), lh = row_ld(H);
+  real *ss = reinterpret_cast<real *>(smem);   // [rows][ln] spins
+  real *dl = ss + (size_t)rows * ln;           // [rows][ln] dlogit
+  real *hh = dl + (size_t)rows * ln;           // [D][rows][lh]
+  real *wt = hh + (size_t)D * rows * lh;       // [rows]
+  int *dg = reinterpret_cast<int *>(wt + rows);
+  const int tid = threadIdx.x, lane = tid & 63, ls = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int kW = kRowThreads / 64;
+  const int8_t *sp = b.spins + mi.spin_off + r0 * n;
+  const double Fq = b.stats[4 * (int64_t)J.q], invB = 1.0 / (double)mi.B;
+  for (int r = wave; r < rows; r += kW)
+    for (int j = lane; j < ln; j += 64) {
+      const real s = r < nr && j < n ? (real)sp[(int64_t)r * n + j] : (real)0;
+      ss[r * ln + j] = s;
+      dl[r * ln + j] = 0;
+      if (r < nr && j < n) b.sf[J.doff + (r0 + r) * n + j] = s;
+    }
+  for (int r = tid; r < rows; r += kRowThreads)
+    wt[r] = r < nr ? (real)((b.f[mi.sample_off + r0 + r] - Fq) * invB) : (real)0;
+  for (int k = tid; k < ((H + 15) & ~15); k += kRowThreads) dg[k] = k < H ? degree(k, n) : n;
+  real *hid = b.hid + J.hoff + r0 * DH, *da = b.da + J.hoff + r0 * DH;
+  if (H == 0)
+    for (int i = tid; i < nr * Hs; i += kRowThreads) hid[i] = da[i] = 0;
+  __syncthreads();
+
+  // acc += A[rows of group g][k] x weight(k) over k < K (A: zeros up to the
+  // next multiple of 16, as weight)
+  auto product = [&](v4 &acc, const real *A, int ld, int g, int K, auto weight) {
+    const int r = 16 * g + ls;
+    const real *ap = A + (r < rows ? r : rows - 1) * ld + 4 * lg;
+#pragma unroll 2
+    for (int k0 = 0; k0 < K; k0 += 16) {
+      real av[4], bv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) bv[u] = weight(k0 + 4 * lg + u);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) av[u] = ap[k0 + u];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc = TL::mul(av[u], bv[u], acc);
+    }
+  };
+  // every (tile of 16 outputs, group of 16 samples) of N outputs: init(o) and
+  // sum(acc, o, g), then store(row, o, value)
+  auto tiles = [&](int N, auto init, auto sum, auto store) {
+    const int items = ((N + 15) >> 4) * NG;
+    for (int it = wave; it < items; it += kW) {
+      const int g = it % NG, o = 16 * (it / NG) + ls;
+      const real c0 = init(o);
+      v4 acc = {c0, c0, c0, c0};
+      sum(acc, o, g);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * g + TL::row(r, lg);
+        if (row < rows) store(row, o, acc[r]);
+      }
+    }
+  };
+  // up through the layers
+  for (int l = 1; l <= D && H > 0; ++l) {
+    real *hl = hh + (size_t)(l - 1) * rows * lh;
+    const float *Wl = l == 1 ? w.W1 : deep_layer(P, n, Hs, l);
+    const float *bl = l == 1 ? w.b1 : Wl + (int64_t)Hs * Hs;
+    tiles(
+        H, [&](int o) { return o < H ? (real)bl[o] : (real)0; },
+        [&](v4 &acc, int o, int g) {
+          const int oc = o < H ? o : H - 1, m = o < H ? dg[oc] : 0;
+          if (l == 1)
+            product(acc, ss, ln, g, n, [&](int k) {
+              const float x = Wl[(int64_t)oc * n + (k < n ? k : n - 1)];
+              return k < m ? (real)x : (real)0;
+            });
+          else
+            product(acc, hl - (size_t)rows * lh, lh, g, H, [&](int k) {
+              const float x = Wl[(int64_t)oc * Hs + (k < H ? k : H - 1)];
+              return k < H && dg[k] <= m ? (real)x : (real)0;
+            });
+        },
+        [&](int row, int o, real v) {
+          const real h = o < H ? rtanh<real>(v) : (real)0;
+          hl[row * lh + o] = h;
+          if (row < nr && o < H) hid[(int64_t)row * DH + (l - 1) * Hs + o] = h;
+        });
+    __syncthreads();
+  }
+  // logits and dlogit
+  real *hD = hh + (size_t)(D - 1) * rows * lh;
+  tiles(
+      n, [&](int o) { return o < n ? (real)w.b2[o] : (real)0; },
+      [&](v4 &acc, int o, int g) {
+        const int oc = o < n ? o : n - 1;
+        if (H > 0)
+          product(acc, hD, lh, g, H, [&](int k) {
+            const float x = w.W2[(int64_t)oc * Hs + (k < H ? k : H - 1)];
+            return k < H && dg[k] <= oc ? (real)x : (real)0;
+          });
+        const int top = (o | 15) + 1;
+        product(acc, ss, ln, g, top < n ? top : n, [&](int k) {
+          const float x = w.W0[(int64_t)oc * n + (k < n ? k : n - 1)];
+          return k < oc ? (real)x : (real)0;
+        });
+      },
+      [&](int row, int o, real z) {
+        if (o >= n) return;
+        const real d = wt[row] * (((real)1 + ss[row * ln + o]) * (real)0.5 - sigmoid<real>(z));
+        dl[row * ln + o] = d;
+        if (row < nr) b.dlogit[J.doff + (r0 + row) * n + o] = d;
+      });
+  __syncthreads();
+  // back down: da^l = dh^l (1 - (h^l)^2) in the place of h^l
+  for (int l = D; l >= 1 && H > 0; --l) {
+    real *hl = hh + (size_t)(l - 1) * rows * lh;
+    tiles(
+        H, [&](int) { return (real)0; },
+        [&](v4 &acc, int o, int g) {
+          const int oc = o < H ? o : H - 1, m = o < H ? dg[oc] : n;
+          if (l == D) {
+            product(acc, dl, ln, g, n, [&](int k) {
+              const float x = w.W2[(int64_t)(k < n ? k : n - 1) * Hs + oc];
+              return k >= m && k < n ? (real)x : (real)0;
+            });
+          } else {
+            const float *Wl = deep_layer(P, n, Hs, l + 1);
+            product(acc, hl + (size_t)rows * lh, lh, g, H, [&](int k) {
+              const float x = Wl[(int64_t)(k < H ? k : H - 1) * Hs + oc];
+              return k < H && dg[k] >= m ? (real)x : (real)0;
+            });
+          }
+        },
+        [&](int row, int o, real v) {
+          const real h = hl[row * lh + o];
+          const real d = v * ((real)1 - h * h);
+          hl[row * lh + o] = d;
+          if (row < nr && o < H) da[(int64_t)row * DH + (l - 1) * Hs + o] = d;
+        });
+    __syncthreads();
+  }
 }
 
 // The rows of the REINFORCE backward for one-layer nets: dlogit = w_b
@@ -2772,8 +2674,6 @@ void (*pick_mgrad(int ht))(MGradArgs) {
 }  // namespace
 
 
-size_t made_param_bytes(int n, int H) { return made_stage_bytes(n, H); }
-
 int64_t made_pack_floats(int n, int npt, int H) { return mpack_floats(n, npt, H); }
 int64_t made_w2t_offset(int n, int npt) { return msample_floats(n, npt); }
 
@@ -2889,42 +2789,17 @@ hipError_t launch_rows_h0(const RowArgs<real> &a, hipStream_t st) {
   return hipGetLastError();
 }
 
-size_t rows_lds_bytes(int n, int H, size_t real_bytes, bool staged) {
-  const size_t rows = real_bytes * (size_t)RB * (2 * ((size_t)n + 1) + H + 1);
-  return rows + (staged ? (made_param_bytes(n, H) + 15) & ~(size_t)15 : 0);
+size_t rows_lds_bytes(int n, int H, int D, int rows, size_t real_bytes) {
+  return rows_bytes(n, n >= 2 ? H : 0, D, rows, real_bytes);
 }
 
 template <typename real>
-hipError_t launch_rows_batch(const RowBatch<real> &a, bool staged, size_t lds_bytes,
-                             int threads, hipStream_t st) {
+hipError_t launch_rows(const RowBatch<real> &a, size_t lds_bytes, hipStream_t st) {
   if (a.n_jobs <= 0 || a.blocks <= 0) return hipSuccess;
-  if (threads < 64 || threads > 1024 || threads % 64) return hipErrorInvalidValue;
-  const void *k = staged ? reinterpret_cast<const void *>(rows_batch_kernel<real, true>)
-                         : reinterpret_cast<const void *>(rows_batch_kernel<real, false>);
-  hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                     (int)lds_bytes);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(rows_kernel<real>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (e != hipSuccess) return e;
-  if (staged)
-    hipLaunchKernelGGL((rows_batch_kernel<real, true>), dim3(a.blocks), dim3(threads), lds_bytes,
-                       st, a);
-  else
-    hipLaunchKernelGGL((rows_batch_kernel<real, false>), dim3(a.blocks), dim3(threads), lds_bytes,
-                       st, a);
-  return hipGetLastError();
-}
-
-template <typename real>
-hipError_t launch_rows_deep(const RowArgs<real> &a, int rb, hipStream_t st) {
-  if (a.mi.B <= 0) return hipSuccess;
-  if (rb < 1 || (int64_t)rb * a.mi.H > kDeepRows || a.mi.D > kDeepMaxD) return hipErrorInvalidValue;
-  const int D = (a.mi.n >= 2 && a.mi.H > 0) ? a.mi.D : 1;
-  const size_t lds =
-      sizeof(real) * (size_t)rb * (2 * ((size_t)a.mi.n + 1) + (size_t)D * a.mi.H + a.mi.H + 2);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(rows_deep_kernel<real>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  const int64_t blocks = (a.mi.B + a.chunk - 1) / a.chunk;
-  hipLaunchKernelGGL(rows_deep_kernel<real>, dim3((unsigned)blocks), dim3(256), lds, st, a, rb);
+  hipLaunchKernelGGL(rows_kernel<real>, dim3(a.blocks), dim3(kRowThreads), lds_bytes, st, a);
   return hipGetLastError();
 }
 
@@ -3034,14 +2909,10 @@ template hipError_t launch_sample_deep<float>(const SampleArgs<float> &, int, in
                                               int, hipStream_t);
 template hipError_t launch_sample_deep<double>(const SampleArgs<double> &, int, int64_t, bool, int,
                                                int, hipStream_t);
-template hipError_t launch_rows_deep<float>(const RowArgs<float> &, int, hipStream_t);
-template hipError_t launch_rows_deep<double>(const RowArgs<double> &, int, hipStream_t);
 template hipError_t launch_sample_h0<float>(const SampleArgs<float> &, int, int64_t, int, hipStream_t);
 template hipError_t launch_sample_h0<double>(const SampleArgs<double> &, int, int64_t, int, hipStream_t);
-template hipError_t launch_rows_batch<float>(const RowBatch<float> &, bool, size_t, int,
-                                             hipStream_t);
-template hipError_t launch_rows_batch<double>(const RowBatch<double> &, bool, size_t, int,
-                                              hipStream_t);
+template hipError_t launch_rows<float>(const RowBatch<float> &, size_t, hipStream_t);
+template hipError_t launch_rows<double>(const RowBatch<double> &, size_t, hipStream_t);
 template hipError_t launch_rows_h0<float>(const RowArgs<float> &, hipStream_t);
 template hipError_t launch_rows_h0<double>(const RowArgs<double> &, hipStream_t);
 template hipError_t launch_batch_sums<float>(const BatchSums<float> &, hipStream_t);
