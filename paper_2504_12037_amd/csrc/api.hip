@@ -1222,6 +1222,11 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
         c.sg = net->sg;
         ProfScope ps(net, TNVAN_KERNEL_CHAIN_FWD_ALL, st);
         HIPCHK(launch_rchain_pq(c, false, st));
+      } else if ((net->rg_n[0] > 0) + (net->rg_n[1] > 0) + (net->rg_n[2] > 0) > 1 && !net->profile) {
+        // (each width on its own only where each is timed)
+        for (int gi = 0; gi < 3; ++gi) { c.pq_lo[gi] = net->rg_lo[gi]; c.pq_n[gi] = net->rg_n[gi]; }
+        c.sg = net->sg;
+        HIPCHK(launch_rchain_fwd_all(c, st));
       } else {
         for (int gi = 0; gi < 3; ++gi) {
           c.task_base = net->rg_lo[gi];
@@ -1332,6 +1337,9 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
         for (int gi = 0; gi < 3; ++gi) { c.pq_lo[gi] = net->brg_lo[gi]; c.pq_n[gi] = gi < 2 ? net->brg_n[gi] : 0; }
         ProfScope ps(net, TNVAN_KERNEL_CHAIN_BWD_ALL, st);
         HIPCHK(launch_rchain_pq(c, true, st));
+      } else if (net->brg_n[0] > 0 && net->brg_n[1] > 0 && !net->profile) {
+        for (int gi = 0; gi < 2; ++gi) { c.pq_lo[gi] = net->brg_lo[gi]; c.pq_n[gi] = net->brg_n[gi]; }
+        HIPCHK(launch_rchain_bwd_all(c, st));
       } else {
         for (int gi = 0; gi < 2; ++gi) {
           c.task_base = net->brg_lo[gi];
@@ -3050,12 +3058,11 @@ tnvan_status tnvan_logz_batch_noalloc(tnvan_net *net, const int64_t *n_samples,
   c.task_start = L.d_ts;
   HIPCHK(launch_unary(c, L.d_clist, net->n_inst, max_nch, maxB, L.d_f_off, U, fabp, st));
   for (int gi = 0; gi < 3; ++gi) {
-    c.task_base = L.seg_off[gi][0];
-    c.n_tasks = L.seg_off[gi][net->n_inst] - L.seg_off[gi][0];
-    c.ntm = 1 << gi;
-    c.sg = (1 << gi) >= 4 ? 1 : sg;
-    if (c.n_tasks > 0) HIPCHK(launch_rchain(c, false, st));
+    c.pq_lo[gi] = L.seg_off[gi][0];
+    c.pq_n[gi] = L.seg_off[gi][net->n_inst] - L.seg_off[gi][0];
   }
+  c.sg = sg;
+  HIPCHK(launch_rchain_fwd_all(c, st));
   HIPCHK(launch_chain_sum(net->inst.as<InstDesc>(), net->cinst.as<ChainInst>(), L.d_clist,
                           net->n_inst, L.d_B, L.d_sample_off, L.d_cpart_off, cpart, L.d_f_off,
                           fabp, logz, st));

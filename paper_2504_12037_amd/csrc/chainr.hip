@@ -33,6 +33,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "launch.h"
 #include "wave.h"
@@ -1587,6 +1588,71 @@ __global__ __launch_bounds__(256, 3) void rchain_bwd_kernel(ChainArgs a) {
   bwd_chain<CT, kS, kK>(a, tk, D, cd, base, L, lane, a.task_base + blockIdx.x * kWaves + wave);
 }
 
+// The adjoint of both chain widths in one launch: the workgroups of two-tile
+// chains first, then those of the split adjoint of one-tile chains (no
+// workgroup holds both, so every wave of the latter reaches its barrier).
+// ln Z_R and adjoint of one 16x16 lattice, 400 samples, FP32, 85 -> 65 us, of
+// three with 8192 samples 152 -> 146 us, of 32 the same 1370 us.
+template <bool kS, bool kK>
+__global__ __launch_bounds__(256, 3) void rchain_bwd_all_kernel(ChainArgs a) {
+  extern __shared__ __align__(16) char smem[];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  const int nb = (a.pq_n[1] + kWaves - 1) / kWaves;
+  if ((int)blockIdx.x < nb) {
+    const int i = blockIdx.x * kWaves + wave;
+    if (i >= a.pq_n[1]) return;
+    const Task tk = task_at(a, a.pq_lo[1] + i);
+    const InstDesc D = a.inst[tk.q];
+    const ChainInst C = a.cinst[tk.q];
+    const ChainDesc cd = a.chains[C.chain_off + tk.c];
+    const RL L = rlayout(a.lim, true, 1);
+    bwd_chain<2, kS, kK>(a, tk, D, cd, smem + (size_t)wave * L.end, L, lane, a.pq_lo[1] + i);
+    return;
+  }
+  const int pair = wave >> 1, role = wave & 1;
+  const int i = (blockIdx.x - nb) * 2 + pair;
+  const bool has = i < a.pq_n[0];
+  const RL L = rlayout(a.lim, true, 1, true);
+  char *bA = smem + (size_t)(2 * pair) * L.end, *bB = bA + L.end;
+  MeetTask M;
+  MeetState<1> S;
+  if (has) {
+    M = meet_task(a, a.pq_lo[0] + i, lane);
+    meet_phase<1, kS>(a, M, role, 0, L, bA, bB, lane, S);
+  }
+  __syncthreads();
+  if (has) meet_phase<1, kS>(a, M, role, 1, L, bA, bB, lane, S);
+}
+
+// Forward over every chain width in one launch, the widest chains first (SG
+// groups per wave on 1-2 tile chains, one on 4-tile chains, kTop the widest):
+// the widths' launches one after the other each end in a tail of their own.
+// The narrow chains run at the wide ones' register count, which costs less:
+// ln Z_R, launch per width against this, of one 16x16 lattice with strips of
+// 5 and 4 columns, 400 samples, FP32, 35.5 -> 24.7 us, of eight with 8192
+// samples 113 -> 108 us (split products 89 -> 78), of 32 359 -> 351 us; of
+// two 26x26 lattices with strips of 6 and 5, 200 samples, 81 -> 61 us.
+template <int kM, int SG, int kTop>
+__global__ __launch_bounds__(256) void rchain_fwd_all_kernel(ChainArgs a) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  int blk = blockIdx.x, gi = 2;
+  for (; gi > 0; --gi) {
+    const int nb = (a.pq_n[gi] + kWaves - 1) / kWaves;
+    if (blk < nb) break;
+    blk -= nb;
+  }
+  const int i = blk * kWaves + wave;
+  if (i >= a.pq_n[gi]) return;
+  const Task tk = task_at(a, a.pq_lo[gi] + i);
+  const ChainInst C = a.cinst[tk.q];
+  const ChainDesc cd = a.chains[C.chain_off + tk.c];
+  if (kTop >= 4 && gi == 2) fwd_chain<kM, 4, 1>(a, tk, cd, lane);
+  else if (gi == 1) fwd_chain<kM, 2, SG>(a, tk, cd, lane);
+  else if (gi == 0) fwd_chain<kM, 1, SG>(a, tk, cd, lane);
+}
+
 // Persistent forward over every chain width (SG groups per wave on 1-2
 // tile chains, one on 4-tile chains)
 template <int kM, int SG>
@@ -1680,6 +1746,41 @@ hipError_t launch_rchain_pq(const ChainArgs &a, bool bwd, hipStream_t st) {
     return e;
   const int grid = std::max(1, std::min((total + kWaves - 1) / kWaves, cus * std::max(per, 1)));
   hipLaunchKernelGGL(k, dim3(grid), dim3(64 * kWaves), lds, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_rchain_fwd_all(const ChainArgs &a, hipStream_t st) {
+  int64_t blocks = 0;
+  for (int gi = 0; gi < 3; ++gi) blocks += (a.pq_n[gi] + kWaves - 1) / kWaves;
+  if (blocks <= 0) return hipSuccess;
+  const int m = a.bf16 ? 1 : a.split != 0 ? 2 : 0;
+  void (*k)(ChainArgs) = nullptr;
+  auto pick = [&](auto mode) {
+    constexpr int M = decltype(mode)::value;
+    if (a.pq_n[2] > 0) k = a.sg >= 2 ? rchain_fwd_all_kernel<M, 2, 4> : rchain_fwd_all_kernel<M, 1, 4>;
+    else k = a.sg >= 2 ? rchain_fwd_all_kernel<M, 2, 2> : rchain_fwd_all_kernel<M, 1, 2>;
+  };
+  if (m == 0) pick(std::integral_constant<int, 0>{});
+  else if (m == 1) pick(std::integral_constant<int, 1>{});
+  else pick(std::integral_constant<int, 2>{});
+  hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(64 * kWaves), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_rchain_bwd_all(const ChainArgs &a, hipStream_t st) {
+  if (a.pq_n[2] > 0) return hipErrorInvalidValue;   // the adjoint takes chains of <= 2 tiles
+  const int64_t blocks = (a.pq_n[1] + kWaves - 1) / kWaves + (a.pq_n[0] + 1) / 2;
+  if (blocks <= 0) return hipSuccess;
+  const bool sp = a.split != 0 && !a.bf16, kk = rk_of(a.lim) > 1;
+  void (*k)(ChainArgs) = sp ? (kk ? rchain_bwd_all_kernel<true, true> : rchain_bwd_all_kernel<true, false>)
+                            : (kk ? rchain_bwd_all_kernel<false, true> : rchain_bwd_all_kernel<false, false>);
+  const size_t lds = (size_t)kWaves * std::max(rlayout(a.lim, true, 1).end, rlayout(a.lim, true, 1, true).end);
+  hipError_t e;
+  if (lds > 65536 && (e = hipFuncSetAttribute(reinterpret_cast<const void *>(k),
+                                              hipFuncAttributeMaxDynamicSharedMemorySize,
+                                              (int)lds)) != hipSuccess)
+    return e;
+  hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(64 * kWaves), lds, st, a);
   return hipGetLastError();
 }
 

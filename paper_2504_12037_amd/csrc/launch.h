@@ -632,6 +632,10 @@ hipError_t launch_chain_mom_sum(const ChainInst *cinst, const int32_t *chain_ins
                                 const int64_t *inst_sample_off, const int64_t *cpart_off,
                                 const double *mpart, int64_t mtot, double *mean, double *var,
                                 hipStream_t st);
+// the forward of every width of a.pq_lo / a.pq_n, a workgroup per kWaves tasks
+hipError_t launch_rchain_fwd_all(const ChainArgs &a, hipStream_t st);
+// the adjoint of both widths of a.pq_lo / a.pq_n in one launch
+hipError_t launch_rchain_bwd_all(const ChainArgs &a, hipStream_t st);
 // every width of a.pq_lo / a.pq_n in one persistent launch
 hipError_t launch_rchain_pq(const ChainArgs &a, bool bwd, hipStream_t st);
 // logz[b] = log_const + sum over chains of the per-chain partials
