@@ -1166,9 +1166,30 @@ bool any_c64(const tnvan_net *net) {
   return std::count(net->use_c64.begin(), net->use_c64.end(), 1) > 0;
 }
 
+E1Args e1_args(tnvan_net *net, const int8_t *spins, double *e1) {
+  E1Args a{};
+  a.inst = net->inst.as<InstDesc>();
+  a.mi = net->d_mi.as<MadeInst>();
+  a.hw_off = net->d_hw_off.as<int32_t>();
+  a.spins = spins;
+  a.ww_a = net->ww_a.as<int32_t>();
+  a.ww_b = net->ww_b.as<int32_t>();
+  a.ww_J = net->ww_J.as<double>();
+  a.hW = net->hW.as<double>();
+  a.e1 = e1;
+  return a;
+}
+bool all_chains(const tnvan_net *net);
+
+// ln Z_R; sum false: nets of register-resident chains alone leave it as
+// chain partials and unary sums.  e1: also E_1, on the side of the unary
+// factors where every instance has some, else in a launch of its own.
 template <typename real>
-tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStream_t st) {
+tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStream_t st,
+                      bool sum = true, double *e1 = nullptr) {
   Phase ph0(net, "tnvan/logz");
+  const bool side = e1 && all_chains(net) && net->rfwd;
+  const E1Args ea = e1_args(net, spins, e1);
   bool level = false;
   tnvan_status s = ensure_sweep(net, 0, net->tune.general_tile_fwd, &level);
   if (s) return s;
@@ -1213,7 +1234,7 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
         Phase ph(net, "tnvan/boundary");
         HIPCHK(launch_unary(c, net->chain_list.as<int32_t>(), net->n_chain_insts, net->u_chunks,
                             net->u_maxB, net->f_off.as<int64_t>(), net->Ubuf.as<float>(),
-                            net->fabp.as<double>(), st));
+                            net->fabp.as<double>(), st, side ? &ea : nullptr));
       }
       Phase ph(net, "tnvan/steps");
       if (persistent(net)) {
@@ -1241,12 +1262,18 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
     } else {
       HIPCHK(launch_chain(c, false, st));
     }
-    HIPCHK(launch_chain_sum(net->inst.as<InstDesc>(), net->cinst.as<ChainInst>(),
-                            net->chain_list.as<int32_t>(), net->n_chain_insts,
-                            net->d_B.as<int64_t>(), net->d_sample_off.as<int64_t>(),
-                            net->cpart_off.as<int64_t>(), net->cpart.as<double>(),
-                            net->f_off.as<int64_t>(),
-                            net->rfwd ? net->fabp.as<double>() : nullptr, logz, st));
+    if (sum)
+      HIPCHK(launch_chain_sum(net->inst.as<InstDesc>(), net->cinst.as<ChainInst>(),
+                              net->chain_list.as<int32_t>(), net->n_chain_insts,
+                              net->d_B.as<int64_t>(), net->d_sample_off.as<int64_t>(),
+                              net->cpart_off.as<int64_t>(), net->cpart.as<double>(),
+                              net->f_off.as<int64_t>(),
+                              net->rfwd ? net->fabp.as<double>() : nullptr, logz, st));
+  }
+  if (e1 && !side) {
+    int64_t bmax = 0;
+    for (int q = 0; q < net->n_inst; ++q) bmax = std::max(bmax, net->nkey[q]);
+    HIPCHK(launch_e1(ea, net->n_inst, bmax, st));
   }
   return TNVAN_OK;
 }
@@ -1693,12 +1720,12 @@ tnvan_status run_step(tnvan_net *net, float lr, double *stats, int8_t *spins_out
   const bool adj_logz = adj && logz_with_adjoint(net);
   // (chain-only nets leave logZ as chain partials, which the free-energy
   // kernel sums itself; with general instances the adjoint writes it out)
-  const bool cpart_logz = adj_logz && all_chains(net);
+  const bool cpart_logz = all_chains(net) && (adj_logz || net->rfwd);
   if (adj_logz)
     s = run_backward<real>(net, spins, adj->grad, adj->dh, adj->dJ, adj->dbeta, st,
                            cpart_logz ? nullptr : net->w_logz.as<double>());
   else
-    s = run_logz<real>(net, spins, net->w_logz.as<double>(), st);
+    s = run_logz<real>(net, spins, net->w_logz.as<double>(), st, !cpart_logz);
   if (s) return s;
   // f_b and the batch statistics of every instance (Eq. 9)
   int64_t Bmax = 1;
@@ -2665,23 +2692,8 @@ tnvan_status tnvan_logz_batch(tnvan_net *net, const int64_t *n_samples, const in
   if (e1)
     if (tnvan_status s = check_device({e1})) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  tnvan_status s = net->precision == TNVAN_FP64 ? run_logz<double>(net, spins, logz, st)
-                                                : run_logz<float>(net, spins, logz, st);
-  if (s != TNVAN_OK || !e1) return s;
-  E1Args a{};
-  a.inst = net->inst.as<InstDesc>();
-  a.mi = net->d_mi.as<MadeInst>();
-  a.hw_off = net->d_hw_off.as<int32_t>();
-  a.spins = spins;
-  a.ww_a = net->ww_a.as<int32_t>();
-  a.ww_b = net->ww_b.as<int32_t>();
-  a.ww_J = net->ww_J.as<double>();
-  a.hW = net->hW.as<double>();
-  a.e1 = e1;
-  int64_t maxB = 0;
-  for (auto b : net->nkey) maxB = std::max(maxB, b);
-  HIPCHK(launch_e1(a, net->n_inst, maxB, st));
-  return TNVAN_OK;
+  return net->precision == TNVAN_FP64 ? run_logz<double>(net, spins, logz, st, true, e1)
+                                      : run_logz<float>(net, spins, logz, st, true, e1);
 }
 
 namespace {

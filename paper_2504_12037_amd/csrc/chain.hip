@@ -45,6 +45,7 @@
 
 #include <algorithm>
 
+#include "e1.h"
 #include "launch.h"
 #include "wave.h"
 
@@ -770,18 +771,32 @@ __global__ void chain_sum_kernel(const InstDesc *inst, const ChainInst *cinst,
 // instance.  The field on R position p of sample s_W is h_p plus the W-R
 // couplings times the neighbouring width-set spins (Sec. 2).  Positions
 // with at most four W-neighbours read the dense slots (all loads of a
-// position at once); others walk the neighbour list.
+// position at once); others walk the neighbour list.  With ea.e1 the last
+// row of blocks forms E_1 (one launch less; its chain of reads runs beside
+// this one's).
 __global__ __launch_bounds__(256) void unary_kernel(ChainArgs a, const int32_t *cis,
                                                     const int64_t *f_off, float *U,
-                                                    double *fabp) {
+                                                    double *fabp, E1Args ea) {
   typedef const __attribute__((address_space(4))) int32_t *ci32;
   typedef const __attribute__((address_space(4))) float *cf32;
   const int q = cis[blockIdx.z];
+  if (ea.e1 && blockIdx.y == gridDim.y - 1) {
+    // E_1 of the samples beside the unary factors
+    __shared__ E1Term terms[kE1Threads];
+    e1_block(ea, q, blockIdx.x * (int64_t)kE1Threads, terms);
+    return;
+  }
   const InstDesc D = a.inst[q];
   const int64_t B = a.inst_B[q];
   const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int p0 = blockIdx.y * kUnaryChunk;
-  if (p0 >= D.nr) return;
+  if (p0 >= D.nr || blockIdx.x * (int64_t)blockDim.x >= B) return;
+  // the sample's width-set spins as a bit mask, read with uniform indices;
+  // width sets beyond the mask's 128 bits read the spin bytes instead
+  // (loaded before the descriptors below, whose latency they share)
+  const int8_t *srow = a.spins + a.inst_spin_off[q] + (b < B ? b : 0) * D.nw;
+  const bool bits = D.nw <= 128;
+  const SpinBits sb = bits ? load_bits_row(srow, D.nw) : SpinBits{{0u, 0u, 0u, 0u}};
   const int p1 = p0 + kUnaryChunk < D.nr ? p0 + kUnaryChunk : D.nr;
   // the chunk's descriptors (field, four W-neighbour records, neighbour
   // count) staged in LDS by one load per thread, then read with uniform
@@ -803,11 +818,6 @@ __global__ __launch_bounds__(256) void unary_kernel(ChainArgs a, const int32_t *
   }
   __syncthreads();
   if (b >= B) return;
-  // the sample's width-set spins as a bit mask, read with uniform indices;
-  // width sets beyond the mask's 128 bits read the spin bytes instead
-  const int8_t *srow = a.spins + a.inst_spin_off[q] + b * D.nw;
-  const bool bits = D.nw <= 128;
-  const SpinBits sb = bits ? load_bits_row(srow, D.nw) : SpinBits{{0u, 0u, 0u, 0u}};
   auto sigma = [&](int w) { return bits ? sb.sigma(w) : (float)srow[w]; };
   const float beta = (float)D.beta;
   float *Uq = U + a.u_off[q];
@@ -818,7 +828,9 @@ __global__ __launch_bounds__(256) void unary_kernel(ChainArgs a, const int32_t *
     // the table holds from its set-up: nothing to store (unless u_all)
     if (!a.u_all && s_n[i] == 0 && s_h[i] == 0.f) continue;
     float f = s_h[i];
-    if (s_n[i] <= 4) {
+    if (s_n[i] == 1) {
+      f += s_j[i][0] * sigma(s_w[i][0]);   // (most positions beside a column)
+    } else if (s_n[i] <= 4) {
       float t[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) t[k] = s_r[i][k] >= 0 ? s_j[i][k] * sigma(s_w[i][k]) : 0.f;
@@ -938,10 +950,12 @@ hipError_t launch_layout(const LayoutArgs &a, hipStream_t st) {
 
 hipError_t launch_unary(const ChainArgs &a, const int32_t *cis, int n_cis, int max_chunks,
                         int64_t max_B, const int64_t *f_off, float *U, double *fabp,
-                        hipStream_t st) {
-  if (n_cis <= 0 || max_B <= 0 || max_chunks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(unary_kernel, dim3((unsigned)((max_B + 255) / 256), max_chunks, n_cis),
-                     dim3(256), 0, st, a, cis, f_off, U, fabp);
+                        hipStream_t st, const E1Args *e1) {
+  if (n_cis <= 0 || max_B <= 0 || max_chunks + (e1 != nullptr) <= 0) return hipSuccess;
+  static_assert(kE1Threads == 256, "the unary kernel's blocks");
+  hipLaunchKernelGGL(unary_kernel,
+                     dim3((unsigned)((max_B + 255) / 256), max_chunks + (e1 != nullptr), n_cis),
+                     dim3(256), 0, st, a, cis, f_off, U, fabp, e1 ? *e1 : E1Args{});
   return hipGetLastError();
 }
 

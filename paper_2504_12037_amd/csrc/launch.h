@@ -559,7 +559,7 @@ struct ChainArgs {
 constexpr int kUnaryChunk = 16;
 hipError_t launch_unary(const ChainArgs &a, const int32_t *cis, int n_cis, int max_chunks,
                         int64_t max_B, const int64_t *f_off, float *U, double *fabp,
-                        hipStream_t st);
+                        hipStream_t st, const struct E1Args *e1 = nullptr);
 // Chains of FP64 nets (chain64.hip): one wave per (instance, chain, 16
 // samples), four waves per workgroup, chains of 1 and 2 tiles in one launch
 // (the two-tile tasks first), of 4 in another (wide); the unary factors and

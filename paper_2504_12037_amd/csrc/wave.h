@@ -122,6 +122,7 @@ __device__ inline SpinBits load_bits16(const int8_t *s, int nw) {
 
 // a sample's spins (nw <= 128) by the fastest form its row allows
 __device__ inline SpinBits load_bits_row(const int8_t *s, int nw) {
+  if (nw <= 0) return SpinBits{{0u, 0u, 0u, 0u}};
   if ((nw & 15) == 0 && (reinterpret_cast<uintptr_t>(s) & 15) == 0) {
     if (nw <= 32) return load_bits16<2>(s, nw);
     if (nw <= 64) return load_bits16<4>(s, nw);
