@@ -1578,11 +1578,13 @@ tnvan_status ensure_batch_sums(tnvan_net *net, const std::vector<int64_t> &hoff,
     std::vector<AtbJob<real>> aj;
     std::vector<ColJob<real>> cj;
     std::vector<int32_t> alo{0}, aflo{0}, clo{0}, cflo{0};
-    int64_t ptot = 0;
+    int64_t ptot = 0, covered = 0;
+    int32_t cur = 0;
     auto atb = [&](const real *X, int ldx, const real *Y, int ldy, int64_t B, int M, int N,
                    int ks, float *o, int ldo, int mask, int nW) {
       if (M <= 0 || N <= 0) return;
-      AtbJob<real> j{X, Y, o, ptot, B, ldx, ldy, M, N, ks, ldo, mask, nW};
+      AtbJob<real> j{X, Y, o, ptot, B, ldx, ldy, M, N, ks, ldo, mask, nW, cur};
+      covered += (int64_t)M * N;
       ptot += (int64_t)ks * M * N;
       int32_t b = 0, f = 0;
       batch_sum_blocks(M, N, ks, &b, &f);
@@ -1592,7 +1594,8 @@ tnvan_status ensure_batch_sums(tnvan_net *net, const std::vector<int64_t> &hoff,
     };
     auto col = [&](const real *X, int ldx, int64_t B, int M, int ks, float *o) {
       if (M <= 0) return;
-      ColJob<real> j{X, o, ptot, B, ldx, M, ks, 0};
+      ColJob<real> j{X, o, ptot, B, ldx, M, ks, cur};
+      covered += M;
       ptot += (int64_t)ks * M;
       int32_t b = 0, f = 0;
       batch_col_blocks(M, ks, &b, &f);
@@ -1603,6 +1606,8 @@ tnvan_status ensure_batch_sums(tnvan_net *net, const std::vector<int64_t> &hoff,
     for (int q = 0; q < net->n_inst; ++q) {
       const MadeInst &m = net->mi[q];
       if (m.B <= 0) continue;
+      cur = q;
+      covered = 0;
       const int n = m.n, H = m.H;
       const int D = (net->deep && n >= 2 && H > 0) ? m.D : 1;
       const real *hid = net->w_hid.as<real>() + hoff[q], *da = net->w_da.as<real>() + hoff[q];
@@ -1628,6 +1633,9 @@ tnvan_status ensure_batch_sums(tnvan_net *net, const std::vector<int64_t> &hoff,
       }
       atb(dl, n, sf, n, m.B, n, n, ks, gW0, n, 2, n);
       col(dl, n, m.B, n, ks, gb2);
+      // layers that a width set of one spin leaves out: gradient 0
+      const int64_t rest = net->param_count[q] - covered;
+      if (rest > 0) atb(dl, 1, dl, 1, 0, (int)rest, 1, 0, g + covered, 1, 0, n);
     }
     // the per-sample rows (one-layer nets with no hidden units have their
     // own): 32 samples per block while that leaves two blocks per CU and
@@ -1867,14 +1875,9 @@ tnvan_status run_step(tnvan_net *net, float lr, double *stats, int8_t *spins_out
       rb.deep = net->deep;
       HIPCHK(launch_rows<real>(rb, net->rw_lds, st));
     }
-    HIPCHK(launch_batch_sums<real>(bs, st));
-  }
-  }
-  if (!fused) {
-    int64_t max_pc = 1;
-    for (auto pc : net->param_count) max_pc = std::max(max_pc, pc);
     Phase ph(net, "tnvan/adam");
-    HIPCHK(launch_adam_step(o, net->n_inst, max_pc, st));
+    HIPCHK(launch_batch_sums<real>(bs, o, st));
+  }
   }
   if (adj && !adj_logz) return run_backward<real>(net, spins, adj->grad, adj->dh, adj->dJ, adj->dbeta, st);
   return TNVAN_OK;

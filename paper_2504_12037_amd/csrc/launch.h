@@ -311,14 +311,14 @@ struct AtbJob {
   const real *X, *Y;
   float *out;
   int64_t part_off, B;
-  int32_t ldx, ldy, M, N, ks, ldo, mask, nW;
+  int32_t ldx, ldy, M, N, ks, ldo, mask, nW, q;
 };
 template <typename real>
 struct ColJob {
   const real *X;
   float *out;
   int64_t part_off, B;
-  int32_t ldx, M, ks, pad;
+  int32_t ldx, M, ks, q;
 };
 template <typename real>
 struct BatchSums {
@@ -331,8 +331,10 @@ struct BatchSums {
   int32_t atb_blocks, atb_fblocks, col_blocks, col_fblocks;
   real *part;
 };
+// ... and the Adam step of every parameter the jobs cover
+struct OptArgs;
 template <typename real>
-hipError_t launch_batch_sums(const BatchSums<real> &a, hipStream_t st);
+hipError_t launch_batch_sums(const BatchSums<real> &a, const OptArgs &o, hipStream_t st);
 // blocks of one job: (atb, atb finish, colsum, colsum finish)
 void batch_sum_blocks(int M, int N, int ks, int32_t *atb, int32_t *fin);
 void batch_col_blocks(int M, int ks, int32_t *col, int32_t *fin);
@@ -463,7 +465,7 @@ struct ObsArgs {
 hipError_t launch_obs_weights(const ObsArgs &a, int n_inst, hipStream_t st);
 hipError_t launch_obs_w(const ObsArgs &a, int n_inst, hipStream_t st);
 
-// One optimiser step of every instance (see adam_step_kernel).
+// One optimiser step of every instance (see batch_update_kernel).
 struct OptArgs {
   const MadeInst *mi;
   float *params, *grad, *m, *v;
@@ -472,7 +474,6 @@ struct OptArgs {
   float lr;
   const int32_t *step_ctr;   // already counting this step
 };
-hipError_t launch_adam_step(const OptArgs &a, int n_inst, int64_t max_pc, hipStream_t st);
 
 // The net's signature for the autotuner's cache (precision, product form,
 // kernels, widest message scope, instance count), its instance count, and

@@ -996,41 +996,83 @@ __global__ __launch_bounds__(256) void rows_h0_kernel(RowArgs<real> a) {
   a.sf[e] = s;
 }
 
-// part[ks][m][n] = sum over batch rows of slice ks of X[b, m] * Y[b, n]
-constexpr int TM = 32, TN = 32, TK = 32;
+// Adam (Kingma & Ba; beta1 = 0.9, beta2 = 0.999, eps = 1e-8) on one
+// parameter, with the bias corrections c1 = 1 - 0.9^t, c2 = 1 - 0.999^t of
+// step t taken in FP64.  Masked parameters have zero gradient, so they and
+// their moments never move.
+__device__ inline void adam_one(float gi, float &p, float &m, float &v, double c1, double c2,
+                                float lr) {
+  m = 0.9f * m + 0.1f * gi;
+  v = 0.999f * v + 0.001f * gi * gi;
+  const double mh = (double)m / c1, vh = (double)v / c2;
+  p = (float)((double)p - (double)lr * mh / (sqrt(vh) + 1e-8));
+}
+
+__device__ inline void pack_scatter(float *P, int n, int Hs, int npt, int64_t i, float v);
+
+// part[ks][m][n] = sum over batch rows of slice ks of X[b, m] * Y[b, n]: a
+// block has 32 x 32 outputs of a slice, each of its waves a quarter of the
+// rows as 16x16x4 products straight from memory (a row's 16 entries are one
+// line), added over the waves in LDS.  Measured on 64 mixed instances (123 k
+// samples, |W| up to 96, H = 128, FP32) against vector products of tiles
+// staged in LDS: 141 + 15 us with the columns in a launch of their own -> 82 us
+// together; slices and Adam 48 us in three launches -> 21 us in one.
+constexpr int TM = 32, TN = 32;
 template <typename real>
 __device__ inline void atb_block(const real *X, int ldx, const real *Y, int ldy, int64_t B, int M,
                                  int N, real *part, int ksplit, int bx, int by, int ks) {
-  __shared__ real xs[TK][TM + 1];
-  __shared__ real ys[TK][TN + 1];
+  using TL = Tile16<real>;
+  using v4 = typename TL::v4;
+  __shared__ real sh[4][TM * TN];
   const int m0 = bx * TM, n0 = by * TN;
   const int64_t chunk = (B + ksplit - 1) / ksplit;
   const int64_t bb0 = (int64_t)ks * chunk;
   const int64_t bb1 = (bb0 + chunk) < B ? (bb0 + chunk) : B;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;   // 2x2 outputs each
-  real acc[2][2] = {{0, 0}, {0, 0}};
-  for (int64_t k0 = bb0; k0 < bb1; k0 += TK) {
-    for (int i = threadIdx.x; i < TK * TM; i += 256) {
-      const int kk = i / TM, mm = i % TM;
-      const int64_t bi = k0 + kk;
-      xs[kk][mm] = (bi < bb1 && m0 + mm < M) ? X[bi * ldx + m0 + mm] : (real)0;
-      ys[kk][mm] = (bi < bb1 && n0 + mm < N) ? Y[bi * ldy + n0 + mm] : (real)0;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < TK; ++kk) {
-      const real x0 = xs[kk][ty * 2], x1 = xs[kk][ty * 2 + 1];
-      const real y0 = ys[kk][tx * 2], y1 = ys[kk][tx * 2 + 1];
-      acc[0][0] += x0 * y0; acc[0][1] += x0 * y1;
-      acc[1][0] += x1 * y0; acc[1][1] += x1 * y1;
-    }
-    __syncthreads();
-  }
+  const int lane = threadIdx.x & 63, ls = lane & 15, lg = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int mm[2] = {m0 + ls, m0 + 16 + ls}, nn[2] = {n0 + ls, n0 + 16 + ls};
+  const bool two_m = m0 + 16 < M, two_n = n0 + 16 < N;
+  v4 acc[2][2];
+#pragma unroll
   for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) {
-      const int m = m0 + ty * 2 + i, nn = n0 + tx * 2 + j;
-      if (m < M && nn < N) part[((int64_t)ks * M + m) * N + nn] = acc[i][j];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = v4{0, 0, 0, 0};
+  // rows of this wave: passes of 16 a block's width apart
+#pragma unroll 2
+  for (int64_t k0 = bb0 + 16 * wave; k0 < bb1; k0 += 64) {
+    real x[4][2], y[4][2];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t b = k0 + 4 * u + lg, bc = b < bb1 ? b : bb1 - 1;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const real vx = X[bc * ldx + (mm[i] < M ? mm[i] : M - 1)];
+        const real vy = Y[bc * ldy + (nn[i] < N ? nn[i] : N - 1)];
+        x[u][i] = b < bb1 && mm[i] < M ? vx : (real)0;
+        y[u][i] = b < bb1 && nn[i] < N ? vy : (real)0;
+      }
     }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      acc[0][0] = TL::mul(x[u][0], y[u][0], acc[0][0]);
+      if (two_n) acc[0][1] = TL::mul(x[u][0], y[u][1], acc[0][1]);
+      if (two_m) acc[1][0] = TL::mul(x[u][1], y[u][0], acc[1][0]);
+      if (two_m && two_n) acc[1][1] = TL::mul(x[u][1], y[u][1], acc[1][1]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        sh[wave][(16 * i + TL::row(r, lg)) * TN + 16 * j + ls] = acc[i][j][r];
+  __syncthreads();
+  for (int t = threadIdx.x; t < TM * TN; t += 256) {
+    const int m = m0 + t / TN, n = n0 + t % TN;
+    if (m < M && n < N)
+      part[((int64_t)ks * M + m) * N + n] = (sh[0][t] + sh[1][t]) + (sh[2][t] + sh[3][t]);
+  }
 }
 
 // out[m*ldo + n] = mask(m, n) * sum_ks part[ks][m][n]
@@ -1040,8 +1082,8 @@ __device__ inline void atb_block(const real *X, int ldx, const real *Y, int ldy,
 // one output idx of the batch sum C = X^T Y: the slices in order, then the
 // mask of its matrix
 template <typename real>
-__device__ inline void atb_finish_one(const real *part, int ksplit, int M, int N, float *out,
-                                      int ldo, int mask_kind, int nW, int64_t idx) {
+__device__ inline float atb_finish_one(const real *part, int ksplit, int M, int N, int mask_kind,
+                                       int nW, int64_t idx) {
   const int64_t tot = (int64_t)M * N;
   const int m = (int)(idx / N), nn = (int)(idx % N);
   // loads in batches of 8 (independent), additions in slice order
@@ -1060,7 +1102,7 @@ __device__ inline void atb_finish_one(const real *part, int ksplit, int M, int N
   else if (mask_kind == 2) keep = nn < m;
   else if (mask_kind == 3) keep = nW >= 2 && (nn + 1) <= degree(m, nW);
   else if (mask_kind == 4) keep = nW >= 2 && degree(nn, nW) <= degree(m, nW);
-  out[(int64_t)m * ldo + nn] = keep ? (float)acc : 0.0f;
+  return keep ? (float)acc : 0.0f;
 }
 
 // column m of batch slice ks
@@ -1085,7 +1127,7 @@ __device__ inline void colsum_one(const real *X, int ldx, int64_t B, int M, real
 }
 
 template <typename real>
-__device__ inline void colsum_finish_one(const real *part, int ksplit, int M, float *out, int m) {
+__device__ inline float colsum_finish_one(const real *part, int ksplit, int M, int m) {
   // loads in batches of 8 (independent), additions in slice order
   double acc = 0;
   int k = 0;
@@ -1097,40 +1139,72 @@ __device__ inline void colsum_finish_one(const real *part, int ksplit, int M, fl
     for (int j = 0; j < 8; ++j) acc += (double)v[j];
   }
   for (; k < ksplit; ++k) acc += (double)part[(int64_t)k * M + m];
-  out[m] = (float)acc;
+  return (float)acc;
 }
 
+// The batch sums of every matrix and column: the matrices' blocks, then the
+// columns'.
 template <typename real>
-__global__ __launch_bounds__(256) void batch_atb_kernel(BatchSums<real> a) {
-  const int b = blockIdx.x, j = job_of(a.atb_lo, a.n_atb, b);
-  const AtbJob<real> J = uload(a.atb + j);
-  const int t = b - uload(a.atb_lo + j);
-  const int tm = (J.M + TM - 1) / TM, tn = (J.N + TN - 1) / TN;
-  atb_block<real>(J.X, J.ldx, J.Y, J.ldy, J.B, J.M, J.N, a.part + J.part_off, J.ks, t % tm,
-                  (t / tm) % tn, t / (tm * tn));
-}
-template <typename real>
-__global__ __launch_bounds__(256) void batch_atb_finish(BatchSums<real> a) {
-  const int b = blockIdx.x, j = job_of(a.atb_flo, a.n_atb, b);
-  const AtbJob<real> J = uload(a.atb + j);
-  const int64_t idx = (int64_t)(b - uload(a.atb_flo + j)) * blockDim.x + threadIdx.x;
-  if (idx < (int64_t)J.M * J.N)
-    atb_finish_one<real>(a.part + J.part_off, J.ks, J.M, J.N, J.out, J.ldo, J.mask, J.nW, idx);
-}
-template <typename real>
-__global__ __launch_bounds__(256) void batch_col_kernel(BatchSums<real> a) {
-  const int b = blockIdx.x, j = job_of(a.col_lo, a.n_col, b);
+__global__ __launch_bounds__(256) void batch_sums_kernel(BatchSums<real> a) {
+  int b = blockIdx.x;
+  if (b < a.atb_blocks) {
+    const int j = job_of(a.atb_lo, a.n_atb, b);
+    const AtbJob<real> J = uload(a.atb + j);
+    const int t = b - uload(a.atb_lo + j);
+    const int tm = (J.M + TM - 1) / TM, tn = (J.N + TN - 1) / TN;
+    atb_block<real>(J.X, J.ldx, J.Y, J.ldy, J.B, J.M, J.N, a.part + J.part_off, J.ks, t % tm,
+                    (t / tm) % tn, t / (tm * tn));
+    return;
+  }
+  b -= a.atb_blocks;
+  const int j = job_of(a.col_lo, a.n_col, b);
   const ColJob<real> J = uload(a.col + j);
   const int t = b - uload(a.col_lo + j), cm = (J.M + 255) / 256;
   const int m = (t % cm) * 256 + threadIdx.x;
   if (m < J.M) colsum_one<real>(J.X, J.ldx, J.B, J.M, a.part + J.part_off, J.ks, m, t / cm);
 }
+
+// The slices added, the gradient stored, and the Adam step of the same
+// parameter.  The step counter already counts this step (the free-energy
+// kernel advanced it).  With o.pack set, each updated parameter is also
+// written into the packed operand tables (pack_scatter), which then stay
+// current.  The jobs cover every parameter of the instances with samples;
+// the others keep their parameters and moments.
 template <typename real>
-__global__ __launch_bounds__(256) void batch_col_finish(BatchSums<real> a) {
-  const int b = blockIdx.x, j = job_of(a.col_flo, a.n_col, b);
-  const ColJob<real> J = uload(a.col + j);
-  const int m = (b - uload(a.col_flo + j)) * 256 + threadIdx.x;
-  if (m < J.M) colsum_finish_one<real>(a.part + J.part_off, J.ks, J.M, J.out, m);
+__global__ __launch_bounds__(256) void batch_update_kernel(BatchSums<real> a, OptArgs o) {
+  int b = blockIdx.x, q;
+  int64_t at;   // the parameter in the flat buffers
+  float g;
+  if (b < a.atb_fblocks) {
+    const int j = job_of(a.atb_flo, a.n_atb, b);
+    const AtbJob<real> J = uload(a.atb + j);
+    const int64_t idx = (int64_t)(b - uload(a.atb_flo + j)) * blockDim.x + threadIdx.x;
+    if (idx >= (int64_t)J.M * J.N) return;
+    g = atb_finish_one<real>(a.part + J.part_off, J.ks, J.M, J.N, J.mask, J.nW, idx);
+    at = (J.out - o.grad) + (idx / J.N) * J.ldo + idx % J.N;
+    q = J.q;
+  } else {
+    b -= a.atb_fblocks;
+    const int j = job_of(a.col_flo, a.n_col, b);
+    const ColJob<real> J = uload(a.col + j);
+    const int m = (b - uload(a.col_flo + j)) * 256 + threadIdx.x;
+    if (m >= J.M) return;
+    g = colsum_finish_one<real>(a.part + J.part_off, J.ks, J.M, m);
+    at = (J.out - o.grad) + m;
+    q = J.q;
+  }
+  o.grad[at] = g;
+  const double t = (double)o.step_ctr[q];
+  const double c1 = 1.0 - pow(0.9, t), c2 = 1.0 - pow(0.999, t);
+  float p = o.params[at], m = o.m[at], v = o.v[at];
+  adam_one(g, p, m, v, c1, c2, o.lr);
+  o.m[at] = m;
+  o.v[at] = v;
+  o.params[at] = p;
+  if (o.pack) {
+    const MadeInst mi = uload(o.mi + q);
+    pack_scatter(o.pack + mi.pack_off, mi.n, mi.H, o.npt, at - mi.param_off, p);
+  }
 }
 
 // f_b = E_1 - logZ_R / beta + ln q / beta (FP64, Eqs. 4 and 9) per sample and
@@ -1324,45 +1398,6 @@ __global__ __launch_bounds__(kE1Threads) void e1_kernel(E1Args a) {
   e1_block(a, blockIdx.y, (int64_t)blockIdx.x * kE1Threads, terms);
 }
 
-// Adam (Kingma & Ba; beta1 = 0.9, beta2 = 0.999, eps = 1e-8) on one
-// parameter, with the bias corrections c1 = 1 - 0.9^t, c2 = 1 - 0.999^t of
-// step t taken in FP64.  Masked parameters have zero gradient, so they and
-// their moments never move.
-__device__ inline void adam_one(float gi, float &p, float &m, float &v, double c1, double c2,
-                                float lr) {
-  m = 0.9f * m + 0.1f * gi;
-  v = 0.999f * v + 0.001f * gi * gi;
-  const double mh = (double)m / c1, vh = (double)v / c2;
-  p = (float)((double)p - (double)lr * mh / (sqrt(vh) + 1e-8));
-}
-
-__device__ inline void pack_scatter(float *P, int n, int Hs, int npt, int64_t i, float v);
-
-// Adam for every instance in one launch (grid.y = instance), on the flat
-// gradient buffer.  The step counter already counts this step (the
-// free-energy kernel advanced it).  With pack set, each updated parameter
-// is also written into the packed operand tables (pack_scatter), which then
-// stay current.
-__global__ __launch_bounds__(256) void adam_step_kernel(OptArgs a) {
-  const int q = blockIdx.y;
-  const MadeInst mi = a.mi[q];
-  // an instance without samples this step keeps its parameters and moments
-  if (mi.B <= 0) return;
-  const int64_t pc = made_pc(mi);
-  float *P = a.params + mi.param_off, *M = a.m + mi.param_off, *V = a.v + mi.param_off;
-  const float *G = a.grad + mi.param_off;
-  const double t = (double)a.step_ctr[q];
-  const double c1 = 1.0 - pow(0.9, t), c2 = 1.0 - pow(0.999, t);
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < pc;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    float p = P[i], m = M[i], v = V[i];
-    adam_one(G[i], p, m, v, c1, c2, a.lr);
-    M[i] = m;
-    V[i] = v;
-    P[i] = p;
-    if (a.pack) pack_scatter(a.pack + mi.pack_off, mi.n, mi.H, a.npt, i, p);
-  }
-}
 
 // ---------------------------------------------------------------------------
 // Exact slicing (Sec. 2, Eqs. 3-4): every configuration of the width set W is
@@ -2597,7 +2632,7 @@ __global__ __launch_bounds__(64 * kMg3W, 8 / kMg3W) void mgrad3_kernel(MGradArgs
 // instance (grid.y); its four row quarters sum rows k, k + 4, ... in order in
 // FP64, sixteen loads in flight at a time; the quarters are added in order,
 // then the parameter's thread stores the gradient, applies Adam and updates
-// the packed tables (as adam_step_kernel).
+// the packed tables (as batch_update_kernel).
 constexpr int kGaRows = 16;   // row loads in flight per thread
 __global__ __launch_bounds__(256) void grad_adam_kernel(MGradArgs g, OptArgs o) {
   __shared__ double sh[4][64];
@@ -2828,15 +2863,12 @@ void batch_col_blocks(int M, int ks, int32_t *col, int32_t *fin) {
 }
 
 template <typename real>
-hipError_t launch_batch_sums(const BatchSums<real> &a, hipStream_t st) {
-  if (a.n_atb > 0 && a.atb_blocks > 0) {
-    hipLaunchKernelGGL(batch_atb_kernel<real>, dim3(a.atb_blocks), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(batch_atb_finish<real>, dim3(a.atb_fblocks), dim3(256), 0, st, a);
-  }
-  if (a.n_col > 0 && a.col_blocks > 0) {
-    hipLaunchKernelGGL(batch_col_kernel<real>, dim3(a.col_blocks), dim3(256), 0, st, a);
-    hipLaunchKernelGGL(batch_col_finish<real>, dim3(a.col_fblocks), dim3(256), 0, st, a);
-  }
+hipError_t launch_batch_sums(const BatchSums<real> &a, const OptArgs &o, hipStream_t st) {
+  if (a.atb_blocks + a.col_blocks > 0)
+    hipLaunchKernelGGL(batch_sums_kernel<real>, dim3(a.atb_blocks + a.col_blocks), dim3(256), 0, st, a);
+  if (a.atb_fblocks + a.col_fblocks > 0)
+    hipLaunchKernelGGL(batch_update_kernel<real>, dim3(a.atb_fblocks + a.col_fblocks), dim3(256), 0,
+                       st, a, o);
   return hipGetLastError();
 }
 
@@ -2852,13 +2884,6 @@ hipError_t launch_e1(const E1Args &a, int n_inst, int64_t max_B, hipStream_t st)
   const int64_t bx = (max_B + kE1Threads - 1) / kE1Threads;
   if (bx > 0x7fffffff) return hipErrorInvalidValue;
   hipLaunchKernelGGL(e1_kernel, dim3((unsigned)bx, n_inst), dim3(kE1Threads), 0, st, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_adam_step(const OptArgs &a, int n_inst, int64_t max_pc, hipStream_t st) {
-  if (n_inst <= 0) return hipSuccess;
-  const int bx = (int)std::max<int64_t>(1, std::min<int64_t>(1024, (max_pc + 255) / 256));
-  hipLaunchKernelGGL(adam_step_kernel, dim3(bx, n_inst), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -2905,8 +2930,8 @@ template hipError_t launch_rows<float>(const RowBatch<float> &, size_t, hipStrea
 template hipError_t launch_rows<double>(const RowBatch<double> &, size_t, hipStream_t);
 template hipError_t launch_rows_h0<float>(const RowArgs<float> &, hipStream_t);
 template hipError_t launch_rows_h0<double>(const RowArgs<double> &, hipStream_t);
-template hipError_t launch_batch_sums<float>(const BatchSums<float> &, hipStream_t);
-template hipError_t launch_batch_sums<double>(const BatchSums<double> &, hipStream_t);
+template hipError_t launch_batch_sums<float>(const BatchSums<float> &, const OptArgs &, hipStream_t);
+template hipError_t launch_batch_sums<double>(const BatchSums<double> &, const OptArgs &, hipStream_t);
 template hipError_t launch_free<float>(const FreeArgs<float> &, int, hipStream_t);
 template hipError_t launch_free<double>(const FreeArgs<double> &, int, hipStream_t);
 
