@@ -330,6 +330,11 @@ struct Phase {
   }
 };
 
+// whether one of n kernels from `kind` on is being timed
+bool timed(const tnvan_net *net, int kind, int n) {
+  return net->profile && !net->capturing && ((net->prof_mask >> kind) & ((1u << n) - 1)) != 0;
+}
+
 // Events around one launch of a profiled kernel (no-op unless profiling).
 struct ProfScope {
   tnvan_net *net;
@@ -1245,7 +1250,8 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
         c.sg = net->sg;
         ProfScope ps(net, TNVAN_KERNEL_CHAIN_FWD_ALL, st);
         HIPCHK(launch_rchain_pq(c, false, st));
-      } else if ((net->rg_n[0] > 0) + (net->rg_n[1] > 0) + (net->rg_n[2] > 0) > 1 && !net->profile) {
+      } else if ((net->rg_n[0] > 0) + (net->rg_n[1] > 0) + (net->rg_n[2] > 0) > 1 &&
+                 !timed(net, TNVAN_KERNEL_CHAIN_FWD_1, 3)) {
         // (each width on its own only where each is timed)
         for (int gi = 0; gi < 3; ++gi) { c.pq_lo[gi] = net->rg_lo[gi]; c.pq_n[gi] = net->rg_n[gi]; }
         c.sg = net->sg;
@@ -1366,7 +1372,8 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
         for (int gi = 0; gi < 3; ++gi) { c.pq_lo[gi] = net->brg_lo[gi]; c.pq_n[gi] = gi < 2 ? net->brg_n[gi] : 0; }
         ProfScope ps(net, TNVAN_KERNEL_CHAIN_BWD_ALL, st);
         HIPCHK(launch_rchain_pq(c, true, st));
-      } else if (net->brg_n[0] > 0 && net->brg_n[1] > 0 && !net->profile) {
+      } else if (net->brg_n[0] > 0 && net->brg_n[1] > 0 &&
+                 !timed(net, TNVAN_KERNEL_CHAIN_BWD_1, 2)) {
         for (int gi = 0; gi < 2; ++gi) { c.pq_lo[gi] = net->brg_lo[gi]; c.pq_n[gi] = net->brg_n[gi]; }
         HIPCHK(launch_rchain_bwd_all(c, st));
       } else {
