@@ -97,13 +97,14 @@ __device__ inline void load_u(const double *ub, int64_t B, const Chain64Step &sd
 }
 
 // diagonal of a group: the product of its spins' factors (1 for the
-// favoured value, |u| for the other; u < 0 favours -1), zero past its states
+// favoured value, |u| for the other; the sign bit of u favours -1, which a
+// factor too small for a double keeps as -0), zero past its states
 template <int CT, int GR>
 __device__ inline void diag(const double (&u)[GR], int g, int lg, double (&d)[CT][4]) {
   auto ph = [&](int j, bool minus) {
     if (j >= GR) return 1.0;
     const double v = u[j < GR ? j : 0];
-    return j < g ? (minus == (v < 0.0) ? 1.0 : fabs(v)) : 1.0;
+    return j < g ? (minus == (bool)__builtin_signbit(v) ? 1.0 : fabs(v)) : 1.0;
   };
   const double fl = ph(0, lg & 1) * ph(1, lg & 2);
   double fr[4];
@@ -406,8 +407,8 @@ __global__ __launch_bounds__(64 * kWaves, kWide ? 1 : 2) void chain64_bwd_kernel
   else bwd_task<1>(a, k, base);
 }
 
-// Unary factors u of every (position, sample): exp(-2 beta |f|), negative
-// for f < 0, and the sums of beta |f| per run of kUnaryChunk positions; one
+// Unary factors u of every (position, sample): exp(-2 beta |f|), its sign bit
+// set for f < 0, and the sums of beta |f| per run of kUnaryChunk positions; one
 // thread per (sample, run).  f is the field plus the W-R couplings times the
 // width-set spins (Sec. 2).
 __global__ __launch_bounds__(256) void unary64_kernel(Chain64Args a, const int32_t *list,
