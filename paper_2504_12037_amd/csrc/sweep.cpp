@@ -324,6 +324,14 @@ struct Levels {
   // ends the waves' programs and appends them; start[k]: first record
   void finish(int32_t (&start)[kSweepWaves]) {
     for (int k = 0; k < waves; ++k) {
+      // before its program a wave loads transfer factors by its first
+      // record's own words (2: offset), so a record that holds something else
+      // there goes behind an empty one
+      if (!B.rec[k].empty() && (B.rec[k][0] & 15) != SWEEP_FWD && (B.rec[k][0] & 15) != SWEEP_JOINT) {
+        std::vector<int32_t> e(kSweepRec, 0);
+        e[0] = SWEEP_WAIT;
+        B.rec[k].insert(B.rec[k].begin(), e.begin(), e.end());
+      }
       B.put(k, {SWEEP_END});
       B.put(k, {SWEEP_END});   // the record loaded ahead of the last
       // (word 19, a record's own lane words, serves the first record)

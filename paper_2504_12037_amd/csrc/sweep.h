@@ -74,7 +74,7 @@ enum SweepOp : int32_t {
   //   4: position      5..8: R-R edges
   SWEEP_SUM = 4,
   SWEEP_LOGZ = 5,   // ln Z_R from the closing entries
-  SWEEP_WAIT = 6,   // barriers alone
+  SWEEP_WAIT = 6,   // barriers alone, or nothing: ahead of a first record that is no unit
 };
 
 struct SweepInst {
