@@ -432,14 +432,15 @@ bool persistent(const tnvan_net *net) { return net->tune.launch_mode == 2; }
 // out per tile: the launch goes persistent with one arena per workgroup, at
 // most as many workgroups as fit (the batch then runs in chunks of that many
 // tiles).  The budget is half of the device memory that is free or already
-// held by the arena, at most 96 GiB (or the tuned limit).  Returns that workgroup count, or 0
-// when one arena per tile fits.
+// held by the arena (`held` bytes of it now), at most 96 GiB (or the tuned
+// limit).  Returns that workgroup count, or 0 when one arena per tile fits.
+// The checkpoints of FP64 chains keep to the same budget, per task.
 constexpr int64_t kArenaMax = (int64_t)96 << 30;
-int arena_cap(const tnvan_net *net, int64_t tile_bytes, int n_tiles) {
+int arena_cap(const tnvan_net *net, int64_t tile_bytes, int n_tiles, size_t held) {
   size_t fr = 0, tot = 0;
   int64_t budget = kArenaMax;
   if (hipMemGetInfo(&fr, &tot) == hipSuccess)
-    budget = std::min<int64_t>(budget, (int64_t)(fr + net->garena.bytes) / 2);
+    budget = std::min<int64_t>(budget, (int64_t)(fr + held) / 2);
   if (net->tune.arena_limit_mib > 0)
     budget = std::min<int64_t>(budget, (int64_t)net->tune.arena_limit_mib << 20);
   if (tile_bytes <= 0 || tile_bytes * (int64_t)n_tiles <= budget) return 0;
@@ -973,7 +974,7 @@ tnvan_status run_sweep(tnvan_net *net, int mode, TileCache &tc, SweepArgs<real> 
     const int64_t per = t.arena * t.tile;
     const size_t need = (size_t)per * grid * sizeof(real);
     if (need > net->garena.bytes || net->tune.arena_limit_mib > 0)
-      if (const int cap = arena_cap(net, per * (int64_t)sizeof(real), grid)) grid = cap;
+      if (const int cap = arena_cap(net, per * (int64_t)sizeof(real), grid, net->garena.bytes)) grid = cap;
     HIPCHK(net->garena.ensure((size_t)per * grid * sizeof(real)));
     a.c.garena = net->garena.as<real>();
     a.c.garena_stride = per;
@@ -1005,7 +1006,7 @@ tnvan_status run_segments(tnvan_net *net, const ContractArgs<real> &c, bool bwd,
     l.chunk = B;
     const size_t need = (size_t)l.stride * B * sizeof(real);
     if (need > net->garena.bytes || net->tune.arena_limit_mib > 0)
-      if (const int cap = arena_cap(net, l.stride * (int64_t)sizeof(real), B)) l.chunk = cap;
+      if (const int cap = arena_cap(net, l.stride * (int64_t)sizeof(real), B, net->garena.bytes)) l.chunk = cap;
     words = std::max(words, l.stride * l.chunk);
   }
   if (words == 0) return TNVAN_OK;
@@ -1072,7 +1073,7 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
     if (tnvan_status s = quiesce(net)) return s;
     std::vector<int32_t> ti, tc, ts, list;
     std::vector<int64_t> uo(net->n_inst, 0), fo(net->n_inst, 0), co(net->n_inst, 0);
-    int64_t ut = 0, ft = 0, ct = 0, ck = 0;
+    int64_t ut = 0, ft = 0, ct = 0;
     c.max_chunks = 0;
     c.max_B = 0;
     for (int q = 0; q < net->n_inst; ++q) {
@@ -1103,9 +1104,7 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
       }
       c.n[gi] = (int)ti.size() - c.lo[gi];
     }
-    // (the two launches run one after the other and share the checkpoints)
     c.ck_tiles = c.n[1] > 0 ? 2 : 1;
-    ck = std::max((int64_t)c.n[2] * 4, (int64_t)(c.n[0] + c.n[1]) * c.ck_tiles) * c.max_steps * 256;
     HIPCHK(upload(c.ti, ti));
     HIPCHK(upload(c.tc, tc));
     HIPCHK(upload(c.ts, ts));
@@ -1116,7 +1115,6 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
     HIPCHK(c.U.ensure(std::max<int64_t>(1, ut) * sizeof(double)));
     HIPCHK(c.fabp.ensure(std::max<int64_t>(1, ft) * sizeof(double)));
     HIPCHK(c.cpart.ensure(std::max<int64_t>(1, ct) * sizeof(double)));
-    HIPCHK(c.ckpt.ensure(std::max<int64_t>(1, ck) * sizeof(double)));
     c.n_list = (int)list.size();
     c.key = net->nkey;
   }
@@ -1148,21 +1146,34 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
   a.grad = grad;
   a.partial = partial;
   a.inst_partial_off = poff;
-  a.ckpt = c.ckpt.as<double>();
   {
     Phase ph(net, "tnvan/boundary");
     HIPCHK(launch_unary64(a, c.list.as<int32_t>(), c.n_list, c.max_chunks, c.max_B,
                           c.f_off.as<int64_t>(), c.U.as<double>(), c.fabp.as<double>(), st));
   }
-  a.task_base = c.lo[2];
-  a.n_tasks = c.n[2];
-  a.ck_tiles = 4;
-  HIPCHK(launch_chain64(a, true, bwd, st));
-  a.task_base = c.lo[1];
-  a.n_two = c.n[1];
-  a.n_tasks = c.n[1] + c.n[0];
-  a.ck_tiles = c.ck_tiles;
-  HIPCHK(launch_chain64(a, false, bwd, st));
+  // chains of four tiles, then those of two and one.  The adjoint keeps the
+  // states of every step of a task: where those of all tasks exceed the
+  // arena budget they run in passes over the same checkpoints (a launch with
+  // its passes one after the other; each task's arithmetic is its own)
+  for (const bool wide : {true, false}) {
+    const int lo = wide ? c.lo[2] : c.lo[1], n = wide ? c.n[2] : c.n[1] + c.n[0];
+    if (n <= 0) continue;
+    a.ck_tiles = wide ? 4 : c.ck_tiles;
+    int pass = n;
+    if (bwd) {
+      const int64_t per = (int64_t)a.ck_tiles * c.max_steps * 256 * sizeof(double);
+      if ((size_t)(per * n) > c.ckpt.bytes || net->tune.arena_limit_mib > 0)
+        if (const int cap = arena_cap(net, per, n, c.ckpt.bytes)) pass = cap;
+      HIPCHK(c.ckpt.ensure((size_t)per * pass));
+      a.ckpt = c.ckpt.as<double>();
+    }
+    for (int t = 0; t < n; t += pass) {
+      a.task_base = lo + t;
+      a.n_tasks = std::min(pass, n - t);
+      a.n_two = wide ? 0 : std::min(std::max(c.n[1] - t, 0), a.n_tasks);
+      HIPCHK(launch_chain64(a, wide, bwd, st));
+    }
+  }
   if (logz)
     HIPCHK(launch_chain_sum(a.inst, a.cinst, c.list.as<int32_t>(), c.n_list, a.inst_B,
                             a.inst_sample_off, a.cpart_off, c.cpart.as<double>(),
@@ -1219,7 +1230,7 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
   } else if (net->glob_fwd) {
     int64_t per = 0;
     for (auto &D : net->P.insts) per = std::max(per, contract_garena_entries(D, net->S_fwd, false));
-    cap = arena_cap(net, per * (int64_t)sizeof(real), net->tc_fwd.n_tiles);
+    cap = arena_cap(net, per * (int64_t)sizeof(real), net->tc_fwd.n_tiles, net->garena.bytes);
     HIPCHK(net->garena.ensure((size_t)per * (cap ? cap : net->tc_fwd.n_tiles) * sizeof(real)));
     a.garena = net->garena.as<real>();
     a.garena_stride = per;
@@ -1338,7 +1349,7 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
   } else if (net->glob_bwd) {
     int64_t per = 0;
     for (auto &D : net->P.insts) per = std::max(per, contract_garena_entries(D, net->S_bwd, true));
-    cap = arena_cap(net, per * (int64_t)sizeof(real), tc.n_tiles);
+    cap = arena_cap(net, per * (int64_t)sizeof(real), tc.n_tiles, net->garena.bytes);
     HIPCHK(net->garena.ensure((size_t)per * (cap ? cap : tc.n_tiles) * sizeof(real)));
     a.garena = net->garena.as<real>();
     a.garena_stride = per;
