@@ -139,14 +139,16 @@ typedef struct {
  * every choice gives the same results up to the summation order of the
  * kernels involved (within each path's tolerance).  A field set to 0 takes
  * the library's default rule. */
-#define TNVAN_TUNE_GENERAL 1     /* kinds: the general-step kernel runs */
+#define TNVAN_TUNE_GENERAL 1     /* kinds: the general-step or level kernels run */
 #define TNVAN_TUNE_REG_CHAIN 2   /* the register-resident chain kernels run */
 #define TNVAN_TUNE_LDS_CHAIN 4   /* the LDS-staged chain kernels run */
 typedef struct {
-  /* samples per workgroup tile of the general-step kernel (dense and
+  /* samples per workgroup tile of the general instances (dense and
    * single-spin steps of non-chain programs), forward and adjoint: 0 or a
    * power of two 1..64 (the arena stays in LDS when the tile fits it, else
-   * it moves to device memory) */
+   * it moves to device memory).  Nets of single-spin programs run the level
+   * kernels at the default and up to 8, whose default follows the batch; the
+   * general-step kernel above 8 */
   int32_t general_tile_fwd;
   int32_t general_tile_bwd;
   /* 16-sample groups per wave of the register-resident chain forward on
@@ -172,8 +174,9 @@ typedef struct {
   int32_t reserved[1];
 } tnvan_tuning;
 
-/* The launch shapes in effect (defaults resolved; chain_groups 0 until a
- * batch has been laid out). */
+/* The launch shapes in effect (defaults resolved; chain_groups and the level
+ * kernels' default tiles 0 until a batch has been laid out, forward and
+ * adjoint each). */
 tnvan_status tnvan_get_tuning(const tnvan_net *net, tnvan_tuning *out);
 /* Request launch shapes (0 = default rule per field).  The next call lays
  * its tables out again.  Errors: a field out of range or a general tile

@@ -168,7 +168,8 @@ struct tnvan_net {
     size_t lds = 0;
     DBuf steps, fins, sums, tab, insts, prog, lanes, close;
   } wd;
-  int S_fwd = 1, S_bwd = 1;
+  int S_fwd = 1, S_bwd = 1;       // tile of the step-by-step kernel
+  int ran_fwd = 0, ran_bwd = 0;   // general tile of the batch laid out (0: none)
   bool glob_fwd = false, glob_bwd = false;
   size_t lds_fwd = 0, lds_bwd = 0;
   std::vector<int32_t> h_blk_inst, h_blk_start;
@@ -385,7 +386,7 @@ bool choose_tiles(tnvan_net *net, bool bwd, int req = 0) {
   auto worst_of = [&](int S, bool glob) {
     size_t worst = 0;
     for (size_t q = 0; q < net->P.insts.size(); ++q)
-      if (!net->use_chain[q])
+      if (!net->on_chain((int)q))
         worst = std::max(worst, contract_lds_bytes(net->P.insts[q], S, bwd, glob, net->rs()));
     return worst;
   };
@@ -583,6 +584,7 @@ tnvan_status set_batch(tnvan_net *net, const int64_t *n_samples) {
   net->tc_fwd.key.clear();
   net->tc_bwd.key.clear();
   net->tc_mom.key.clear();
+  net->ran_fwd = net->ran_bwd = 0;
   net->skey.clear();
   net->ckey.clear();
   return TNVAN_OK;
@@ -1211,13 +1213,13 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
   bool level = false;
   tnvan_status s = ensure_sweep(net, 0, net->tune.general_tile_fwd, &level);
   if (s) return s;
-  if (level) net->S_fwd = net->sw[0].tile;
   bool segs = false;
   if ((s = ensure_segments(net, net->tune.general_tile_fwd, &segs))) return s;
-  if (segs) net->S_fwd = 1;
-  s = ensure_tiles(net, net->tc_fwd, net->S_fwd, false);
+  const int S = level ? net->sw[0].tile : segs ? 1 : net->S_fwd;
+  s = ensure_tiles(net, net->tc_fwd, S, false);
   if (s) return s;
-  auto a = contract_args<real>(net, net->tc_fwd, net->S_fwd);
+  net->ran_fwd = S;
+  auto a = contract_args<real>(net, net->tc_fwd, S);
   a.spins = spins;
   a.logz = logz;
   int cap = 0;
@@ -1229,7 +1231,7 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
     if ((s = run_segments<real>(net, a, false, st))) return s;
   } else if (net->glob_fwd) {
     int64_t per = 0;
-    for (auto &D : net->P.insts) per = std::max(per, contract_garena_entries(D, net->S_fwd, false));
+    for (auto &D : net->P.insts) per = std::max(per, contract_garena_entries(D, S, false));
     cap = arena_cap(net, per * (int64_t)sizeof(real), net->tc_fwd.n_tiles, net->garena.bytes);
     HIPCHK(net->garena.ensure((size_t)per * (cap ? cap : net->tc_fwd.n_tiles) * sizeof(real)));
     a.garena = net->garena.as<real>();
@@ -1326,14 +1328,14 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
   bool level = false;
   tnvan_status s = ensure_sweep(net, 1, net->tune.general_tile_bwd, &level);
   if (s) return s;
-  if (level) net->S_bwd = net->sw[1].tile;
   bool segs = false;
   if ((s = ensure_segments(net, net->tune.general_tile_bwd, &segs))) return s;
-  if (segs) net->S_bwd = 1;
-  s = ensure_tiles(net, net->tc_bwd, net->S_bwd, true);
+  const int S = level ? net->sw[1].tile : segs ? 1 : net->S_bwd;
+  s = ensure_tiles(net, net->tc_bwd, S, true);
   if (s) return s;
+  net->ran_bwd = S;
   TileCache &tc = net->tc_bwd;
-  auto a = contract_args<real>(net, tc, net->S_bwd);
+  auto a = contract_args<real>(net, tc, S);
   a.spins = spins;
   a.grad = grad;
   HIPCHK(net->partial.ensure(std::max<int64_t>(1, tc.partial_total) * sizeof(real)));
@@ -1348,7 +1350,7 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
     if ((s = run_segments<real>(net, a, true, st))) return s;
   } else if (net->glob_bwd) {
     int64_t per = 0;
-    for (auto &D : net->P.insts) per = std::max(per, contract_garena_entries(D, net->S_bwd, true));
+    for (auto &D : net->P.insts) per = std::max(per, contract_garena_entries(D, S, true));
     cap = arena_cap(net, per * (int64_t)sizeof(real), tc.n_tiles, net->garena.bytes);
     HIPCHK(net->garena.ensure((size_t)per * (cap ? cap : tc.n_tiles) * sizeof(real)));
     a.garena = net->garena.as<real>();
@@ -2157,8 +2159,11 @@ tnvan_status net_signature(const tnvan_net *net, std::string &out) {
   int maxw = 0;
   for (auto &D : net->P.insts) maxw = std::max(maxw, (int)D.max_w);
   static const char *prec[] = {"fp64", "fp32", "bf16"};
+  // (a tile tuned on one general kernel says nothing about another)
+  const bool gen = (t.kinds & TNVAN_TUNE_GENERAL) != 0;
   out = std::string(prec[net->precision]) + (net->split ? "+split" : "") + "|k" +
-        std::to_string(t.kinds) + "|w" + std::to_string(maxw) + "|n" + std::to_string(net->n_inst);
+        std::to_string(t.kinds) + (gen && net->sweep ? "+level" : gen && net->segments ? "+segments" : "") +
+        (any_c64(net) ? "+chain64" : "") + "|w" + std::to_string(maxw) + "|n" + std::to_string(net->n_inst);
   return TNVAN_OK;
 }
 
@@ -3109,11 +3114,21 @@ tnvan_status tnvan_get_tuning(const tnvan_net *net, tnvan_tuning *out) {
   if (!out) return set_err(TNVAN_E_INVALID, "out is NULL");
   *out = tnvan_tuning{};
   bool gen = false, chain = false;
-  for (int q = 0; q < net->n_inst; ++q) (net->use_chain[q] ? chain : gen) = true;
+  for (int q = 0; q < net->n_inst; ++q) {
+    chain = chain || net->use_chain[q];
+    gen = gen || !net->on_chain(q);
+  }
   out->kinds = (gen ? TNVAN_TUNE_GENERAL : 0) | (chain && net->rfwd ? TNVAN_TUNE_REG_CHAIN : 0) |
                (chain && !net->rfwd ? TNVAN_TUNE_LDS_CHAIN : 0);
-  out->general_tile_fwd = gen ? net->S_fwd : 0;
-  out->general_tile_bwd = gen ? net->S_bwd : 0;
+  // the level kernels choose a default tile by the batch; the segments take
+  // one sample each whatever tile up to theirs is asked for
+  auto tile = [&](int req, int S, int ran) {
+    if (net->sweep && req == 0) return ran;
+    if (net->wd.state > 0 && req <= kSweepTile) return 1;
+    return S;
+  };
+  out->general_tile_fwd = gen ? tile(net->tune.general_tile_fwd, net->S_fwd, net->ran_fwd) : 0;
+  out->general_tile_bwd = gen ? tile(net->tune.general_tile_bwd, net->S_bwd, net->ran_bwd) : 0;
   out->chain_groups = chain && net->rfwd ? (net->tune.chain_groups > 0 ? net->tune.chain_groups
                                                                        : net->ckey.empty() ? 0 : net->sg)
                                          : 0;
@@ -3167,6 +3182,7 @@ tnvan_status tnvan_set_tuning(tnvan_net *net, const tnvan_tuning *in) {
   // for the work queued with the old layout), and a recorded step is stale
   net->tc_fwd.key.clear();
   net->tc_bwd.key.clear();
+  net->ran_fwd = net->ran_bwd = 0;
   net->ckey.clear();
   g_buf_gen.fetch_add(1);
   return TNVAN_OK;
