@@ -147,15 +147,20 @@ struct tnvan_net {
   DBuf d_sample_off, d_B, d_spin_off, d_spin_base, d_edge_base;
   TileCache tc_fwd, tc_bwd, tc_mom;
   // every instance off the chain kernels runs the level kernels (sweep.h):
-  // the schedule per mode (forward, adjoint, jets) for its tile size
+  // the schedules per mode (forward, adjoint, jets) and tile (1, 2, 4, 8),
+  // each built when a batch first asks for it and kept, so that batches of
+  // different sizes in turn find theirs; and the shapes of the batch laid out
   struct SweepTab {
-    int key = -1;               // tile the schedule was asked for
-    int tile = 0;               // samples per tile
-    int waves = 0;              // waves per workgroup
-    bool glob = false;          // arena in device memory
-    size_t lds = 0;             // 0: no tile of that size fits
+    bool built = false;
+    size_t lds[2] = {0, 0};     // with the arena in LDS, in device memory
     int64_t arena = 0;          // entries per sample of the largest arena
     DBuf insts, prog, lanes, close;
+  } sw_tab[3][4];
+  struct SweepShape {
+    SweepTab *tab = nullptr;
+    int tile = 0;               // samples per tile
+    bool glob = false;          // arena in device memory
+    size_t lds = 0;
   } sw[3];
   bool sweep = false;
   // every instance off the chain kernels runs in segments between launches
@@ -744,7 +749,36 @@ tnvan_status ensure_chain_tasks(tnvan_net *net) {
   return TNVAN_OK;
 }
 
-// The schedule of the level kernels of `mode` for the current batch, with
+// The schedule of the level kernels of `mode` for tiles of S samples.
+tnvan_status sweep_table(tnvan_net *net, int mode, int S, tnvan_net::SweepTab **out) {
+  tnvan_net::SweepTab &t = net->sw_tab[mode][ilog2(S)];
+  *out = &t;
+  if (t.built) return TNVAN_OK;
+  if (net->capturing) return set_err(TNVAN_E_STATE, "schedule changed while recording");
+  const int rs = net->rs();
+  std::vector<int32_t> run(net->n_inst);
+  for (int q = 0; q < net->n_inst; ++q) run[q] = !net->on_chain(q);
+  SweepPlan plan;
+  build_sweep(net->P, run, S, kSweepWaves, mode == 1, sweep_walk(mode, rs), plan);
+  t.lds[0] = t.lds[1] = 0;
+  t.arena = 1;
+  for (int q = 0; q < net->n_inst; ++q) {
+    if (!run[q]) continue;
+    for (int g = 0; g < 2; ++g)
+      t.lds[g] = std::max(t.lds[g], sweep_lds_bytes(net->P.insts[q], plan.insts[q], S, mode, g != 0, rs));
+    t.arena = std::max<int64_t>(t.arena, plan.insts[q].arena);
+  }
+  if (mode == 2) t.arena *= 3;
+  // (the table's own buffers: no launch reads them yet)
+  HIPCHK(upload(t.insts, plan.insts));
+  HIPCHK(upload(t.prog, plan.prog));
+  HIPCHK(upload(t.lanes, plan.lanes));
+  HIPCHK(upload(t.close, plan.close));
+  t.built = true;
+  return TNVAN_OK;
+}
+
+// The shape of the level kernels of `mode` for the current batch, with
 // req samples per tile (0: the default rule); *ok false when the net has
 // other programs or no such tile fits the LDS: the step-by-step kernel runs.
 //
@@ -763,69 +797,45 @@ tnvan_status ensure_chain_tasks(tnvan_net *net) {
 tnvan_status ensure_sweep(tnvan_net *net, int mode, int req, bool *ok) {
   *ok = false;
   if (!net->sweep || req > kSweepTile) return TNVAN_OK;
-  tnvan_net::SweepTab &t = net->sw[mode];
-  const int rs = net->rs();
   auto tiles = [&](int S) {
     int64_t n = 0;
     for (int q = 0; q < net->n_inst; ++q)
       if (!net->on_chain(q)) n += (net->nkey[q] + S - 1) / S;
     return n;
   };
-  std::vector<int32_t> run(net->n_inst);
-  for (int q = 0; q < net->n_inst; ++q) run[q] = !net->on_chain(q);
-  SweepPlan plan;
-  const int waves = kSweepWaves;
-  auto lds_of = [&](int S, bool glob) {
-    build_sweep(net->P, run, S, waves, mode == 1, sweep_walk(mode, rs), plan);
-    size_t w = 0;
-    for (int q = 0; q < net->n_inst; ++q)
-      if (run[q]) w = std::max(w, sweep_lds_bytes(net->P.insts[q], plan.insts[q], S, mode, glob, rs));
-    return w;
-  };
   int dev = 0, maxlds = 65536;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+  const size_t budget = std::min<size_t>((size_t)maxlds, 80 * 1024);
   int S = req;
   if (S == 0) {
-    S = mode == 1 && rs == 8 ? 2 : kSweepTile;
+    S = mode == 1 && net->rs() == 8 ? 2 : kSweepTile;
     while (S > 1 && tiles(S) < (S > 2 ? 512 : 256)) S >>= 1;
   }
-  const int S0 = S, key = 2 * S + (req > 0);
-  if (t.key == key) {   // scheduled before
-    *ok = t.lds > 0;
-    return TNVAN_OK;
-  }
-  bool glob = mode == 1;
-  size_t lds = lds_of(S, glob);
+  const int S0 = S;
+  tnvan_net::SweepShape &p = net->sw[mode];
+  p.glob = mode == 1;
+  auto take = [&](int tile) -> tnvan_status {
+    S = tile;
+    return sweep_table(net, mode, S, &p.tab);
+  };
+  auto lds = [&] { return p.tab->lds[p.glob]; };
+  if (tnvan_status s = take(S)) return s;
   if (req == 0) {
-    const size_t budget = std::min<size_t>((size_t)maxlds, 80 * 1024);
-    while (S > 1 && lds > budget && (glob || (S > 2 && S0 < kSweepTile))) lds = lds_of(S >>= 1, glob);
-    if (!glob && lds > budget) {
-      glob = true;
-      S = S0;
-      lds = lds_of(S, true);
-      while (S > 1 && lds > budget) lds = lds_of(S >>= 1, true);
+    while (S > 1 && lds() > budget && (p.glob || (S > 2 && S0 < kSweepTile)))
+      if (tnvan_status s = take(S >> 1)) return s;
+    if (!p.glob && lds() > budget) {
+      p.glob = true;
+      if (tnvan_status s = take(S0)) return s;
+      while (S > 1 && lds() > budget)
+        if (tnvan_status s = take(S >> 1)) return s;
     }
-  } else if (!glob && lds > (size_t)maxlds) {
-    glob = true;
-    lds = lds_of(S, true);
+  } else if (!p.glob && lds() > (size_t)maxlds) {
+    p.glob = true;
   }
-  if (net->capturing) return set_err(TNVAN_E_STATE, "schedule changed while recording");
-  if (tnvan_status s = quiesce(net)) return s;
-  t.key = -1;
-  t.tile = S;
-  t.waves = waves;
-  t.glob = glob;
-  t.lds = lds <= (size_t)maxlds ? lds : 0;
-  t.arena = 1;
-  for (auto &w : plan.insts) t.arena = std::max<int64_t>(t.arena, w.arena);
-  if (mode == 2) t.arena *= 3;
-  HIPCHK(upload(t.insts, plan.insts));
-  HIPCHK(upload(t.prog, plan.prog));
-  HIPCHK(upload(t.lanes, plan.lanes));
-  HIPCHK(upload(t.close, plan.close));
-  t.key = key;
-  *ok = t.lds > 0;
+  p.tile = S;
+  p.lds = lds();
+  *ok = p.lds <= (size_t)maxlds;
   return TNVAN_OK;
 }
 
@@ -966,14 +976,15 @@ ContractArgs<real> contract_args(tnvan_net *net, TileCache &tc, int S) {
 // arena_cap.
 template <typename real>
 tnvan_status run_sweep(tnvan_net *net, int mode, TileCache &tc, SweepArgs<real> &a, hipStream_t st) {
-  tnvan_net::SweepTab &t = net->sw[mode];
+  const tnvan_net::SweepShape &p = net->sw[mode];
+  const tnvan_net::SweepTab &t = *p.tab;
   a.insts = t.insts.as<SweepInst>();
   a.prog = t.prog.as<int32_t>();
   a.lanes = t.lanes.as<int32_t>();
   a.close = t.close.as<int32_t>();
   int grid = persistent(net) ? std::min(tc.n_tiles, 1024) : tc.n_tiles;
-  if (t.glob && tc.n_tiles > 0) {
-    const int64_t per = t.arena * t.tile;
+  if (p.glob && tc.n_tiles > 0) {
+    const int64_t per = t.arena * p.tile;
     const size_t need = (size_t)per * grid * sizeof(real);
     if (need > net->garena.bytes || net->tune.arena_limit_mib > 0)
       if (const int cap = arena_cap(net, per * (int64_t)sizeof(real), grid, net->garena.bytes)) grid = cap;
@@ -981,7 +992,7 @@ tnvan_status run_sweep(tnvan_net *net, int mode, TileCache &tc, SweepArgs<real> 
     a.c.garena = net->garena.as<real>();
     a.c.garena_stride = per;
   }
-  HIPCHK(launch_sweep<real>(a, tc.n_tiles, t.lds, mode, t.glob, t.waves, grid, st));
+  HIPCHK(launch_sweep<real>(a, tc.n_tiles, p.lds, mode, p.glob, kSweepWaves, grid, st));
   return TNVAN_OK;
 }
 
@@ -2553,8 +2564,9 @@ void tnvan_free_network(tnvan_net *net) {
                   &net->c64.f_off, &net->c64.cpart_off, &net->c64.U, &net->c64.fabp,
                   &net->c64.cpart, &net->c64.ckpt})
     b->release();
-  for (auto &t : net->sw)
-    for (DBuf *b : {&t.insts, &t.prog, &t.lanes, &t.close}) b->release();
+  for (auto &mode : net->sw_tab)
+    for (auto &t : mode)
+      for (DBuf *b : {&t.insts, &t.prog, &t.lanes, &t.close}) b->release();
   TileCache *tcs[] = {&net->tc_fwd, &net->tc_bwd, &net->tc_mom};
   for (TileCache *tc : tcs) {
     tc->tile_inst.release(); tc->tile_start.release(); tc->first_tile.release();
