@@ -1503,6 +1503,33 @@ tnvan_status ensure_sample_blocks(tnvan_net *net) {
   return TNVAN_OK;
 }
 
+// Small deeper networks on four lanes per sample instead of 16 (the same
+// spins).  Four lanes need a quarter of the instructions for a position's
+// products and read staged parameters, which pays more the longer the width
+// set and the fuller the chip (16 samples to a wave: 16384 are a wave per
+// SIMD).  But the H / (|W| - 1) units that a position completes go by a quarter
+// of the lanes: `e` tanh one after the other, on as many lanes at a time as
+// units |W| - 1 apart fall on; and four layers' staged columns leave one block
+// per CU.  The lines are where the two cross, over |W| = 2 to 33, H = 8 to 64 and
+// 64 to 65536 samples: sampling times of four lanes over 16, two layers,
+// FP32: |W| = 3, H = 64: 1.37 at 64 samples, 0.83 at 8192, 0.39 at 65536; |W| = 9,
+// H = 64: 1.25, 1.00, 0.58; |W| = 5, H = 16: 1.36, 1.29, 0.97; |W| = 12, H = 32: 1.04
+// at 64, 0.66 at 65536; |W| = 33, H = 64: 0.95 and 0.57; four layers, H = 32:
+// |W| = 20 0.96 and 1.36, |W| = 9 1.34 and 1.63.  FP64, two layers, H = 32: |W| = 5
+// 1.96 at 64, 0.84 at 65536; |W| = 12 0.79 and 0.35.  The choice is within a fifth
+// of the better side in all but a few small ones of these.
+bool deep_four_lanes(int rs, int n, int H, int D, int64_t samples) {
+  const int run = std::max(1, n - 1), lanes = run & 1 ? 4 : run & 2 ? 2 : 1;
+  const int e = ((H + run - 1) / run + lanes - 1) / lanes, many = H > 32;
+  if (rs == 8) {
+    if (samples >= 16384) return D < 4 || n >= 8 + 3 * e / 2 - 8 * many;
+    return samples >= 8192 ? n >= 2 + 2 * e - 4 * many
+                           : n >= 6 + 3 * e - 2 * many + (D == 4 ? 3 : 0);
+  }
+  if (samples >= 16384) return D == 4 ? many && n < 24 : H > 24 || n >= 6 || (D == 2 && H <= 8);
+  return samples >= 8192 ? many || n >= 10 : n >= 12 + e - 2 * many;
+}
+
 template <typename real>
 tnvan_status run_sample(tnvan_net *net, const float *uniforms, int8_t *spins, void *logq,
                         hipStream_t st) {
@@ -1552,15 +1579,16 @@ tnvan_status run_sample(tnvan_net *net, const float *uniforms, int8_t *spins, vo
     int64_t maxB = 0;
     for (int q = 0; q < net->n_inst; ++q) maxB = std::max(maxB, net->nkey[q]);
     ProfScope ps(net, TNVAN_KERNEL_SAMPLE, st);
-    // small networks: four lanes per sample
     bool small = true;
-    int max_n = 1, max_D = 1;
+    int max_n = 1, max_H = 0, max_D = 1;
     for (auto &m : net->mi) {
-      if (m.n > kDeep4MaxN || m.H > kDeep4MaxH) small = false;
+      if (m.n > kDeepSmallN || m.H > kDeepSmallH) small = false;
       max_n = std::max(max_n, (int)m.n);
+      max_H = std::max(max_H, (int)m.H);
       max_D = std::max(max_D, (int)m.D);
     }
-    HIPCHK(launch_sample_deep<real>(a, net->n_inst, maxB, small, max_n, max_D, st));
+    const int lanes = !small ? 64 : deep_four_lanes(net->rs(), max_n, max_H, max_D, net->B_total) ? 4 : 16;
+    HIPCHK(launch_sample_deep<real>(a, net->n_inst, maxB, lanes, max_n, max_D, st));
     return TNVAN_OK;
   }
   if (net->h0) {

@@ -194,16 +194,15 @@ template <typename real>
 hipError_t launch_sample_h0(const SampleArgs<real> &a, int n_inst, int64_t max_B, int max_n,
                             hipStream_t st);
 
-// Deeper networks (some instance with D > 1 hidden layers): one wave per
-// sample for every instance, a lane owning hidden units lane + 64 kk and
-// positions lane + 64 jj; the completed tanh values of each layer in LDS.
-// small (every instance |W| <= kDeep4MaxN and H <= kDeep4MaxH): four lanes
-// per sample instead, 16 samples per wave.  max_n, max_D: largest |W| and
-// most layers.
+// Deeper networks (some instance with D > 1 hidden layers): `lanes` per
+// sample for every instance.  64: a wave, a lane owning hidden units lane + 64
+// kk and positions lane + 64 jj, the completed tanh values of each layer in
+// LDS.  16 or 4: every instance |W| <= kDeepSmallN and H <= kDeepSmallH, four
+// or 16 samples per wave.  max_n, max_D: largest |W| and most layers.
 constexpr int kDeepMaxN = 256, kDeepMaxH = 256, kDeepMaxD = 4;
-constexpr int kDeep4MaxN = 128, kDeep4MaxH = 64;
+constexpr int kDeepSmallN = 128, kDeepSmallH = 64;
 template <typename real>
-hipError_t launch_sample_deep(const SampleArgs<real> &a, int n_inst, int64_t max_B, bool small,
+hipError_t launch_sample_deep(const SampleArgs<real> &a, int n_inst, int64_t max_B, int lanes,
                               int max_n, int max_D, hipStream_t st);
 
 // Matrix-core sampler (FP32): one wave per 16 samples of one instance.
