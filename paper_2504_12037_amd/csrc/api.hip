@@ -219,7 +219,10 @@ struct tnvan_net {
     int64_t max_B = 0;
     DBuf steps, ti, tc, ts, list, u_off, f_off, cpart_off, U, fabp, cpart, ckpt;
   } c64;
-  bool on_chain(int q) const { return use_chain[q] || use_c64[q]; }
+  // some other instance runs step by step, and the FP64 chains only beside a
+  // batch large enough (c64_on, set_batch)
+  bool c64_rest = false, c64_on = true;
+  bool on_chain(int q) const { return use_chain[q] || (use_c64[q] && c64_on); }
   DBuf cinst, chains, csteps, Tp, Tt, Tb, fld_wr, fld_J32, hR32;
   ChainLim lim_fwd{}, lim_bwd{};
   DBuf Tl, Tbl, cedges, ckpt;
@@ -391,7 +394,7 @@ bool choose_tiles(tnvan_net *net, bool bwd, int req = 0) {
   auto worst_of = [&](int S, bool glob) {
     size_t worst = 0;
     for (size_t q = 0; q < net->P.insts.size(); ++q)
-      if (!net->on_chain((int)q))
+      if (!net->use_chain[q] && (!net->use_c64[q] || net->c64_rest))
         worst = std::max(worst, contract_lds_bytes(net->P.insts[q], S, bwd, glob, net->rs()));
     return worst;
   };
@@ -590,6 +593,10 @@ tnvan_status set_batch(tnvan_net *net, const int64_t *n_samples) {
   net->tc_bwd.key.clear();
   net->tc_mom.key.clear();
   net->ran_fwd = net->ran_bwd = 0;
+  int64_t chain64 = 0;
+  for (int q = 0; q < net->n_inst; ++q)
+    if (net->use_c64[q]) chain64 += key[q];
+  net->c64_on = !net->c64_rest || chain64 >= kChain64Batch;
   net->skey.clear();
   net->ckey.clear();
   return TNVAN_OK;
@@ -1194,7 +1201,7 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
   return TNVAN_OK;
 }
 bool any_c64(const tnvan_net *net) {
-  return std::count(net->use_c64.begin(), net->use_c64.end(), 1) > 0;
+  return net->c64_on && std::count(net->use_c64.begin(), net->use_c64.end(), 1) > 0;
 }
 
 E1Args e1_args(tnvan_net *net, const int8_t *spins, double *e1) {
@@ -2202,7 +2209,7 @@ tnvan_status net_signature(const tnvan_net *net, std::string &out) {
   const bool gen = (t.kinds & TNVAN_TUNE_GENERAL) != 0;
   out = std::string(prec[net->precision]) + (net->split ? "+split" : "") + "|k" +
         std::to_string(t.kinds) + (gen && net->sweep ? "+level" : gen && net->segments ? "+segments" : "") +
-        (any_c64(net) ? "+chain64" : "") + "|w" + std::to_string(maxw) + "|n" + std::to_string(net->n_inst);
+        (std::count(net->use_c64.begin(), net->use_c64.end(), 1) > 0 ? "+chain64" : "") + "|w" + std::to_string(maxw) + "|n" + std::to_string(net->n_inst);
   return TNVAN_OK;
 }
 
@@ -2492,13 +2499,29 @@ tnvan_status tnvan_build_network(const tnvan_instance *inst, int32_t n_inst,
     int dev = 0, maxlds = 65536;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
+    // (an instance too small for three launches joins where others make them:
+    // beside larger chains, or random graphs that it would else keep off the
+    // level kernels)
+    std::vector<int32_t> fit(n_inst, 0);
+    bool big = false, rest = false, level = true, wide = false, segs = true;
     for (int q = 0; q < n_inst; ++q) {
       const ChainInst &C = P.cinst[q];
-      if (!C.ok || !C.rq_ok || C.rtiles > kChain64Tiles || P.insts[q].nr < kChain64MinR ||
-          chain64_lds(true, C.max_steps) > (size_t)maxlds)
+      fit[q] = C.ok && C.rq_ok && C.rtiles <= kChain64Tiles && chain64_lds(true, C.max_steps) <= (size_t)maxlds;
+      if (fit[q]) {
+        big = big || P.insts[q].nr >= kChain64MinR;
         continue;
+      }
+      rest = true;
+      level = level && sweep_fits(P, q);
+      segs = segs && wide_fits(P, q);
+      wide = wide || P.insts[q].max_w > kTabW;
+    }
+    const bool steps = rest && !(level || (wide && segs));   // some stay step by step
+    for (int q = 0; q < n_inst; ++q) {
+      if (!fit[q] || !(big || (rest && !steps))) continue;
       net->use_c64[q] = 1;
-      net->c64.max_steps = std::max(net->c64.max_steps, (int)C.max_steps);
+      net->c64_rest = steps;
+      net->c64.max_steps = std::max(net->c64.max_steps, (int)P.cinst[q].max_steps);
     }
     std::vector<Chain64Step> cs;
     for (int q = 0; q < n_inst; ++q)

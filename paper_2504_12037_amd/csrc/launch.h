@@ -603,10 +603,20 @@ hipError_t launch_unary64(const Chain64Args &a, const int32_t *list, int n_list,
                           int64_t max_B, const int64_t *f_off, double *U, double *fabp,
                           hipStream_t st);
 hipError_t launch_chain64(const Chain64Args &a, bool wide, bool bwd, hipStream_t st);
-// instances with fewer remainder positions stay on the general kernel, one
-// launch instead of three (a 4x4 lattice, 12 positions, 1024 samples: 12
-// against 17 us for ln Z_R)
+// nets whose instances all have fewer remainder positions stay on the
+// general kernel, one launch instead of three (a 4x4 lattice, 12 positions,
+// 1024 samples: 12 against 17 us for ln Z_R); beside larger ones they take
+// part in the launches (lattices of 4x4, 6x6 and 8x8, 1000 samples: 34.7 us all
+// step by step, 38.9 us with the last alone here, 19.1 us all three); so they do
+// beside random graphs, which one step-by-step instance keeps off the level
+// kernels (a 4x4 lattice and a 256-spin graph, 1000 samples each: 381 -> 100 us)
 constexpr int kChain64MinR = 32;
+// in a net with instances on the step-by-step kernel the chains run here from
+// this many samples of their own on: below, that kernel's launch has room for
+// their tiles and these launches come after it (ln Z_R and adjoint of a
+// 64-spin SK model and a 16x16 lattice, 1000 samples each: 108 and 765 us step
+// by step, 122 and 846 us with the lattice here; 4000: 256 and 1814, 179 and 1070)
+constexpr int64_t kChain64Batch = 2048;
 
 // LDS bytes: shared part of a workgroup and per-wave part
 size_t chain_shared_lds(const ChainLim &L, bool bwd, bool bf16);
