@@ -420,10 +420,13 @@ __device__ inline void contract_tile(const ContractArgs<real> &a, const int tile
       // eight chains of every eighth position, added pairwise (the level
       // kernels' order: the same bits)
       double fs[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-      for (int p0 = 0; p0 < D.nr; p0 += 8)
+      int p0 = 0;
+      for (; p0 + 8 <= D.nr; p0 += 8)   // (no test per load: eight at a time)
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (p0 + j < D.nr) fs[j] += (double)fab[(p0 + j) * S + s];
+        for (int j = 0; j < 8; ++j) fs[j] += (double)fab[(p0 + j) * S + s];
+#pragma unroll
+      for (int j = 0; j < 7; ++j)
+        if (p0 + j < D.nr) fs[j] += (double)fab[(p0 + j) * S + s];
       double acc = D.log_const + (((fs[0] + fs[1]) + (fs[2] + fs[3])) + ((fs[4] + fs[5]) + (fs[6] + fs[7])));
       int64_t esum = 0;
       for (int t = 0; t < D.n_steps; ++t) {
