@@ -76,11 +76,13 @@ SAMPLE_FLOPS = 2 * HIDDEN * NW + NW * NW
 KERNEL_FLOPS = {
     "chain_fwd_2": FWD_STRIP5, "chain_fwd_1": FWD_STRIP4,
     "chain_bwd_2": 3 * FWD_STRIP5, "chain_bwd_1": 3 * FWD_STRIP4,
+    "chain_bwd_all": 3 * FWD_FLOPS,
     "made_grad": MADE_GRAD, "sample": SAMPLE_FLOPS,
 }
 KERNEL_NAMES = {
     "chain_fwd_2": "rchain_fwd_kernel<{mode}, 2, 2>", "chain_fwd_1": "rchain_fwd_kernel<{mode}, 1, 2>",
     "chain_bwd_2": "rchain_bwd_kernel<2, {split}, {kk}>", "chain_bwd_1": "rchain_meet_kernel<{split}>",
+    "chain_bwd_all": "rchain_bwd_all_kernel<{split}, {kk}>",
     "made_grad": "mgrad_kernel<2, 16>", "sample": "msample_kernel<2, false>",
 }
 PEAK_FP32 = 157.3e12       # MI355X FP32 (vector and 16x16x4 matrix), published
@@ -234,8 +236,8 @@ def main():
         torch.cuda.synchronize()
         del src, dst
     # eager launches; the library records HIP events around the launches of
-    # the dominant kernel of the step (the 2-tile adjoint chain kernel, by the
-    # rocprofv3 statistics) and of no other kernel, in every PROFILE_EVERY-th
+    # the dominant kernel of the step (the adjoint chain kernel of both widths,
+    # by the rocprofv3 statistics) and of no other kernel, in every PROFILE_EVERY-th
     # timed step: each timed launch adds two event records to the stream,
     # which serialise the queue around it (about 10 us per step)
     # FP32 path with split-BF16 products in the chain kernels (three BF16
@@ -246,7 +248,7 @@ def main():
               flags=Net.FLAG_PROFILE | (Net.FLAG_SPLIT_BF16 if split else 0) |
               (Net.FLAG_MARKERS if args.markers else 0),
               checkpoint_every=args.checkpoint_every)
-    net.profile_only(["chain_bwd_2"])
+    net.profile_only(["chain_bwd_all"])
     for k in range(nI):
         net.set_params(k, torch.from_numpy(S.made_init(nw, HIDDEN, 7 + k)))
     spins = torch.empty(nI * B * nw, dtype=torch.int8, device="cuda")
@@ -269,7 +271,7 @@ def main():
     e1 = torch.cuda.Event(enable_timing=True)
     e0.record(st)
     for i in range(args.steps):
-        net.profile_only(["chain_bwd_2"] if i % PROFILE_EVERY == 0 else [])
+        net.profile_only(["chain_bwd_all"] if i % PROFILE_EVERY == 0 else [])
         step()
     e1.record(st)
     torch.cuda.synchronize()
@@ -630,9 +632,9 @@ def kname(k, split, ck=1):
 def roofline_line(ktime, nI, split, ck=1):
     """The dominant kernel's live timing against its peak (None on paths
     without it, e.g. FP64)."""
-    if "chain_bwd_2" not in ktime:
+    dom = "chain_bwd_all"
+    if dom not in ktime:
         return None
-    dom = "chain_bwd_2"
     dom_avg = ktime[dom][0] / ktime[dom][1]
     achieved = KERNEL_FLOPS[dom] * nI * B / dom_avg
     # the peak of the units the products run on: BF16 dense for split

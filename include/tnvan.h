@@ -216,8 +216,11 @@ typedef enum {
   TNVAN_KERNEL_CHAIN_BWD_2 = 4,   /* ... 2 tiles */
   TNVAN_KERNEL_SAMPLE = 5,        /* matrix-core sampler */
   TNVAN_KERNEL_MADE_GRAD = 6,     /* fused REINFORCE backward (without its row reduction) */
-  TNVAN_KERNEL_CHAIN_FWD_ALL = 7, /* register-resident forward, every width in one persistent launch */
-  TNVAN_KERNEL_CHAIN_BWD_ALL = 8, /* register-resident adjoint, every width in one persistent launch */
+  /* register-resident forward and adjoint, every width in one launch: what
+   * nets of several widths run unless a width above is being timed, which
+   * puts each in a launch of its own */
+  TNVAN_KERNEL_CHAIN_FWD_ALL = 7,
+  TNVAN_KERNEL_CHAIN_BWD_ALL = 8,
   TNVAN_KERNEL_COUNT = 9
 } tnvan_kernel;
 

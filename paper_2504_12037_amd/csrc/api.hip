@@ -1286,6 +1286,7 @@ tnvan_status run_logz(tnvan_net *net, const int8_t *spins, double *logz, hipStre
         // (each width on its own only where each is timed)
         for (int gi = 0; gi < 3; ++gi) { c.pq_lo[gi] = net->rg_lo[gi]; c.pq_n[gi] = net->rg_n[gi]; }
         c.sg = net->sg;
+        ProfScope ps(net, TNVAN_KERNEL_CHAIN_FWD_ALL, st);
         HIPCHK(launch_rchain_fwd_all(c, st));
       } else {
         for (int gi = 0; gi < 3; ++gi) {
@@ -1406,6 +1407,7 @@ tnvan_status run_backward(tnvan_net *net, const int8_t *spins, const double *gra
       } else if (net->brg_n[0] > 0 && net->brg_n[1] > 0 &&
                  !timed(net, TNVAN_KERNEL_CHAIN_BWD_1, 2)) {
         for (int gi = 0; gi < 2; ++gi) { c.pq_lo[gi] = net->brg_lo[gi]; c.pq_n[gi] = net->brg_n[gi]; }
+        ProfScope ps(net, TNVAN_KERNEL_CHAIN_BWD_ALL, st);
         HIPCHK(launch_rchain_bwd_all(c, st));
       } else {
         for (int gi = 0; gi < 2; ++gi) {
