@@ -32,6 +32,7 @@
 
 #include "lanes.h"
 #include "launch.h"
+#include "msgbits.h"
 #include "sweep.h"
 #include "uload.h"
 
@@ -41,26 +42,6 @@ namespace {
 
 constexpr int kThreads = 64 * kSweepWaves;   // most
 
-template <typename real> struct SBits;
-template <> struct SBits<float> {
-  using U = uint32_t;
-  __device__ static U bits(float x) { return __float_as_uint(x); }
-  __device__ static int expo(U b) {
-    return (int)((b >> 23) & 0xffu) - 126;
-  }
-  // 2^-expo (a message's largest entry is below 2^2: no clamp)
-  __device__ static float scale(U b) { return __uint_as_float((253u << 23) - (b & 0x7f800000u)); }
-};
-template <> struct SBits<double> {
-  using U = unsigned long long;
-  __device__ static U bits(double x) { return (U)__double_as_longlong(x); }
-  __device__ static int expo(U b) {
-    return (int)((b >> 52) & 0x7ffull) - 1022;
-  }
-  __device__ static double scale(U b) {
-    return __longlong_as_double((long long)((2045ull << 52) - (b & (0x7ffull << 52))));
-  }
-};
 __device__ inline float sexp(float x) { return expf(x); }
 __device__ inline double sexp(double x) { return exp(x); }
 
@@ -186,14 +167,14 @@ struct UnitIn {
   int base[NI ? NI : 1], xs[NI ? NI : 1], code[NI ? NI : 1];
   real sc[NI ? NI : 1];
   template <int S>
-  __device__ void set(const Rec &r, const typename SBits<real>::U *mx, int s, int lw) {
+  __device__ void set(const Rec &r, const typename MsgBits<real>::U *mx, int s, int lw) {
 #pragma unroll
     for (int k = 0; k < NI; ++k) {
       const int m = r[9 + 2 * k];
       base[k] = r[8 + 2 * k] + ((lw >> (8 * k)) & 0xff);
       xs[k] = 1 << ((m >> 12) & 15);
       code[k] = m;
-      sc[k] = SBits<real>::scale(mx[(m >> 16) * S + s]);
+      sc[k] = MsgBits<real>::scale(mx[(m >> 16) * S + s]);
     }
   }
   template <int C> __device__ int at(int k) const { return base[k] + walk_at<C>(code[k]); }
@@ -214,8 +195,8 @@ __device__ inline void each(F f) {
 // T phi by the messages in turn and adds the last product of spin -1 to the
 // finished one of spin +1 with one rounding.  tp: T at the first pass.
 template <typename real, bool kJet, int S, int NI, int NC>
-__device__ inline typename SBits<real>::U unit_fwd(const Unit<real> &u, const real *T, const real tp[2],
-                                const typename SBits<real>::U *mx, const real *phi, real *arena,
+__device__ inline typename MsgBits<real>::U unit_fwd(const Unit<real> &u, const real *T, const real tp[2],
+                                const typename MsgBits<real>::U *mx, const real *phi, real *arena,
                                 int s, int lo, int lw) {
   using V = Val<real, kJet>;
   UnitIn<real, NI> in;
@@ -232,9 +213,9 @@ __device__ inline typename SBits<real>::U unit_fwd(const Unit<real> &u, const re
   in.template set<S>(u.r, mx, s, lw);
   const real ph0 = phi[2 * u.gpos * S + s], ph1 = phi[(2 * u.gpos + 1) * S + s];
   // (positive numbers compare as their bits)
-  typename SBits<real>::U lmax = 0;
+  typename MsgBits<real>::U lmax = 0;
   auto largest = [&](real x) {
-    const auto b = SBits<real>::bits(x);
+    const auto b = MsgBits<real>::bits(x);
     lmax = b > lmax ? b : lmax;
   };
   if (NI <= 1 && u.dense) {
@@ -297,10 +278,10 @@ __device__ inline typename SBits<real>::U unit_fwd(const Unit<real> &u, const re
 // plain (v[0]) and signed by each edge's output spin.
 template <typename real, int S, int NI, int NC>
 __device__ inline void unit_joint(const Unit<real> &u, const real *T, const real tp[2],
-                                  const typename SBits<real>::U *mx, const real *phi,
+                                  const typename MsgBits<real>::U *mx, const real *phi,
                                   const real *arena, real *scr, int s, int lo, int lw, bool on,
                                   real v[1 + kSweepEdges]) {
-  using FB = SBits<real>;
+  using FB = MsgBits<real>;
   UnitIn<real, NI> in;
   constexpr int E = 64 / S;
   const real *T0 = T + u.tpos + lo, *T1 = T0 + (1 << u.w);
@@ -368,7 +349,7 @@ __device__ inline void unit_dispatch(int n_in, int nc, F f) {
 // to the same place, and nothing branches on them.
 template <typename real, int kMode, bool kGlobal, int kLogS>
 __device__ inline void sweep_tile(const SweepArgs<real> &w, const int tile, char *smem) {
-  using FB = SBits<real>;
+  using FB = MsgBits<real>;
   using U = typename FB::U;
   constexpr bool kSeg = kMode == 3, kBwd = kMode == 1 || kSeg, kJet = kMode == 2;
   constexpr int kNC = 1 << sweep_walk(kMode, (int)sizeof(real));

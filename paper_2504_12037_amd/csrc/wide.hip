@@ -31,27 +31,13 @@
 
 #include "lanes.h"
 #include "launch.h"
+#include "msgbits.h"
 #include "sweep.h"
 #include "uload.h"
 
 namespace tnvan {
 
 namespace {
-
-template <typename real> struct WBits;
-template <> struct WBits<float> {
-  using U = uint32_t;
-  __device__ static U bits(float x) { return __float_as_uint(x); }
-  // 2^-expo (a message's largest entry is below 2^2: no clamp)
-  __device__ static float scale(U b) { return __uint_as_float((253u << 23) - (b & 0x7f800000u)); }
-};
-template <> struct WBits<double> {
-  using U = unsigned long long;
-  __device__ static U bits(double x) { return (U)__double_as_longlong(x); }
-  __device__ static double scale(U b) {
-    return __longlong_as_double((long long)((2045ull << 52) - (b & (0x7ffull << 52))));
-  }
-};
 
 constexpr int kT = kWideThreads, kR = kWideRegs;
 
@@ -75,7 +61,7 @@ __device__ inline const WideStep *find_step(const WideStep *steps, int w0, int &
 // rounded.
 template <typename real, bool kEnd>
 __device__ inline void wide_products(const WideArgs<real> &a, const WideStep *ws, int blk,
-                                     const real *arena, const typename WBits<real>::U *mx,
+                                     const real *arena, const typename MsgBits<real>::U *mx,
                                      const real *phi, const int (&o)[kR], real (&p0)[kR],
                                      real (&p1)[kR]) {
   const int w = uload(&ws->w), n_in = uload(&ws->n_in), gpos = uload(&ws->gpos);
@@ -123,7 +109,7 @@ __device__ inline void wide_products(const WideArgs<real> &a, const WideStep *ws
     const int32_t *tab = a.tab + uload(&in->idx);
     const int base = uload(&in->off) + (tab[threadIdx.x] | uload(tab + kT + kR + blk));
     const int xs = 1 << uload(&in->xbit);
-    const real sc = WBits<real>::scale(mx[uload(&in->step)]);
+    const real sc = MsgBits<real>::scale(mx[uload(&in->step)]);
     real m0[kR], m1[kR];
 #pragma unroll
     for (int r = 0; r < kR; ++r) {
@@ -165,7 +151,7 @@ __device__ inline void wide_entries(const WideArgs<real> &a, const WideStep *ws,
 // forward: out[o] = sum_x T[x, o] phi[x] prod_k m_k
 template <typename real>
 __global__ __launch_bounds__(kT) void wide_fwd_kernel(WideArgs<real> a) {
-  using FB = WBits<real>;
+  using FB = MsgBits<real>;
   using U = typename FB::U;
   __shared__ U sh[kT / 64];
   real *mem = a.mem + (int64_t)blockIdx.y * a.stride;
@@ -200,7 +186,7 @@ __global__ __launch_bounds__(kT) void wide_fwd_kernel(WideArgs<real> a) {
 // scaled entry
 template <typename real>
 __global__ __launch_bounds__(kT) void wide_bwd_kernel(WideArgs<real> a) {
-  using FB = WBits<real>;
+  using FB = MsgBits<real>;
   using U = typename FB::U;
   __shared__ real c[2 << kWideChunk];
   __shared__ real sums[(1 + kWideEdges) * (kT / 64)];
@@ -312,7 +298,7 @@ __global__ __launch_bounds__(kT) void wide_bwd_kernel(WideArgs<real> a) {
 // the rho of inputs whose sums were split over workgroups
 template <typename real>
 __global__ __launch_bounds__(kT) void wide_fin_kernel(WideArgs<real> a) {
-  using FB = WBits<real>;
+  using FB = MsgBits<real>;
   using U = typename FB::U;
   real *mem = a.mem + (int64_t)blockIdx.y * a.stride;
   const U *mx = reinterpret_cast<const U *>(mem + a.state);
