@@ -316,7 +316,8 @@ tnvan_status tnvan_sample(tnvan_net *net, const int64_t *n_samples,
  *   spins  dev int8 [sum n_samples * |W|] (layout as tnvan_sample)
  *   logz   dev double out [sum n_samples]
  *   e1     dev double out [sum n_samples], or NULL (not computed); FP64 in
- *          every precision, the W-W terms in edge order, then the fields */
+ *          every precision, four sums of every fourth term (the W-W terms in
+ *          edge order, then the fields) added pairwise */
 tnvan_status tnvan_logz_batch(tnvan_net *net, const int64_t *n_samples,
                               const int8_t *spins, double *logz, double *e1, void *stream);
 

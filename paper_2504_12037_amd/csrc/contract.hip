@@ -1,7 +1,10 @@
 // Batched conditional log-partition function of the remainder and its
-// adjoint (Sec. 2, Eqs. 2-4): programs with grouped dense steps, and tiles
-// above eight samples; other single-spin programs run the level kernels
-// (sweep.hip), those with scopes above 14 in segments (wide.hip).
+// adjoint (Sec. 2, Eqs. 2-4): programs with grouped dense steps, every general
+// instance of a net that holds one, tiles above eight samples, and graphs whose
+// level schedule does not fit the LDS (the adjoint of a 512-spin random
+// 3-regular graph at scopes of 13, in FP64 of 12).  Other single-spin programs
+// run the level kernels (sweep.hip), nets with scopes above 14 segments
+// (wide.hip).
 //
 // One workgroup (256 threads) contracts a tile of S samples of one instance
 // through every elimination step of the compiled program.  Work items of a
