@@ -166,9 +166,9 @@ typedef struct {
    * work queue, the costliest first (0: the default, 1) */
   int32_t launch_mode;
   /* upper bound in MiB on the general kernel's device arenas of one call, and
-   * on the adjoint's checkpoints of FP64 chains (0: the default budget, half
-   * of the device memory that is free or held by them, at most 96 GiB); a
-   * batch that exceeds it runs in chunks.  Not timed by the autotuner, which keeps
+   * on the unary factors and the adjoint's checkpoints of FP64 chains, each (0:
+   * the default budget, half of the device memory that is free or held by
+   * them, at most 96 GiB); a batch that exceeds it runs in chunks.  Not timed by the autotuner, which keeps
    * the value in effect. */
   int32_t arena_limit_mib;
   int32_t reserved[1];

@@ -214,7 +214,11 @@ struct tnvan_net {
   std::vector<int32_t> use_c64;
   struct Chains64 {
     std::vector<int64_t> key;
-    int lo[3] = {0, 0, 0}, n[3] = {0, 0, 0};
+    // samples that a pass takes of every instance, as many as the arena budget
+    // has room for their unary factors; its tasks by width (1, 2, 4 tiles)
+    struct Pass { int lo[3], n[3]; };
+    std::vector<Pass> pass;
+    int64_t win = 0;
     int n_list = 0, max_chunks = 0, max_steps = 0, ck_tiles = 1;
     int64_t max_B = 0;
     DBuf steps, ti, tc, ts, list, u_off, f_off, cpart_off, U, fabp, cpart, ckpt;
@@ -1093,9 +1097,17 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
     if (tnvan_status s = quiesce(net)) return s;
     std::vector<int32_t> ti, tc, ts, list;
     std::vector<int64_t> uo(net->n_inst, 0), fo(net->n_inst, 0), co(net->n_inst, 0);
-    int64_t ut = 0, ft = 0, ct = 0;
+    int64_t ut = 0, ft = 0, ct = 0, row = 0;
     c.max_chunks = 0;
     c.max_B = 0;
+    for (int q = 0; q < net->n_inst; ++q) {
+      if (!net->use_c64[q]) continue;
+      c.max_B = std::max(c.max_B, net->nkey[q]);
+      if (net->nkey[q] > 0) row += net->P.insts[q].nr;
+    }
+    const int groups = (int)((c.max_B + 15) / 16);
+    const int cap = arena_cap(net, row * 16 * (int64_t)sizeof(double), groups, c.U.bytes);
+    c.win = 16 * (int64_t)(cap ? cap : std::max(groups, 1));
     for (int q = 0; q < net->n_inst; ++q) {
       if (!net->use_c64[q]) continue;
       const int64_t B = net->nkey[q];
@@ -1104,27 +1116,32 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
       uo[q] = ut;
       fo[q] = ft;
       co[q] = ct;
-      ut += (int64_t)nr * B;
+      ut += (int64_t)nr * std::min(B, c.win);
       ft += (int64_t)nch * B;
       ct += (int64_t)net->P.cinst[q].n_chains * B;
       c.max_chunks = std::max(c.max_chunks, nch);
-      c.max_B = std::max(c.max_B, B);
     }
-    for (int gi = 2; gi >= 0; --gi) {
-      c.lo[gi] = (int)ti.size();
-      for (int q : list) {
-        const ChainInst &C = net->P.cinst[q];
-        for (int64_t b = 0; b < net->nkey[q]; b += 16)
-          for (int k = 0; k < C.n_chains; ++k)
-            if (net->P.chains[C.chain_off + k].rt == 1 << gi) {
-              ti.push_back(q);
-              tc.push_back(k);
-              ts.push_back((int32_t)b);
-            }
+    c.pass.clear();
+    c.ck_tiles = 1;
+    for (int64_t w0 = 0; w0 < c.max_B; w0 += c.win) {
+      tnvan_net::Chains64::Pass ps{};
+      for (int gi = 2; gi >= 0; --gi) {
+        ps.lo[gi] = (int)ti.size();
+        for (int q : list) {
+          const ChainInst &C = net->P.cinst[q];
+          for (int64_t b = w0; b < std::min(net->nkey[q], w0 + c.win); b += 16)
+            for (int k = 0; k < C.n_chains; ++k)
+              if (net->P.chains[C.chain_off + k].rt == 1 << gi) {
+                ti.push_back(q);
+                tc.push_back(k);
+                ts.push_back((int32_t)b);
+              }
+        }
+        ps.n[gi] = (int)ti.size() - ps.lo[gi];
       }
-      c.n[gi] = (int)ti.size() - c.lo[gi];
+      if (ps.n[1] > 0) c.ck_tiles = 2;
+      c.pass.push_back(ps);
     }
-    c.ck_tiles = c.n[1] > 0 ? 2 : 1;
     HIPCHK(upload(c.ti, ti));
     HIPCHK(upload(c.tc, tc));
     HIPCHK(upload(c.ts, ts));
@@ -1166,32 +1183,38 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
   a.grad = grad;
   a.partial = partial;
   a.inst_partial_off = poff;
-  {
-    Phase ph(net, "tnvan/boundary");
-    HIPCHK(launch_unary64(a, c.list.as<int32_t>(), c.n_list, c.max_chunks, c.max_B,
-                          c.f_off.as<int64_t>(), c.U.as<double>(), c.fabp.as<double>(), st));
-  }
-  // chains of four tiles, then those of two and one.  The adjoint keeps the
-  // states of every step of a task: where those of all tasks exceed the
-  // arena budget they run in passes over the same checkpoints (a launch with
-  // its passes one after the other; each task's arithmetic is its own)
-  for (const bool wide : {true, false}) {
-    const int lo = wide ? c.lo[2] : c.lo[1], n = wide ? c.n[2] : c.n[1] + c.n[0];
-    if (n <= 0) continue;
-    a.ck_tiles = wide ? 4 : c.ck_tiles;
-    int pass = n;
-    if (bwd) {
-      const int64_t per = (int64_t)a.ck_tiles * c.max_steps * 256 * sizeof(double);
-      if ((size_t)(per * n) > c.ckpt.bytes || net->tune.arena_limit_mib > 0)
-        if (const int cap = arena_cap(net, per, n, c.ckpt.bytes)) pass = cap;
-      HIPCHK(c.ckpt.ensure((size_t)per * pass));
-      a.ckpt = c.ckpt.as<double>();
+  a.win = c.win;
+  for (size_t w = 0; w < c.pass.size(); ++w) {
+    const auto &ps = c.pass[w];
+    a.w0 = (int64_t)w * c.win;
+    {
+      Phase ph(net, "tnvan/boundary");
+      HIPCHK(launch_unary64(a, c.list.as<int32_t>(), c.n_list, c.max_chunks,
+                            std::min(c.win, c.max_B - a.w0), c.f_off.as<int64_t>(),
+                            c.U.as<double>(), c.fabp.as<double>(), st));
     }
-    for (int t = 0; t < n; t += pass) {
-      a.task_base = lo + t;
-      a.n_tasks = std::min(pass, n - t);
-      a.n_two = wide ? 0 : std::min(std::max(c.n[1] - t, 0), a.n_tasks);
-      HIPCHK(launch_chain64(a, wide, bwd, st));
+    // chains of four tiles, then those of two and one.  The adjoint keeps the
+    // states of every step of a task: where those of all tasks exceed the
+    // arena budget they run in launches over the same checkpoints, one after
+    // the other (each task's arithmetic is its own)
+    for (const bool wide : {true, false}) {
+      const int lo = wide ? ps.lo[2] : ps.lo[1], n = wide ? ps.n[2] : ps.n[1] + ps.n[0];
+      if (n <= 0) continue;
+      a.ck_tiles = wide ? 4 : c.ck_tiles;
+      int some = n;
+      if (bwd) {
+        const int64_t per = (int64_t)a.ck_tiles * c.max_steps * 256 * sizeof(double);
+        if ((size_t)(per * n) > c.ckpt.bytes || net->tune.arena_limit_mib > 0)
+          if (const int cap = arena_cap(net, per, n, c.ckpt.bytes)) some = cap;
+        HIPCHK(c.ckpt.ensure((size_t)per * some));
+        a.ckpt = c.ckpt.as<double>();
+      }
+      for (int t = 0; t < n; t += some) {
+        a.task_base = lo + t;
+        a.n_tasks = std::min(some, n - t);
+        a.n_two = wide ? 0 : std::min(std::max(ps.n[1] - t, 0), a.n_tasks);
+        HIPCHK(launch_chain64(a, wide, bwd, st));
+      }
     }
   }
   if (logz)
@@ -3249,6 +3272,7 @@ tnvan_status tnvan_set_tuning(tnvan_net *net, const tnvan_tuning *in) {
   net->tc_bwd.key.clear();
   net->ran_fwd = net->ran_bwd = 0;
   net->ckey.clear();
+  net->c64.key.clear();
   g_buf_gen.fetch_add(1);
   return TNVAN_OK;
 }

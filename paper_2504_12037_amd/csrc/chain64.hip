@@ -91,9 +91,9 @@ template <int CT> struct Spins { static constexpr int v = CT == 1 ? 4 : CT == 2 
 
 // unary factors of a group's positions of the lane's sample
 template <int GR>
-__device__ inline void load_u(const double *ub, int64_t B, const Chain64Step &sd, double (&u)[GR]) {
+__device__ inline void load_u(const double *ub, int64_t us, const Chain64Step &sd, double (&u)[GR]) {
 #pragma unroll
-  for (int j = 0; j < GR; ++j) u[j] = ub[(int64_t)(sd.gpos + (j < sd.g ? j : 0)) * B];
+  for (int j = 0; j < GR; ++j) u[j] = ub[(int64_t)(sd.gpos + (j < sd.g ? j : 0)) * us];
 }
 
 // diagonal of a group: the product of its spins' factors (1 for the
@@ -133,7 +133,7 @@ __device__ inline void product(const double (&t)[CT][CT][4], const double (&x)[C
 
 struct Wave {
   int i, q, c, lane, ls, lg;   // i: the task in its launch
-  int64_t b0, B;
+  int64_t b0, B, us;        // us: samples that a position of U holds
 };
 
 // The forward recursion of one chain, the state of every step to keep(t, x)
@@ -145,12 +145,12 @@ __device__ inline double forward(const Chain64Args &a, const Wave &k, const Inst
   constexpr int GR = Spins<CT>::v;
   const Chain64Step *cs = a.csteps + cd.cs_off;
   const int64_t b = k.b0 + k.ls;
-  const double *ub = a.U + a.u_off[k.q] + (b < k.B ? b : k.B - 1);
+  const double *ub = a.U + a.u_off[k.q] + ((b < k.B ? b : k.B - 1) - a.w0);
   double x[CT][4];
   const Chain64Step s0 = uload(cs);
   {
     double u[GR];
-    load_u<GR>(ub, k.B, s0, u);
+    load_u<GR>(ub, k.us, s0, u);
     diag<CT, GR>(u, s0.g, k.lg, x);
   }
   esum = 0;
@@ -162,7 +162,7 @@ __device__ inline double forward(const Chain64Args &a, const Wave &k, const Inst
     const bool last = t == cd.n_steps - 1;
     const Chain64Step sn = uload(cs + (last ? t : t + 1));
     load_t<CT>(a.T + sn.t_off, sn, k.ls, k.lg, tn);
-    load_u<GR>(ub, k.B, uload(cs + (t + 2 < cd.n_steps ? t + 2 : cd.n_steps - 1)), un);
+    load_u<GR>(ub, k.us, uload(cs + (t + 2 < cd.n_steps ? t + 2 : cd.n_steps - 1)), un);
     keep(t, x);
     d4 acc[CT];
     product<CT>(tc, x, acc);
@@ -189,7 +189,7 @@ __device__ inline double forward(const Chain64Args &a, const Wave &k, const Inst
   };
   double tA[CT][CT][4], tB[CT][CT][4], uA[GR], uB[GR];
   load_t<CT>(a.T + s0.t_off, s0, k.ls, k.lg, tA);
-  load_u<GR>(ub, k.B, uload(cs + (cd.n_steps > 1 ? 1 : 0)), uA);
+  load_u<GR>(ub, k.us, uload(cs + (cd.n_steps > 1 ? 1 : 0)), uA);
   for (int t = 0;; t += 2) {
     if (step(t, tA, uA, tB, uB)) break;
     if (step(t + 1, tB, uB, tA, uA)) break;
@@ -209,6 +209,7 @@ __device__ inline bool wave_task(const Chain64Args &a, Wave &k) {
   k.c = uload(a.task_chain + a.task_base + i);
   k.b0 = uload(a.task_start + a.task_base + i);
   k.B = uload(a.inst_B + k.q);
+  k.us = k.B < a.win ? k.B : a.win;
   return true;
 }
 
@@ -275,7 +276,7 @@ __device__ inline void bwd_task(const Chain64Args &a, const Wave &k, char *base)
   const int8_t *sp = a.spins + a.inst_spin_off[k.q] + bc * D.nw;
   const bool bits = D.nw <= 128;
   const SpinBits sb = bits ? load_bits_row(sp, D.nw) : SpinBits{{0u, 0u, 0u, 0u}};
-  const double *ub = a.U + a.u_off[k.q] + bc;
+  const double *ub = a.U + a.u_off[k.q] + (bc - a.w0);
   double *prow = a.partial + a.inst_partial_off[k.q] + (k.b0 / CW) * (int64_t)D.n_partial;
   // R of the closing entry (state 0: register 0 of lane group 0)
   double R[CT][4];
@@ -294,7 +295,7 @@ __device__ inline void bwd_task(const Chain64Args &a, const Wave &k, char *base)
 #pragma unroll
   for (int xt = 0; xt < CT; ++xt) A[xt] = *slot(cd.n_steps - 1, xt);
   load_t<CT>(a.T + c.t_off, c, ls, lg, tf);
-  load_u<GR>(ub, k.B, c, u);
+  load_u<GR>(ub, k.us, c, u);
   for (int t = cd.n_steps - 1; t >= 0; --t) {
     const int tp = t > 0 ? t - 1 : 0;
     const Chain64Step cn = uload(cs + tp);
@@ -389,7 +390,7 @@ __device__ inline void bwd_task(const Chain64Args &a, const Wave &k, char *base)
     for (int xt = 0; xt < CT; ++xt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) R[xt][r] = d[xt][r] * lam[xt][r] * sc;
-    load_u<GR>(ub, k.B, cn, u);
+    load_u<GR>(ub, k.us, cn, u);
     c = cn;
     __builtin_amdgcn_wave_barrier();
   }
@@ -407,9 +408,9 @@ __global__ __launch_bounds__(64 * kWaves, kWide ? 1 : 2) void chain64_bwd_kernel
   else bwd_task<1>(a, k, base);
 }
 
-// Unary factors u of every (position, sample): exp(-2 beta |f|), its sign bit
-// set for f < 0, and the sums of beta |f| per run of kUnaryChunk positions; one
-// thread per (sample, run).  f is the field plus the W-R couplings times the
+// Unary factors u of every (position, sample of the pass): exp(-2 beta |f|),
+// its sign bit set for f < 0, and the sums of beta |f| per run of kUnaryChunk
+// positions; one thread per (sample, run).  f is the field plus the W-R couplings times the
 // width-set spins (Sec. 2).
 __global__ __launch_bounds__(256) void unary64_kernel(Chain64Args a, const int32_t *list,
                                                       const int64_t *f_off, double *U,
@@ -417,9 +418,10 @@ __global__ __launch_bounds__(256) void unary64_kernel(Chain64Args a, const int32
   const int q = list[blockIdx.z];
   const InstDesc D = a.inst[q];
   const int64_t B = a.inst_B[q];
-  const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, b = a.w0 + i;
   const int p0 = blockIdx.y * kUnaryChunk;
-  if (p0 >= D.nr || b >= B) return;
+  if (p0 >= D.nr || b >= B || i >= a.win) return;
+  const int64_t us = B < a.win ? B : a.win;
   const int p1 = p0 + kUnaryChunk < D.nr ? p0 + kUnaryChunk : D.nr;
   const int8_t *sp = a.spins + a.inst_spin_off[q] + b * D.nw;
   double *Uq = U + a.u_off[q];
@@ -430,7 +432,7 @@ __global__ __launch_bounds__(256) void unary64_kernel(Chain64Args a, const int32
     for (int k = k0; k < k1; ++k)
       f += a.fld_J[D.fld_nnz_off + k] * (double)sp[a.fld_w[D.fld_nnz_off + k]];
     const double af = D.beta * fabs(f), sm = exp(-2.0 * af);
-    Uq[(int64_t)p * B + b] = f >= 0.0 ? sm : -sm;
+    Uq[(int64_t)p * us + i] = f >= 0.0 ? sm : -sm;
     fab += af;
   }
   fabp[f_off[q] + (int64_t)blockIdx.y * B + b] = fab;

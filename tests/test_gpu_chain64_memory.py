@@ -46,6 +46,23 @@ def test_checkpoints_belong_to_the_adjoint_and_its_budget():
     assert all(torch.equal(x, y) for x, y in zip(*outs))
 
 
+def test_unary_factors_stay_within_the_budget():
+    # 224 remainder spins, 8 bytes each: 36 MB for the whole batch
+    from paper_2504_12037_amd import Net
+    inst = S.c2_lattice(1.0, 0)
+    sp = torch.from_numpy(S.uniform_spins(B, inst.n_width, 3)).cuda().reshape(-1)
+    net = Net([inst], precision="fp64")
+    want = net.logz(sp, B).clone()
+    net = Net([inst], precision="fp64")
+    net.set_tuning(arena_limit_mib=1)
+    lz, grown = _grown(lambda: net.logz(sp, B))
+    assert torch.equal(lz, want)
+    assert grown < 18 << 20, grown
+    # the limit taken back: one pass again, the same bits
+    net.set_tuning()
+    assert torch.equal(net.logz(sp, B), want)
+
+
 def test_passes_across_the_widths():
     # strips of one, two and four tiles and an empty instance beside them, one
     # MiB: passes that end among the two-tile chains, and four-tile ones alone
@@ -61,4 +78,5 @@ def test_passes_across_the_widths():
         net = Net(insts, precision="fp64")
         net.set_tuning(arena_limit_mib=limit)
         outs.append([x.clone() for x in net.logz_and_backward(sp, g, Bs)])
+        assert torch.equal(net.logz(sp, Bs), outs[-1][0])
     assert all(torch.equal(x, y) for x, y in zip(*outs))
