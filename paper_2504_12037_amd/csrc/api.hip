@@ -1183,7 +1183,7 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
   a.grad = grad;
   a.partial = partial;
   a.inst_partial_off = poff;
-  a.win = c.win;
+  a.win = (int32_t)std::min<int64_t>(c.win, INT32_MAX);
   for (size_t w = 0; w < c.pass.size(); ++w) {
     const auto &ps = c.pass[w];
     a.w0 = (int64_t)w * c.win;

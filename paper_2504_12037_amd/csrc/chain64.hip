@@ -91,7 +91,7 @@ template <int CT> struct Spins { static constexpr int v = CT == 1 ? 4 : CT == 2 
 
 // unary factors of a group's positions of the lane's sample
 template <int GR>
-__device__ inline void load_u(const double *ub, int64_t us, const Chain64Step &sd, double (&u)[GR]) {
+__device__ inline void load_u(const double *ub, int us, const Chain64Step &sd, double (&u)[GR]) {
 #pragma unroll
   for (int j = 0; j < GR; ++j) u[j] = ub[(int64_t)(sd.gpos + (j < sd.g ? j : 0)) * us];
 }
@@ -133,7 +133,8 @@ __device__ inline void product(const double (&t)[CT][CT][4], const double (&x)[C
 
 struct Wave {
   int i, q, c, lane, ls, lg;   // i: the task in its launch
-  int64_t b0, B, us;        // us: samples that a position of U holds
+  int64_t b0, B;
+  int us;                   // samples that a position of U holds
 };
 
 // The forward recursion of one chain, the state of every step to keep(t, x)
@@ -209,7 +210,7 @@ __device__ inline bool wave_task(const Chain64Args &a, Wave &k) {
   k.c = uload(a.task_chain + a.task_base + i);
   k.b0 = uload(a.task_start + a.task_base + i);
   k.B = uload(a.inst_B + k.q);
-  k.us = k.B < a.win ? k.B : a.win;
+  k.us = (int)k.B < a.win ? (int)k.B : a.win;   // (32 bits: a scalar minimum)
   return true;
 }
 
@@ -421,7 +422,7 @@ __global__ __launch_bounds__(256) void unary64_kernel(Chain64Args a, const int32
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, b = a.w0 + i;
   const int p0 = blockIdx.y * kUnaryChunk;
   if (p0 >= D.nr || b >= B || i >= a.win) return;
-  const int64_t us = B < a.win ? B : a.win;
+  const int us = (int)B < a.win ? (int)B : a.win;
   const int p1 = p0 + kUnaryChunk < D.nr ? p0 + kUnaryChunk : D.nr;
   const int8_t *sp = a.spins + a.inst_spin_off[q] + b * D.nw;
   double *Uq = U + a.u_off[q];

@@ -586,7 +586,8 @@ struct Chain64Args {
   int32_t task_base, n_tasks, n_two;   // n_two: its first tasks, two tiles each
   int32_t max_steps;                // of the longest chain
   int32_t ck_tiles;                 // tiles of a checkpoint
-  int64_t w0, win;                  // samples of the pass: w0 .. w0 + win - 1
+  int32_t win;                      // samples of the pass: w0 .. w0 + win - 1
+  int64_t w0;
   int32_t write_logz;
   const int64_t *inst_B, *inst_sample_off, *inst_spin_off, *cpart_off;
   const int8_t *spins;
