@@ -1184,6 +1184,25 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
   a.partial = partial;
   a.inst_partial_off = poff;
   a.win = (int32_t)std::min<int64_t>(c.win, INT32_MAX);
+  // chains of four tiles, then those of two and one.  The adjoint keeps the
+  // states of every step of a task: where those of a pass's tasks (the first
+  // has the most) exceed the arena budget they run in launches of `some` over
+  // the same checkpoints, one after the other (each task's arithmetic is its
+  // own)
+  int some[2] = {INT32_MAX, INT32_MAX};
+  size_t need = 0;
+  for (int wide = 0; wide < 2 && bwd && !c.pass.empty(); ++wide) {
+    const auto &ps = c.pass[0];
+    const int n = wide ? ps.n[2] : ps.n[1] + ps.n[0];
+    const int64_t per = (int64_t)(wide ? 4 : c.ck_tiles) * c.max_steps * 256 * sizeof(double);
+    if (n <= 0) continue;
+    some[wide] = n;
+    if ((size_t)(per * n) > c.ckpt.bytes || net->tune.arena_limit_mib > 0)
+      if (const int cap = arena_cap(net, per, n, c.ckpt.bytes)) some[wide] = cap;
+    need = std::max(need, (size_t)per * some[wide]);
+  }
+  HIPCHK(c.ckpt.ensure(need));
+  a.ckpt = c.ckpt.as<double>();
   for (size_t w = 0; w < c.pass.size(); ++w) {
     const auto &ps = c.pass[w];
     a.w0 = (int64_t)w * c.win;
@@ -1193,27 +1212,14 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
                             std::min(c.win, c.max_B - a.w0), c.f_off.as<int64_t>(),
                             c.U.as<double>(), c.fabp.as<double>(), st));
     }
-    // chains of four tiles, then those of two and one.  The adjoint keeps the
-    // states of every step of a task: where those of all tasks exceed the
-    // arena budget they run in launches over the same checkpoints, one after
-    // the other (each task's arithmetic is its own)
-    for (const bool wide : {true, false}) {
+    for (int wide = 1; wide >= 0; --wide) {
       const int lo = wide ? ps.lo[2] : ps.lo[1], n = wide ? ps.n[2] : ps.n[1] + ps.n[0];
-      if (n <= 0) continue;
       a.ck_tiles = wide ? 4 : c.ck_tiles;
-      int some = n;
-      if (bwd) {
-        const int64_t per = (int64_t)a.ck_tiles * c.max_steps * 256 * sizeof(double);
-        if ((size_t)(per * n) > c.ckpt.bytes || net->tune.arena_limit_mib > 0)
-          if (const int cap = arena_cap(net, per, n, c.ckpt.bytes)) some = cap;
-        HIPCHK(c.ckpt.ensure((size_t)per * some));
-        a.ckpt = c.ckpt.as<double>();
-      }
-      for (int t = 0; t < n; t += some) {
+      for (int t = 0; t < n; t += a.n_tasks) {
         a.task_base = lo + t;
-        a.n_tasks = std::min(some, n - t);
+        a.n_tasks = std::min(some[wide], n - t);
         a.n_two = wide ? 0 : std::min(std::max(ps.n[1] - t, 0), a.n_tasks);
-        HIPCHK(launch_chain64(a, wide, bwd, st));
+        HIPCHK(launch_chain64(a, wide != 0, bwd, st));
       }
     }
   }
