@@ -98,13 +98,16 @@ __device__ inline void load_u(const double *ub, int us, const Chain64Step &sd, d
 
 // diagonal of a group: the product of its spins' factors (1 for the
 // favoured value, |u| for the other; the sign bit of u favours -1, which a
-// factor too small for a double keeps as -0), zero past its states
+// factor too small for a double keeps as -0), zero past its states.  The sign
+// by the class of u, any of -inf, -normal, -denormal and -0: one comparison,
+// where the bit itself cost the adjoint of a 16x16 lattice, 1000 samples, 117
+// us against 113
 template <int CT, int GR>
 __device__ inline void diag(const double (&u)[GR], int g, int lg, double (&d)[CT][4]) {
   auto ph = [&](int j, bool minus) {
     if (j >= GR) return 1.0;
     const double v = u[j < GR ? j : 0];
-    return j < g ? (minus == (bool)__builtin_signbit(v) ? 1.0 : fabs(v)) : 1.0;
+    return j < g ? (minus == __builtin_amdgcn_class(v, 0x3C) ? 1.0 : fabs(v)) : 1.0;
   };
   const double fl = ph(0, lg & 1) * ph(1, lg & 2);
   double fr[4];
