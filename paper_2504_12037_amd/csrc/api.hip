@@ -1106,7 +1106,11 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
       if (net->nkey[q] > 0) row += net->P.insts[q].nr;
     }
     const int groups = (int)((c.max_B + 15) / 16);
-    const int cap = arena_cap(net, row * 16 * (int64_t)sizeof(double), groups, c.U.bytes);
+    // (small buffers are not put to the budget: the query of the free memory
+    // costs a net's first call 20 us)
+    const int64_t per = row * 16 * (int64_t)sizeof(double);
+    const int cap = per * groups > kChain64Small || net->tune.arena_limit_mib > 0
+                        ? arena_cap(net, per, groups, c.U.bytes) : 0;
     c.win = 16 * (int64_t)(cap ? cap : std::max(groups, 1));
     for (int q = 0; q < net->n_inst; ++q) {
       if (!net->use_c64[q]) continue;
@@ -1197,7 +1201,7 @@ tnvan_status run_chain64(tnvan_net *net, const int8_t *spins, bool bwd, const do
     const int64_t per = (int64_t)(wide ? 4 : c.ck_tiles) * c.max_steps * 256 * sizeof(double);
     if (n <= 0) continue;
     some[wide] = n;
-    if ((size_t)(per * n) > c.ckpt.bytes || net->tune.arena_limit_mib > 0)
+    if (per * n > std::max<int64_t>((int64_t)c.ckpt.bytes, kChain64Small) || net->tune.arena_limit_mib > 0)
       if (const int cap = arena_cap(net, per, n, c.ckpt.bytes)) some[wide] = cap;
     need = std::max(need, (size_t)per * some[wide]);
   }

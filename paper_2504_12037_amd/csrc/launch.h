@@ -619,6 +619,8 @@ constexpr int kChain64MinR = 32;
 // 64-spin SK model and a 16x16 lattice, 1000 samples each: 108 and 765 us step
 // by step, 122 and 846 us with the lattice here; 4000: 256 and 1814, 179 and 1070)
 constexpr int64_t kChain64Batch = 2048;
+// bytes below which their buffers are allocated without a look at the budget
+constexpr int64_t kChain64Small = (int64_t)64 << 20;
 
 // LDS bytes: shared part of a workgroup and per-wave part
 size_t chain_shared_lds(const ChainLim &L, bool bwd, bool bf16);
