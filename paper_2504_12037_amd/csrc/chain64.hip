@@ -98,16 +98,18 @@ __device__ inline void load_u(const double *ub, int us, const Chain64Step &sd, d
 
 // diagonal of a group: the product of its spins' factors (1 for the
 // favoured value, |u| for the other; the sign bit of u favours -1, which a
-// factor too small for a double keeps as -0), zero past its states.  The sign
-// by the class of u, any of -inf, -normal, -denormal and -0: one comparison,
-// where the bit itself cost the adjoint of a 16x16 lattice, 1000 samples, 117
-// us against 113
-template <int CT, int GR>
+// factor too small for a double keeps as -0), zero past its states.  kClass:
+// the sign by the class of u (-inf, -normal, -denormal or -0), one comparison,
+// which suits the reverse walk (the adjoint of a 16x16 lattice, 1000 samples,
+// 112 against 117 us) and not the recursion forward (an 8x8 one 18.9 against
+// 18.6)
+template <int CT, int GR, bool kClass>
 __device__ inline void diag(const double (&u)[GR], int g, int lg, double (&d)[CT][4]) {
   auto ph = [&](int j, bool minus) {
     if (j >= GR) return 1.0;
     const double v = u[j < GR ? j : 0];
-    return j < g ? (minus == __builtin_amdgcn_class(v, 0x3C) ? 1.0 : fabs(v)) : 1.0;
+    const bool neg = kClass ? __builtin_amdgcn_class(v, 0x3C) : (bool)__builtin_signbit(v);
+    return j < g ? (minus == neg ? 1.0 : fabs(v)) : 1.0;
   };
   const double fl = ph(0, lg & 1) * ph(1, lg & 2);
   double fr[4];
@@ -155,7 +157,7 @@ __device__ inline double forward(const Chain64Args &a, const Wave &k, const Inst
   {
     double u[GR];
     load_u<GR>(ub, k.us, s0, u);
-    diag<CT, GR>(u, s0.g, k.lg, x);
+    diag<CT, GR, false>(u, s0.g, k.lg, x);
   }
   esum = 0;
   double raw = 1.0;
@@ -182,7 +184,7 @@ __device__ inline double forward(const Chain64Args &a, const Wave &k, const Inst
     const int e = expo64(lanes_max<16, 64>(m));
     const double sc = pow2neg64(e);
     double d[CT][4];
-    diag<CT, GR>(uc, sn.g, k.lg, d);
+    diag<CT, GR, false>(uc, sn.g, k.lg, d);
 #pragma unroll
     for (int n = 0; n < CT; ++n)
 #pragma unroll
@@ -389,7 +391,7 @@ __device__ inline void bwd_task(const Chain64Args &a, const Wave &k, char *base)
       if (dst[r] >= 0) prow[dst[r]] = Q[r];
     const double sc = t > 0 ? pow2neg64(ex[tp * CW + ls]) : 0.0;
     double d[CT][4];
-    diag<CT, GR>(u, c.g, lg, d);
+    diag<CT, GR, true>(u, c.g, lg, d);
 #pragma unroll
     for (int xt = 0; xt < CT; ++xt)
 #pragma unroll
